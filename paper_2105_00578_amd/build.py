@@ -19,8 +19,11 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsphynx.so")
 ARCH = "gfx950"
 
-SOURCES = ["spmm.hip", "spmm_vec.hip", "setup.hip", "dense.hip", "split.hip", "quality.hip",
-           "adjoint.hip", "poly.hip", "refine.hip", "capi.hip"]
+# (source, object, extra flags); the vector-row products are one source built in
+# ten units (element type x epilogue), first because they take longest
+UNITS = [("spmm_vec.hip", f"spmm_vec_{p}.o", [f"-DSPHX_VEC_PART={p}"]) for p in range(10)]
+UNITS += [(f + ".hip", f + ".o", []) for f in
+          ("refine", "dense", "spmm", "capi", "setup", "quality", "split", "adjoint", "poly")]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -38,9 +41,10 @@ def hipcc() -> str:
     return p
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, name, extra = unit
+    obj = os.path.join(BUILD, name)
+    cmd = [hipcc(), *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {src}\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
@@ -49,9 +53,9 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    jobs = jobs or min(len(SOURCES), max(1, (os.cpu_count() or 4)))
+    jobs = jobs or min(len(UNITS), max(1, (os.cpu_count() or 4)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -139,7 +139,10 @@ int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
 
 // Padded blocks: n x ld with ld * sizeof(T) a multiple of 16 bytes (columns
 // m..ld-1 are padding).  Thread-per-row products with 16-byte vector loads.
-int padded_ld(int m, int elem_bytes);
+inline int padded_ld(int m, int elem_bytes) {
+  const int e = 16 / elem_bytes;
+  return (m + e - 1) / e * e;
+}
 
 // Events that bracket the kernels of one product: a single launch is stamped
 // by its own dispatch (start and end of execution); several launches are

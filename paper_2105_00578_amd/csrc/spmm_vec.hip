@@ -775,11 +775,6 @@ int dispatch_nv(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, const P
 
 }  // namespace
 
-int padded_ld(int m, int elem_bytes) {
-  const int e = 16 / elem_bytes;
-  return (m + e - 1) / e * e;
-}
-
 template <typename T>
 int vspmm_store(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, int m,
                 EpiStoreP<T> epi, hipStream_t s) {
@@ -794,8 +789,7 @@ int vspmm_residual(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, int 
     // a streaming pass forms the residual, the Jacobi step and the norms
     // (the fused residual epilogue keeps per-lane index reads and ran at
     // about two thirds of the store product's rate there)
-    int r = dispatch_nv<T, VStore>(g, plan, X, ld, EpiStoreP<T>{epi.LX, ld}, m, nullptr,
-                                   nullptr, s);
+    int r = vspmm_store<T>(g, plan, X, ld, m, EpiStoreP<T>{epi.LX, ld}, s);
     if (r != SPHX_OK) return r;
     return resid_stream<T>(g->n, X, ld, m, epi, norm_partials, n_norm_blocks, s);
   }
@@ -818,19 +812,34 @@ int vspmm_poly(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, int m,
   return dispatch_nv<T, VPoly>(g, plan, X, ld, epi, m, nullptr, nullptr, s, ev);
 }
 
-#define SPHX_VINST(T)                                                                       \
-  template int vspmm_store<T>(sphx_graph *, const SpmmPlan &, const T *, int, int,         \
-                              EpiStoreP<T>, hipStream_t);                                  \
-  template int vspmm_residual<T>(sphx_graph *, const SpmmPlan &, const T *, int, int,      \
-                                 EpiResidualP<T>, double *, int *, hipStream_t);           \
-  template int vspmm_shiftdot<T>(sphx_graph *, const SpmmPlan &, const T *, int, int,      \
-                                 EpiShiftDotP<T>, double *, int *, hipStream_t);           \
-  template int vspmm_cheb<T>(sphx_graph *, const SpmmPlan &, const T *, int, int,          \
-                             EpiChebP<T>, hipStream_t, const LaunchEvents *);              \
-  template int vspmm_poly<T>(sphx_graph *, const SpmmPlan &, const T *, int, int,          \
-                             EpiPolyP<T>, hipStream_t, const LaunchEvents *);
-SPHX_VINST(float)
-SPHX_VINST(double)
-#undef SPHX_VINST
+// One epilogue and element type per translation unit (the build compiles
+// this file once for each SPHX_VEC_PART, so that the units build in parallel):
+// parts 0..4 are the FP32 epilogues, 5..9 the FP64 ones.
+#ifndef SPHX_VEC_PART
+#error "compile with -DSPHX_VEC_PART=0..9"
+#endif
+#if SPHX_VEC_PART < 5
+using PartT = float;
+#else
+using PartT = double;
+#endif
+#if SPHX_VEC_PART % 5 == 0
+template int vspmm_store<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                                EpiStoreP<PartT>, hipStream_t);
+#elif SPHX_VEC_PART % 5 == 1
+extern template int vspmm_store<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                                       EpiStoreP<PartT>, hipStream_t);
+template int vspmm_residual<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                                   EpiResidualP<PartT>, double *, int *, hipStream_t);
+#elif SPHX_VEC_PART % 5 == 2
+template int vspmm_shiftdot<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                                   EpiShiftDotP<PartT>, double *, int *, hipStream_t);
+#elif SPHX_VEC_PART % 5 == 3
+template int vspmm_cheb<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                               EpiChebP<PartT>, hipStream_t, const LaunchEvents *);
+#else
+template int vspmm_poly<PartT>(sphx_graph *, const SpmmPlan &, const PartT *, int, int,
+                               EpiPolyP<PartT>, hipStream_t, const LaunchEvents *);
+#endif
 
 }  // namespace sphx
