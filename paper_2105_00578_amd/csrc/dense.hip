@@ -288,29 +288,61 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double *partials, int
 constexpr int LDA = kMaxW + 1;
 static_assert(kMaxW < 64, "Rayleigh-Ritz pivot search: one candidate per lane of a wave");
 
-// Cyclic Jacobi eigensolver (round-robin parallel ordering) on the k x k
-// symmetric matrix in A (LDS, stride LDA); V receives the eigenvectors, and
-// the returned pointer (A or B) the rotated matrix.  For odd k the matrices
-// carry one zero row and column k (its pairs never rotate), so that every
-// pair of a round has two rows.  The pairs of one round are disjoint, so
+// Cyclic Jacobi eigensolver (round-robin parallel ordering) on a k x k
+// symmetric matrix.  For odd k the matrix carries one zero row and column k
+// (its pairs never rotate), so that every pair of a round has two rows; kk is
+// the even order.  The pairs (p, q), p < q, of one round are disjoint, so
 // A <- R^T A R splits into independent 2 x 2 blocks (pair I's rows, pair J's
 // columns).  In every wave, lane I computes the angle of pair I from the
 // matrix of the previous round; each thread then takes one block, fetches
 // the angles of I and J from those lanes, rotates its rows with I's angle,
 // then its columns with J's (a row pass followed by a column pass; a pair
 // that does not rotate has c = 1, s = 0, which leaves its entries exactly as
-// they are), and writes the block into the other buffer; V <- V R likewise
-// by blocks, in place.  One barrier per round.  Before each sweep every pair
-// is tested once: the sweeps stop when no pair would rotate.
-__device__ __forceinline__ void jacobi_pair(int r, int t, int kk, int &p, int &q) {
-  // written with selects (t varies across lanes)
-  int a = r + t, b = r - t;
-  a = a >= kk - 1 ? a - (kk - 1) : a;
-  b = b < 0 ? b + (kk - 1) : b;
-  a = t == 0 ? kk - 1 : a;
-  b = t == 0 ? r : b;
-  p = min(a, b);
-  q = max(a, b);
+// they are); V <- V R likewise by blocks.  Before each sweep every pair is
+// tested once: the sweeps stop when no pair would rotate.
+//
+// A round is bound by instruction issue (one or two waves work; a wave issues
+// at most one FP64 operation per 4 cycles) and by its chain of LDS trips, so
+// index work is kept out of it: the matrices are stored in the order of the
+// round, pair I in rows and columns 2 I (p) and 2 I + 1 (q), so a thread's
+// block is two aligned 16-byte reads at a fixed address, and each entry is
+// written to its place in the next round's order, in the other buffer
+// (JTab: per round and pair, the next byte offsets of its two rows and its two
+// columns; one barrier per round).  Threads past the last block repeat block
+// 0 of their kind, writing the same values, so that the loads need no branch.
+// Measured, k_rr in all (rank 11 / 15 / 21 / 27, pencils of random H and P
+// columns): 32.5 / 48.1 / 88.5 / 152 us, with the index arithmetic and 8-byte
+// reads in the round 52.5 / 77.5 / 125 / 221 us.  The angles fetched through
+// LDS instead of lane shuffles: 36.8 / 54.7 / 106 / 167 us.
+constexpr int JLD = kMaxW + 2;            // row stride of the ordered matrices
+constexpr int kJBuf = kMaxW * JLD;        // doubles of one of them
+// [A, V, A', V']: the buffers alternate by round
+constexpr int kJWork = 4 * kJBuf;
+
+struct JTab {
+  // low half: the pair's first (p) row or column, high half: the second (q)
+  uint32_t row[kMaxW - 1][kMaxW / 2], col[kMaxW - 1][kMaxW / 2];
+};
+static_assert(kMaxW * JLD * 8 < 65536, "row byte offsets fit 16 bits");
+
+// place of index i in the order of round 0 (pair 0 is (0, kk - 1), pair t is
+// (t, kk - 1 - t)); the index at place 2 t is t, at 2 t + 1 it is kk - 1 - t
+__device__ __forceinline__ int jacobi_place(int i, int kk) {
+  return 2 * i < kk ? 2 * i : 2 * (kk - 1 - i) + 1;
+}
+
+// pair and slot, as one place, of index i in round r: kk - 1 meets r; any
+// other index is r + t or r - t modulo kk - 1 and meets the other one
+__device__ __forceinline__ int jacobi_place_at(int i, int r, int kk) {
+  const int q = kk - 1;
+  if (i == q) return 1;                   // pair 0, the larger index
+  int d = i - r;
+  d = d < 0 ? d + q : d;
+  const int t = 2 * d < q ? d : q - d;
+  if (t == 0) return 0;
+  int j = 2 * d < q ? r - t : r + t;      // the partner
+  j = j < 0 ? j + q : (j >= q ? j - q : j);
+  return 2 * t + (i > j ? 1 : 0);
 }
 
 // rotations stop once an off-diagonal entry is at rounding level (a few ulps
@@ -350,8 +382,8 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
   double th = (aqq - app) * recip(h);
   th = fmin(fmax(th, -1e150), 1e150);
   const double q = fma(th, th, 1.0);
-  const double sq = q * rsqrt_nr(q);
-  const double tt = (th >= 0 ? 1.0 : -1.0) * recip(fabs(th) + sq);
+  const double den = fma(q, rsqrt_nr(q), fabs(th));
+  const double tt = (th >= 0 ? 1.0 : -1.0) * recip(den);
   const double cc = rsqrt_nr(fma(tt, tt, 1.0));
   c = rot ? cc : 1.0;
   s = rot ? tt * cc : 0.0;
@@ -361,115 +393,160 @@ constexpr int kJacobiThreads = 256;
 // blocks per thread and round: 2 (kMaxW / 2)^2 over kJacobiThreads threads
 constexpr int kJacobiItems = (2 * (kMaxW / 2) * (kMaxW / 2) + kJacobiThreads - 1) / kJacobiThreads;
 
-// The matrices are at offsets ao (A), bo (B) and vo (V) of the LDS array S;
-// returns the offset of the rotated matrix.
-__device__ __forceinline__ int jacobi_eig(double *S, int ao, int bo, int vo, int k, int *flags) {
-  double *A = S + ao;
-  double *V = S + vo;
-  __shared__ double anorm;
+// The rounds' table for order kk, by threads first .. first + cnt - 1.
+__device__ __forceinline__ void jacobi_table(JTab *tab, int kk, int first, int cnt) {
+  const int id = (int)threadIdx.x - first;
+  if (id < 0 || id >= cnt) return;
+  uint16_t *row = reinterpret_cast<uint16_t *>(tab->row);
+  uint16_t *col = reinterpret_cast<uint16_t *>(tab->col);
+  for (int e = id; e < (kk - 1) * kk; e += cnt) {
+    const int r = e / kk, i = e - r * kk;
+    const int at = r * kMaxW + jacobi_place_at(i, r, kk);
+    const int to = jacobi_place_at(i, r + 1 == kk - 1 ? 0 : r + 1, kk);
+    row[at] = (uint16_t)(to * JLD * 8);
+    col[at] = (uint16_t)(to * 8);
+  }
+}
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// The sweeps over work = [A, V, A', V'] (A and V in the order of round 0);
+// returns the offset (0 or 2 kJBuf) of the final A, in the same order.
+template <int kItems>
+__device__ __forceinline__ int jacobi_sweeps(double *work, const JTab *tab, int k,
+                                             double abs_floor, int *flags) {
   const int t = threadIdx.x;
   const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int kk = k + (k & 1);
-  for (int e = t; e < kk * kk; e += blockDim.x) {
-    const int i = e / kk, j = e - i * kk;
-    V[i * LDA + j] = (i == j) ? 1.0 : 0.0;
-    if (i == k || j == k) A[i * LDA + j] = 0.0;   // odd k: the zero row and column
-  }
-  if (t < 64) {
-    double s = 0.0;
-    for (int e = t; e < k * k; e += 64) {
-      int i = e / k, j = e - i * k;
-      s += A[i * LDA + j] * A[i * LDA + j];
-    }
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (t == 0) anorm = sqrt(s);
-  }
-  if (t < 3) flags[t] = 0;
-  __syncthreads();
-  if (k < 2) return ao;
-  const double abs_floor = 4e-16 * anorm + 1e-300;
   const int npair = kk / 2;              // <= kMaxW / 2 < 64: one pair per lane
   const int nblk = npair * npair;
   const int nwork = 2 * nblk;
-  const int npq = k * (k - 1) / 2;
-  // this thread's blocks (fixed over the rounds): pair indices and kind
-  int bI[kJacobiItems], bJ[kJacobiItems];
-  bool bV[kJacobiItems], bOk[kJacobiItems];
+  const int la = lane < npair ? 2 * lane * (JLD + 1) : 0;   // this lane's diagonal block
+  // this thread's blocks: pair indices (V: rows 2 I and 2 I + 1 of V) and kind
+  int bI[kItems], bJ[kItems], src[kItems];
+  bool bV[kItems];
 #pragma unroll
-  for (int u = 0; u < kJacobiItems; ++u) {
+  for (int u = 0; u < kItems; ++u) {
     const int e = t + u * kJacobiThreads;
-    bOk[u] = e < nwork;
     bV[u] = e >= nblk;
     const int b = e < nblk ? e : (e < nwork ? e - nblk : 0);
     bI[u] = b / npair;
     bJ[u] = b - bI[u] * npair;
+    src[u] = (bV[u] ? kJBuf : 0) + 2 * bI[u] * JLD + 2 * bJ[u];
   }
-  int cur = ao, nxt = bo;
+  int cur = 0;                           // offset of this round's A, V
   for (int sweep = 0; sweep < 40; ++sweep) {
     // flags cycle through three words: the one tested now was cleared two
     // sweeps ago, and read by every thread before the barriers of the last
     // sweep, when it is cleared again
     int *rot = flags + sweep % 3;
     if (t == 0) flags[(sweep + 1) % 3] = 0;
-    for (int e = t; e < npq; e += blockDim.x) {
-      // pair (p, q), p < q: e = q (q - 1) / 2 + p
-      int q = (int)((1.0 + sqrt(1.0 + 8.0 * e)) * 0.5);
-      while (q * (q - 1) / 2 > e) --q;
-      while ((q + 1) * q / 2 <= e) ++q;
-      const int p = e - q * (q - 1) / 2;
-      if (jacobi_rotates(S[cur + p * LDA + q], S[cur + p * LDA + p], S[cur + q * LDA + q],
-                         abs_floor))
-        *rot = 1;
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      if (bV[u]) continue;
+      const int I = bI[u], J = bJ[u];
+      const double *a = work + cur + src[u];
+      const double *dI = work + cur + 2 * I * (JLD + 1), *dJ = work + cur + 2 * J * (JLD + 1);
+      // indices: place 2 I holds I, 2 I + 1 holds kk - 1 - I
+      const int i0 = I, i1 = kk - 1 - I, j0 = J, j1 = kk - 1 - J;
+      const double di0 = dI[0], di1 = dI[JLD + 1], dj0 = dJ[0], dj1 = dJ[JLD + 1];
+      const bool any = ((i0 < j0) & jacobi_rotates(a[0], di0, dj0, abs_floor)) |
+                       ((i0 < j1) & jacobi_rotates(a[1], di0, dj1, abs_floor)) |
+                       ((i1 < j0) & jacobi_rotates(a[JLD], di1, dj0, abs_floor)) |
+                       ((i1 < j1) & jacobi_rotates(a[JLD + 1], di1, dj1, abs_floor));
+      if (any) *rot = 1;
     }
     __syncthreads();
     if (*rot == 0) break;
     for (int r = 0; r < kk - 1; ++r) {
-      double c, s;
-      {
-        int p, q;
-        jacobi_pair(r, lane < npair ? lane : 0, kk, p, q);
-        const double apq = S[cur + p * LDA + q];
-        const double app = S[cur + p * LDA + p], aqq = S[cur + q * LDA + q];
-        const bool rr = (lane < npair) & (q < k) & jacobi_rotates(apq, app, aqq, abs_floor);
-        jacobi_rotation(app, aqq, apq, rr, c, s);
-      }
+      const int nxt = 2 * kJBuf - cur;
+      if (wave * 64 < nwork) {           // the same for a whole wave
+        const d2 ad = *reinterpret_cast<const d2 *>(work + cur + la);
+        const double aqq = work[cur + la + JLD + 1];
+        d2 x0[kItems], x1[kItems];
+        uint32_t tr[kItems], tc[kItems];
 #pragma unroll
-      for (int u = 0; u < kJacobiItems; ++u) {
-        if (u * kJacobiThreads >= nwork) break;     // uniform
-        const int I = bI[u], J = bJ[u];
-        const double cI0 = __shfl(c, I), sI0 = __shfl(s, I);
-        const double cJ = __shfl(c, J), sJ = __shfl(s, J);
-        if (!bOk[u]) continue;
-        const bool isv = bV[u];
-        const double cI = isv ? 1.0 : cI0, sI = isv ? 0.0 : sI0;
-        int p0, q0, p1, q1;
-        jacobi_pair(r, I, kk, p0, q0);
-        jacobi_pair(r, J, kk, p1, q1);
-        const int mi = isv ? vo : cur, oi = isv ? vo : nxt;
-        double a00 = S[mi + p0 * LDA + p1], a01 = S[mi + p0 * LDA + q1];
-        double a10 = S[mi + q0 * LDA + p1], a11 = S[mi + q0 * LDA + q1];
-        {
-          const double b00 = cI * a00 - sI * a10, b10 = sI * a00 + cI * a10;
-          const double b01 = cI * a01 - sI * a11, b11 = sI * a01 + cI * a11;
-          a00 = b00; a10 = b10; a01 = b01; a11 = b11;
+        for (int u = 0; u < kItems; ++u) {
+          x0[u] = *reinterpret_cast<const d2 *>(work + cur + src[u]);
+          x1[u] = *reinterpret_cast<const d2 *>(work + cur + src[u] + JLD);
+          tr[u] = tab->row[r][bI[u]];
+          tc[u] = tab->col[r][bJ[u]];
         }
-        {
-          const double b00 = cJ * a00 - sJ * a01, b01 = sJ * a00 + cJ * a01;
-          const double b10 = cJ * a10 - sJ * a11, b11 = sJ * a10 + cJ * a11;
-          a00 = b00; a01 = b01; a10 = b10; a11 = b11;
+        const bool rr = (lane < npair) & jacobi_rotates(ad[1], ad[0], aqq, abs_floor);
+        double c, s;
+        jacobi_rotation(ad[0], aqq, ad[1], rr, c, s);
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) {
+          if (u * kJacobiThreads >= nwork) break;     // uniform
+          const double cI0 = __shfl(c, bI[u]), sI0 = __shfl(s, bI[u]);
+          const double cJ = __shfl(c, bJ[u]), sJ = __shfl(s, bJ[u]);
+          const double cI = bV[u] ? 1.0 : cI0, sI = bV[u] ? 0.0 : sI0;
+          const double a00 = x0[u][0], a01 = x0[u][1], a10 = x1[u][0], a11 = x1[u][1];
+          const double b00 = fma(cI, a00, -(sI * a10)), b10 = fma(sI, a00, cI * a10);
+          const double b01 = fma(cI, a01, -(sI * a11)), b11 = fma(sI, a01, cI * a11);
+          // byte offsets (V: its rows stay)
+          const uint32_t v0 = (uint32_t)(2 * bI[u] * JLD * 8);
+          const uint32_t r0 = bV[u] ? v0 : tr[u] & 0xffffu;
+          const uint32_t r1 = bV[u] ? v0 + JLD * 8 : tr[u] >> 16;
+          const uint32_t c0 = tc[u] & 0xffffu, c1 = tc[u] >> 16;
+          char *o = reinterpret_cast<char *>(work + nxt + (bV[u] ? kJBuf : 0));
+          *reinterpret_cast<double *>(o + (r0 + c0)) = fma(cJ, b00, -(sJ * b01));
+          *reinterpret_cast<double *>(o + (r0 + c1)) = fma(sJ, b00, cJ * b01);
+          *reinterpret_cast<double *>(o + (r1 + c0)) = fma(cJ, b10, -(sJ * b11));
+          *reinterpret_cast<double *>(o + (r1 + c1)) = fma(sJ, b10, cJ * b11);
         }
-        S[oi + p0 * LDA + p1] = a00;
-        S[oi + p0 * LDA + q1] = a01;
-        S[oi + q0 * LDA + p1] = a10;
-        S[oi + q0 * LDA + q1] = a11;
       }
       __syncthreads();
-      const int tmp = cur;
       cur = nxt;
-      nxt = tmp;
     }
   }
   return cur;
+}
+
+// Eigenpairs of the k x k matrix A (LDS, stride LDA): lam[i], and V(i, c) at
+// (returned pointer)[i * JLD + jacobi_place(c, kk)], kk = k + (k & 1).  A may
+// not overlap work; tab is that of order kk.  Every thread of the block calls
+// this, and the caller's writes of A and tab need a barrier before.  Ends with
+// a barrier.
+__device__ __forceinline__ const double *jacobi_eig(const double *A, double *work,
+                                                    const JTab *tab, int k, double *lam,
+                                                    int *flags) {
+  __shared__ double anorm;
+  const int t = threadIdx.x;
+  const int kk = k + (k & 1);
+  if (t < 64) {
+    double s = 0.0;
+    for (int e = t; e < k * k; e += 64) {
+      int i = e / k, j = e - i * k;
+      s = fma(A[i * LDA + j], A[i * LDA + j], s);
+    }
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (t == 0) anorm = sqrt(s);
+  } else {
+    const int tx = t & 15, ty = (t - 64) >> 4;      // 12 rows of 16 threads
+    for (int i = ty; i < kk; i += (kJacobiThreads - 64) / 16)
+      for (int j = tx; j < kk; j += 16) {
+        const int pj = jacobi_place(j, kk);
+        work[jacobi_place(i, kk) * JLD + pj] = (i == k || j == k) ? 0.0 : A[i * LDA + j];
+        work[kJBuf + i * JLD + pj] = (i == j) ? 1.0 : 0.0;
+      }
+  }
+  if (t < 3) flags[t] = 0;
+  __syncthreads();
+  int cur = 0;
+  if (k >= 2) {
+    const double abs_floor = 4e-16 * anorm + 1e-300;
+    // blocks per thread: one up to kk = 22 (the pencils of 7 vectors), two up
+    // to kk = 32, else kJacobiItems
+    const int nwork = kk * kk / 2;
+    if (nwork <= kJacobiThreads) cur = jacobi_sweeps<1>(work, tab, k, abs_floor, flags);
+    else if (nwork <= 2 * kJacobiThreads) cur = jacobi_sweeps<2>(work, tab, k, abs_floor, flags);
+    else cur = jacobi_sweeps<kJacobiItems>(work, tab, k, abs_floor, flags);
+  }
+  if (t < k) lam[t] = work[cur + jacobi_place(t, kk) * (JLD + 1)];
+  __syncthreads();
+  return work + cur + kJBuf;
 }
 
 // Rayleigh-Ritz (Algorithm 1, RR(S, nev)) on the reduced Gram matrices.
@@ -481,152 +558,160 @@ __device__ __forceinline__ int jacobi_eig(double *S, int ao, int bo, int vo, int
 // up to the tolerance (those are dropped as linearly dependent), and
 // Gs(piv, piv) = L L^T.  The rows of W = L^-1 are formed along with the
 // columns of L: row k is W[k][c] = -(1 / l_kk) sum_j L[k][j] W[j][c] for
-// c < k and 1 / l_kk for c = k, where the sums are accumulated step by step
-// for every row not chosen yet (acc[i][c] += l_ik W[k][c], right-looking),
-// so L itself is never stored.  With C = W^T, S(:, piv) C is B-orthonormal
+// c < k and 1 / l_kk for c = k.  With C = W^T, S(:, piv) C is B-orthonormal
 // and the projected matrix A' = W As(piv, piv) W^T is diagonalised by cyclic
 // Jacobi; the m smallest Ritz pairs give Y = D P W^T Z.  If fewer than m
 // columns survive, the P block is dropped and the step retried once.
+//
+// The kernel is one workgroup and bound by latency and issue, so the
+// factorisation runs in one wave without barriers, lane i holding row i: a
+// step is the pivot search, one pass over the columns of L formed so far
+// (left-looking: both sums take the broadcast entry L[p][q]; the terms are
+// subtracted in the order of the steps) and one write of a column of L and a
+// row of W.
 constexpr int kRRThreads = kJacobiThreads;
 
-// (v, i) or (ov, oi), whichever comes first in the order: larger value,
-// then lower index; an index < 0 marks no candidate
-__device__ __forceinline__ void take_better(double &v, int &i, double ov, int oi) {
-  // non-short-circuit operators: selects, no branches
-  const bool b = (oi >= 0) & ((i < 0) | (ov > v) | ((ov == v) & (oi < i)));
-  v = b ? ov : v;
-  i = b ? oi : i;
-}
-
-// Value and index of lane (lane ^ pattern) within rows of 16 lanes (DPP).
+// Maximum of x over the wave, in every lane: within each row of 16 lanes by
+// DPP moves (swap of neighbours, of pairs, then the half-row and row mirrors,
+// each pairing every lane with one holding the other half's largest so far),
+// then across the four rows by lane reads.
 template <int kCtrl>
-__device__ __forceinline__ void dpp_take(double &v, int &i) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, false);
-  const int oi = __builtin_amdgcn_update_dpp(-1, i, kCtrl, 0xF, 0xF, false);
-  take_better(v, i, __hiloint2double(hi, lo), oi);
+__device__ __forceinline__ unsigned dpp_max(unsigned x) {
+  const unsigned y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, 0xF, 0xF, false);
+  return x > y ? x : y;
+}
+__device__ __forceinline__ unsigned wave_max(unsigned x) {
+  x = dpp_max<0xB1>(x);    // quad_perm(1, 0, 3, 2)
+  x = dpp_max<0x4E>(x);    // quad_perm(2, 3, 0, 1)
+  x = dpp_max<0x141>(x);   // row_half_mirror
+  x = dpp_max<0x140>(x);   // row_mirror
+  unsigned b = (unsigned)__builtin_amdgcn_readlane((int)x, 0);
+#pragma unroll
+  for (int r = 1; r < 4; ++r) {
+    const unsigned y = (unsigned)__builtin_amdgcn_readlane((int)x, 16 * r);
+    b = b > y ? b : y;
+  }
+  return b;
 }
 
-// The first (value, index) of the wave in the order above, in every lane
-// (all 64 lanes active): within each row of 16 lanes by DPP moves (swap of
-// neighbours, of pairs, then the half-row and row mirrors, each pairing
-// every lane with one holding the other half's best so far), then across the
-// four rows by lane reads.
-__device__ __forceinline__ void wave_argmax(double &v, int &i) {
-  dpp_take<0xB1>(v, i);    // quad_perm(1, 0, 3, 2)
-  dpp_take<0x4E>(v, i);    // quad_perm(2, 3, 0, 1)
-  dpp_take<0x141>(v, i);   // row_half_mirror
-  dpp_take<0x140>(v, i);   // row_mirror
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  double bv = __hiloint2double(__builtin_amdgcn_readlane(hi, 0), __builtin_amdgcn_readlane(lo, 0));
-  int bi = __builtin_amdgcn_readlane(i, 0);
-#pragma unroll
-  for (int r = 1; r < 4; ++r)
-    take_better(bv, bi,
-                __hiloint2double(__builtin_amdgcn_readlane(hi, 16 * r),
-                                 __builtin_amdgcn_readlane(lo, 16 * r)),
-                __builtin_amdgcn_readlane(i, 16 * r));
-  v = bv;
-  i = bi;
+// Lane of the largest positive d of the wave (the lowest lane on ties), in
+// every lane, or -1.  Positive doubles order as their bits, so the high words
+// decide unless several lanes share the largest one.
+__device__ __forceinline__ int wave_pivot(double d) {
+  const bool pos = d > 0.0;
+  const unsigned hi = pos ? (unsigned)__double2hiint(d) : 0u;
+  const unsigned lo = pos ? (unsigned)__double2loint(d) : 0u;
+  const unsigned mh = wave_max(hi);
+  unsigned long long who = __ballot(pos && hi == mh);
+  if (who == 0ull) return -1;
+  if (who & (who - 1)) {                       // uniform: more than one lane
+    const unsigned ml = wave_max(hi == mh ? lo : 0u);
+    who = __ballot(pos && hi == mh && lo == ml);
+  }
+  return __ffsll((long long)who) - 1;
 }
-constexpr int kRRItems = (kMaxW * kMaxW + kRRThreads - 1) / kRRThreads;
+
+// value of lane p (the same p in every lane)
+__device__ __forceinline__ double lane_value(double v, int p) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), p),
+                          __builtin_amdgcn_readlane(__double2loint(v), p));
+}
 
 __global__ __launch_bounds__(kRRThreads) void k_rr(const double *__restrict__ gram, RRArgs a,
                                                    double *Y, double *theta, DevStatus *st) {
   constexpr int MS = kMaxW * LDA;
-  __shared__ double Msh[4 * MS];
-  double *M1 = Msh, *M2 = Msh + MS, *M3 = Msh + 2 * MS, *Wi = Msh + 3 * MS;
-  __shared__ double sc[kMaxW], lam[kMaxW], dg[2][kMaxW];
+  __shared__ __align__(16) double Msh[kJWork + 2 * MS];
+  __shared__ JTab tab;
+  // M1 and M2 share the rotations' buffers, which are filled from M3
+  static_assert(MS <= kJBuf, "M1 and M2 fit the first two buffers");
+  double *M1 = Msh, *M2 = Msh + kJBuf, *M3 = Msh + kJWork, *Wi = Msh + kJWork + MS;
+  __shared__ double sc[kMaxW], lam[kMaxW];
   __shared__ int piv[kMaxW], ipiv[kMaxW], perm[kMaxW];
-  __shared__ int flags[3];
+  __shared__ int flags[3], rank;
   const int t = threadIdx.x;
-  const int lane = t & 63;
   const int w = a.w, m = a.m;
   const double *GA = gram;
   const double *GB = gram + kMaxW * kMaxW;
   int restarted = 0;
   for (int attempt = 0; attempt < 2; ++attempt) {
     const int wl = attempt == 0 ? w : a.p_begin;   // drop P on retry
+    // M1 = Gs, M3 = As, M2 = the columns of L (column q in row q of M2);
+    // after the factorisation M1, M2 and M3 take As(piv, piv),
+    // As(piv, piv) W^T and A' in turn
+    const int tx = t & 15, ty = t >> 4;
+    for (int i = ty; i < wl; i += 16)
+      for (int j = tx; j < wl; j += 16) {
+        int lo = i < j ? i : j, hi = i < j ? j : i;
+        M1[i * LDA + j] = GB[lo * kMaxW + hi];
+        M3[i * LDA + j] = GA[lo * kMaxW + hi];
+      }
+    for (int e = t; e < (wl + 7) / 8 * 8 * LDA; e += blockDim.x) M2[e] = Wi[e] = 0.0;
+    __syncthreads();
     if (t < kMaxW) {
-      double g = (t < wl) ? GB[t * kMaxW + t] : 0.0;
+      double g = (t < wl) ? M1[t * LDA + t] : 0.0;
       sc[t] = (t < wl && g > 0.0) ? 1.0 / sqrt(g) : 0.0;
       ipiv[t] = -1;
     }
     __syncthreads();
-    // M1 = Gs (then its Schur complements, diagonal also in dg), M3 = As,
-    // M2 = the accumulated sums acc[i][c] of the rows of W; after the
-    // factorisation M1, M2 and M3 take As(piv, piv), As(piv, piv) W^T and A'
-    // in turn
-    for (int e = t; e < wl * wl; e += blockDim.x) {
-      int i = e / wl, j = e - i * wl;
-      int lo = i < j ? i : j, hi = i < j ? j : i;
-      double sij = sc[i] * sc[j];
-      const double gs = GB[lo * kMaxW + hi] * sij;
-      M1[i * LDA + j] = gs;
-      if (i == j) dg[0][i] = gs;
-      M3[i * LDA + j] = GA[lo * kMaxW + hi] * sij;
-      M2[i * LDA + j] = 0.0;
-    }
-    // this thread's entries (i, j) of the wl x wl matrices, fixed over the
-    // steps, and whether row i / column j has been chosen (the same for every
-    // thread: the pivots are)
-    int ei[kRRItems], ej[kRRItems];
-    bool ci[kRRItems], cj[kRRItems];
-#pragma unroll
-    for (int u = 0; u < kRRItems; ++u) {
-      const int e = t + u * kRRThreads;
-      const bool ok = e < wl * wl;
-      ei[u] = ok ? e / wl : 0;
-      ej[u] = ok ? e - ei[u] * wl : 0;
-      ci[u] = !ok;                 // nothing to do for entries past the matrix
-      cj[u] = false;
-    }
-    bool ct = t >= wl;             // column t chosen (or past the matrix)
+    for (int i = ty; i < wl; i += 16)
+      for (int j = tx; j < wl; j += 16) {
+        double sij = sc[i] * sc[j];
+        M1[i * LDA + j] *= sij;
+        M3[i * LDA + j] *= sij;
+      }
     __syncthreads();
-    // ---- pivoted Cholesky of Gs, one barrier per step: every wave finds
-    // the pivot itself from the diagonal of the previous step (dg[k & 1],
-    // which this step does not write; chosen columns hold 0 there)
-    int k = 0;
-    for (; k < wl; ++k) {
-      // the largest positive remaining diagonal entry, the lowest index on
-      // ties (one candidate per lane: wl <= kMaxW < 64)
-      double bv = lane < wl ? dg[k & 1][lane] : 0.0;
-      int best = bv > 0.0 ? lane : -1;
-      wave_argmax(bv, best);
-      const int p = (best >= 0 && bv > a.drop_tol) ? best : -1;
-      if (p < 0) break;
-      const double pval = bv;
-      const double rd = 1.0 / sqrt(pval);
-      if (t == 0) {
-        piv[k] = p;
-        ipiv[p] = k;
-      }
-      // row k of W
-      if (t <= k) Wi[k * LDA + t] = t == k ? rd : -rd * M2[p * LDA + t];
-      // chosen columns leave the diagonal search
-      if (t == p) ct = true;
-      if (t < wl && ct) dg[(k + 1) & 1][t] = 0.0;
-      // Schur complement on the columns not chosen yet, and the sums of the
-      // rows of W not formed yet (column p of M1 and row p of M2 are not
-      // written in this step); all loads of an entry are issued first
+    if (t < 64) {
+      // ---- pivoted Cholesky of Gs: lane i holds row i (lanes past the
+      // matrix, and rows already chosen, hold d = 0 and never are a pivot)
+      const int i = t < wl ? t : 0;
+      double d = t < wl ? M1[i * LDA + i] : 0.0;
+      bool open = t < wl;
+      int k = 0;
+      for (; k < wl; ++k) {
+        const int p = wave_pivot(d);
+        if (p < 0) break;
+        const double pval = lane_value(d, p);
+        if (!(pval > a.drop_tol)) break;
+        const double rd = 1.0 / sqrt(pval);
+        // s = Gs[p][i] - sum_q L[p][q] L[i][q], v = sum_q L[p][q] W[q][i]
+        double s = M1[p * LDA + i], v = 0.0;
+        const double *lp = M2 + p, *lq = M2 + i, *wq = Wi + i;
+        // (rows k .. of M2 and Wi are zero, so whole groups of 8 are taken)
+        for (int q = 0; q < k; q += 8, lp += 8 * LDA, lq += 8 * LDA, wq += 8 * LDA) {
+          double b[8], l[8], x[8];
 #pragma unroll
-      for (int u = 0; u < kRRItems; ++u) {
-        const int i = ei[u], j = ej[u];
-        if (i == p) ci[u] = true;
-        if (j == p) cj[u] = true;
-        if (ci[u]) continue;
-        const double mip = M1[i * LDA + p], mjp = M1[j * LDA + p], mij = M1[i * LDA + j];
-        const double apj = M2[p * LDA + j], aij = M2[i * LDA + j];
-        const double li = mip * rd;
-        if (!cj[u]) {
-          const double v = mij - li * (mjp * rd);
-          M1[i * LDA + j] = v;
-          if (i == j) dg[(k + 1) & 1][i] = v;
+          for (int u = 0; u < 8; ++u) {
+            b[u] = lp[u * LDA];
+            l[u] = lq[u * LDA];
+            x[u] = wq[u * LDA];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            s = fma(-b[u], l[u], s);
+            v = fma(b[u], x[u], v);
+          }
         }
-        if (j <= k) M2[i * LDA + j] = aij + li * (j == k ? rd : -rd * apj);
+        const double l = open ? s * rd : 0.0;
+        if (t == p) open = false;
+        d = open ? fma(-l, l, d) : 0.0;
+        if (t < wl) {
+          M2[k * LDA + t] = l;
+          Wi[k * LDA + t] = t < k ? -rd * v : (t == k ? rd : 0.0);
+        }
+        if (t == 0) {
+          piv[k] = p;
+          ipiv[p] = k;
+        }
+        // one wave: its LDS writes are read in order by the next step
+        __builtin_amdgcn_wave_barrier();
       }
-      __syncthreads();
+      if (t == 0) rank = k;
+    } else {
+      // the other waves prepare the rotations' table meanwhile
+      jacobi_table(&tab, wl + (wl & 1), 64, kRRThreads - 64);
     }
+    __syncthreads();
+    const int k = rank;
     if (k >= m || attempt == 1 || a.p_begin >= w) {
       if (k < m) {
         // breakdown: keep X as it is
@@ -641,50 +726,51 @@ __global__ __launch_bounds__(kRRThreads) void k_rr(const double *__restrict__ gr
         }
         return;
       }
-      // Ap = As(piv, piv) -> M1
-      for (int e = t; e < k * k; e += blockDim.x) {
-        const int i = e / k, j = e - i * k;
-        M1[i * LDA + j] = M3[piv[i] * LDA + piv[j]];
-      }
+      // Ap = As(piv, piv) -> M1; the table again if columns were dropped
+      if (k + (k & 1) != wl + (wl & 1)) jacobi_table(&tab, k + (k & 1), 0, kRRThreads);
+      for (int i = ty; i < k; i += 16)
+        for (int j = tx; j < k; j += 16) M1[i * LDA + j] = M3[piv[i] * LDA + piv[j]];
       __syncthreads();
       // T = Ap W^T -> M2 (W lower triangular: j <= c)
-      for (int e = t; e < k * k; e += blockDim.x) {
-        const int i = e / k, c = e - i * k;
-        double s0 = 0.0, s1 = 0.0;
-        int j = 0;
-        for (; j + 1 <= c; j += 2) {
-          s0 += M1[i * LDA + j] * Wi[c * LDA + j];
-          s1 += M1[i * LDA + j + 1] * Wi[c * LDA + j + 1];
+      for (int i = ty; i < k; i += 16)
+        for (int c = tx; c < k; c += 16) {
+          double s0 = 0.0, s1 = 0.0;
+          int j = 0;
+#pragma unroll 4
+          for (; j + 1 <= c; j += 2) {
+            s0 = fma(M1[i * LDA + j], Wi[c * LDA + j], s0);
+            s1 = fma(M1[i * LDA + j + 1], Wi[c * LDA + j + 1], s1);
+          }
+          if (j <= c) s0 = fma(M1[i * LDA + j], Wi[c * LDA + j], s0);
+          M2[i * LDA + c] = s0 + s1;
         }
-        if (j <= c) s0 += M1[i * LDA + j] * Wi[c * LDA + j];
-        M2[i * LDA + c] = s0 + s1;
-      }
       __syncthreads();
       // A' = W T -> M3 (j <= i), upper triangle computed and mirrored
-      for (int e = t; e < k * k; e += blockDim.x) {
-        const int i = e / k, c = e - i * k;
-        if (i > c) continue;
-        double s0 = 0.0, s1 = 0.0;
-        int j = 0;
-        for (; j + 1 <= i; j += 2) {
-          s0 += Wi[i * LDA + j] * M2[j * LDA + c];
-          s1 += Wi[i * LDA + j + 1] * M2[(j + 1) * LDA + c];
+      for (int i = ty; i < k; i += 16)
+        for (int c = tx; c < k; c += 16) {
+          if (i > c) continue;
+          double s0 = 0.0, s1 = 0.0;
+          int j = 0;
+#pragma unroll 4
+          for (; j + 1 <= i; j += 2) {
+            s0 = fma(Wi[i * LDA + j], M2[j * LDA + c], s0);
+            s1 = fma(Wi[i * LDA + j + 1], M2[(j + 1) * LDA + c], s1);
+          }
+          if (j <= i) s0 = fma(Wi[i * LDA + j], M2[j * LDA + c], s0);
+          M3[i * LDA + c] = s0 + s1;
+          M3[c * LDA + i] = s0 + s1;
         }
-        if (j <= i) s0 += Wi[i * LDA + j] * M2[j * LDA + c];
-        M3[i * LDA + c] = s0 + s1;
-        M3[c * LDA + i] = s0 + s1;
-      }
       __syncthreads();
-      // eigenpairs of A': values on the diagonal, vectors in M2
-      const int af = jacobi_eig(Msh, 2 * MS, 0, MS, k, flags);
-      if (t < k) lam[t] = Msh[af + t * LDA + t];
-      __syncthreads();
+      // eigenpairs of A'
+      const double *Z = jacobi_eig(M3, Msh, &tab, k, lam, flags);
+      const int kk = k + (k & 1);
       if (t < k) {
-        int rank = 0;
+        int below = 0;
         double v = lam[t];
+#pragma unroll 4
         for (int j = 0; j < k; ++j)
-          if (lam[j] < v || (lam[j] == v && j < t)) ++rank;
-        perm[rank] = t;
+          below += ((lam[j] < v) | ((lam[j] == v) & (j < t))) ? 1 : 0;
+        perm[below] = t;
       }
       __syncthreads();
       // Y (basis row i, Ritz vector c) = sc_i (W^T z_perm[c])[position of
@@ -693,14 +779,15 @@ __global__ __launch_bounds__(kRRThreads) void k_rr(const double *__restrict__ gr
         int i = e / kMaxNev, c = e - i * kMaxNev;
         double v = 0.0;
         if (i < wl && c < m && ipiv[i] >= 0) {
-          const int r = ipiv[i], zc = perm[c];
+          const int r = ipiv[i], zc = jacobi_place(perm[c], kk);
           double s0 = 0.0, s1 = 0.0;
           int j = r;
+#pragma unroll 4
           for (; j + 1 < k; j += 2) {
-            s0 += Wi[j * LDA + r] * M2[j * LDA + zc];
-            s1 += Wi[(j + 1) * LDA + r] * M2[(j + 1) * LDA + zc];
+            s0 = fma(Wi[j * LDA + r], Z[j * JLD + zc], s0);
+            s1 = fma(Wi[(j + 1) * LDA + r], Z[(j + 1) * JLD + zc], s1);
           }
-          if (j < k) s0 += Wi[j * LDA + r] * M2[j * LDA + zc];
+          if (j < k) s0 = fma(Wi[j * LDA + r], Z[j * JLD + zc], s0);
           v = sc[i] * (s0 + s1);
         }
         Y[e] = v;
@@ -729,8 +816,9 @@ __global__ __launch_bounds__(kRRThreads) void k_rr(const double *__restrict__ gr
 __global__ __launch_bounds__(kJacobiThreads) void k_harmonic_ritz(const double *__restrict__ Hg, int k1,
                                                        double *theta, int *status) {
   constexpr int MS = kMaxW * LDA;
-  __shared__ double Msh[3 * MS];
-  double *Mk = Msh, *Mc = Msh + MS, *Mv = Msh + 2 * MS;
+  __shared__ __align__(16) double Msh[kJWork + MS];
+  __shared__ JTab tab;
+  double *Mk = Msh, *Mv = Msh + kJBuf, *Mc = Msh + kJWork;
   __shared__ double lam[kMaxW];
   __shared__ int flags[3], bad;
   const int t = threadIdx.x;
@@ -743,6 +831,7 @@ __global__ __launch_bounds__(kJacobiThreads) void k_harmonic_ritz(const double *
     Mc[i * LDA + j] = sum;
   }
   if (t == 0) bad = 0;
+  jacobi_table(&tab, k1 + (k1 & 1), 0, kJacobiThreads);
   __syncthreads();
   // Cholesky of Mk in place (lower), one thread
   if (t == 0) {
@@ -791,10 +880,8 @@ __global__ __launch_bounds__(kJacobiThreads) void k_harmonic_ritz(const double *
     }
   }
   __syncthreads();
-  // Mk (the factor) is free now: the second buffer of the rotations
-  const int af = jacobi_eig(Msh, MS, 0, 2 * MS, k1, flags);
-  if (t < k1) lam[t] = Msh[af + t * LDA + t];
-  __syncthreads();
+  // Mk (the factor) and Mv are free now: they lie in the rotations' buffers
+  (void)jacobi_eig(Mc, Msh, &tab, k1, lam, flags);
   if (t == 0) {
     bool used[kMaxW];
     for (int i = 0; i < k1; ++i) used[i] = false;
