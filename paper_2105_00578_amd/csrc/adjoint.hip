@@ -28,8 +28,9 @@
 // Laplacian kernel with the shift lam_k B and the dots p^T A p fused into its
 // epilogue.  The CG scalars (r^T z, alpha, beta, convergence flags) live on
 // the device and are computed by one-block reductions in a fixed order; the
-// host reads the flags every kCgCheck steps only.  Convergence: the relative
-// residual in the preconditioner's norm, sqrt(r^T z / f^T J f) <= cg_tol.
+// host reads the flags of a batch of kCgCheck steps while the next batch runs.
+// Convergence: the relative residual in the preconditioner's norm,
+// sqrt(r^T z / f^T J f) <= cg_tol; a converged column no longer moves.
 #include <algorithm>
 #include <cmath>
 
@@ -136,142 +137,300 @@ __global__ void k_project_rhs(const double *G, const double *Vp, const double *b
   }
 }
 
-// Device state of the projected CG (one entry per column).
+// ---- projected CG
+//
+// A step is four launches: the product (with p^T A p partials per block),
+// k_cg_update (alpha, x and r, and the partial sums of the projection),
+// k_cg_reduce, and k_cg_direction (the projection, beta and the new p).  At
+// the sizes met here (some 10^4 to 10^5 rows of 3..16 columns) a step is bound
+// by launches and by its chain of reductions, not by bytes, so every small
+// sum is taken where it is used: each block of k_cg_update adds the product's
+// partials itself, and each block of k_cg_direction forms beta itself; only
+// block 0 writes the state, into the other of two copies.  With z = J r,
+// M = V^T B z and G = V^T r, the projected residual z' = z - V M has
+// r^T z' = r^T z - sum_j G_jk M_jk, so neither z nor z' is stored.
+// Measured on a 256 x 200 grid, 5 columns (51,200 rows): 25 us per step where
+// eight kernels with one-block reductions took 63.
 struct CgState {
-  double rz[kMaxNev], rz0[kMaxNev], alpha[kMaxNev], beta[kMaxNev];
+  double rz[kMaxNev], rz0[kMaxNev];
   int done[kMaxNev];
   int iters;       // steps with at least one active column
   int breakdown;   // a column met p^T A p <= 0 before converging
 };
+// what k_cg_update's alphas tell the state
+struct CgAlpha {
+  int broke[kMaxNev];
+  int any;
+};
 
-// Optional step x += alpha p, r -= alpha Ap (state given), then z = J r with
-// J_ik = 1 / (d_i - lam_k b_i) (1 / d_i where that is not positive).
-__global__ void k_cg_step_jac(double *MU, double *R, const double *P, const double *AP,
-                              const CgState *st, const double *d, const double *bd,
-                              AdjParams p, int64_t n, int ld, double *Z) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * ld;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / ld;
-    const int k = (int)(e - i * ld);
-    if (k >= p.nev) { Z[e] = 0.0; continue; }
-    double r = R[e];
-    if (st) {
-      const double al = st->alpha[k];
-      MU[e] += al * P[e];
-      r -= al * AP[e];
-      R[e] = r;
-    }
-    double diag = d[i] - p.lam[k] * (bd ? bd[i] : 1.0);
-    if (!(diag > 0.0)) diag = d[i];
-    Z[e] = r / diag;
-  }
+constexpr int kCgTile = 64;       // rows per tile of k_cg_update
+constexpr int kCgBlocks = 1024;   // its blocks, at most
+constexpr int kCgParts = 1024;    // product partials a block adds by itself
+
+// sums per block of k_cg_update: M and G (nev x nev each), then r^T z
+__host__ __device__ inline int cg_sums(int nev) { return 2 * nev * nev + nev; }
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// 1 / J_ik = d_i - lam_k b_i (d_i where that is not positive)
+__device__ __forceinline__ double cg_diag(double d, double b, double lam) {
+  const double x = d - lam * b;
+  return x > 0.0 ? x : d;
 }
 
-// z <- z - V M (M = V^T B z, device) and per-block partial sums of r^T z per
-// column (fixed order: rows within a thread, then threads in LDS order).
-__global__ __launch_bounds__(256) void k_cg_project(double *Z, const double *Vp,
-                                                    const double *M, const double *R,
-                                                    int64_t n, int nev, int ld,
-                                                    double *rz_partials) {
-  __shared__ double sh[256];
-  const int rc = 256 / ld;                 // rows per block step (ld <= 16)
-  const int row = threadIdx.x / ld, c = threadIdx.x % ld;
-  const bool live = threadIdx.x < rc * ld && c < nev;
-  double acc = 0.0;
-  if (live)
-    for (int64_t i = (int64_t)blockIdx.x * rc + row; i < n; i += (int64_t)gridDim.x * rc) {
-      double s = 0.0;
-      for (int j = 0; j < nev; ++j) s += Vp[i * ld + j] * M[j * nev + c];
-      const double z = Z[i * ld + c] - s;
-      Z[i * ld + c] = z;
-      acc += R[i * ld + c] * z;
-    }
-  sh[threadIdx.x] = live ? acc : 0.0;
-  __syncthreads();
-  if (threadIdx.x < nev) {
-    double a = 0.0;
-    for (int r = 0; r < rc; ++r) a += sh[r * ld + threadIdx.x];
-    rz_partials[(int64_t)blockIdx.x * kMaxNev + threadIdx.x] = a;
-  }
-}
-
-// Fixed-order block sum of column c's partials (stride between blocks given).
-__device__ double block_reduce_col(const double *parts, int64_t stride, int nparts) {
-  __shared__ double sh[256];
+// out[c] = sum of column c's product partials (when there are more than
+// kCgParts of them), one block per column, fixed order.
+__global__ __launch_bounds__(1024) void k_cg_pap(const double *parts, int nparts, double *out) {
+  __shared__ double sh[16];
+  const double *x = parts + (int64_t)blockIdx.x * kMaxNormBlocks;
   double a = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += blockDim.x) a += parts[(int64_t)b * stride];
-  sh[threadIdx.x] = a;
+  for (int b = threadIdx.x; b < nparts; b += 1024) a += x[b];
+  for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
   __syncthreads();
-  for (int off = blockDim.x / 2; off >= 1; off >>= 1) {
-    if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-// r^T z of the step: init (first preconditioned residual) or update with beta
-// and the convergence test r^T z <= tol^2 f^T J f.
-__global__ __launch_bounds__(256) void k_cg_rz(const double *rz_partials, int nparts, int nev,
-                                               double tol2, int init, CgState *st) {
-  for (int c = 0; c < nev; ++c) {
-    const double rz = block_reduce_col(rz_partials + c, kMaxNev, nparts);
-    if (threadIdx.x == 0) {
-      if (init) {
-        st->rz0[c] = rz;
-        st->rz[c] = rz;
-        st->done[c] = !(rz > 0.0);
-        st->alpha[c] = 0.0;
-        st->beta[c] = 0.0;
-      } else {
-        const bool was = st->done[c] != 0;
-        const bool conv = was || rz <= tol2 * st->rz0[c];
-        st->beta[c] = conv ? 0.0 : rz / st->rz[c];
-        st->rz[c] = rz;
-        st->done[c] = conv ? 1 : 0;
-      }
-    }
-  }
-  if (threadIdx.x == 0 && init) {
-    st->iters = 0;
-    st->breakdown = 0;
+  if (threadIdx.x == 0) {
+    double r = 0.0;
+    for (int q = 0; q < 16; ++q) r += sh[q];
+    out[(int64_t)blockIdx.x * kMaxNormBlocks] = r;
   }
 }
 
-// alpha = r^T z / p^T A p from the product's per-block p^T A p partials
-// (sum-major, kMaxNormBlocks apart); a column whose p^T A p is not positive
-// stops (breakdown flag).
-__global__ __launch_bounds__(256) void k_cg_alpha(const double *pap_partials, int nparts,
-                                                  int nev, CgState *st) {
-  bool any = false;
-  for (int c = 0; c < nev; ++c) {
-    const double pap = block_reduce_col(pap_partials + (int64_t)c * kMaxNormBlocks, 1, nparts);
-    if (threadIdx.x == 0) {
-      double al = 0.0;
-      if (!st->done[c]) {
-        if (pap > 0.0) {
-          al = st->rz[c] / pap;
-          any = true;
-        } else {
-          st->done[c] = 1;
-          st->breakdown = 1;
+// x += alpha p, r -= alpha A p (pap: the product's partials, sum-major, or
+// null for no step), then the block's sums of M, G and r^T z over its tiles,
+// stored value-major (value v of block b at sums[v * gridDim.x + b]).  Each
+// tile's V, r, z and b are staged in LDS; a thread owns one (j, k) pair of
+// every ng-th row of the tile, and the groups are added in order at the end.
+// kItems: pairs of a tile per thread, 1 for rows of up to 8 columns, else 2.
+template <int kItems>
+__global__ __launch_bounds__(256) void k_cg_update(double *MU, double *R, const double *P,
+                                                   const double *AP, const double *Vp,
+                                                   const double *pap, int nparts,
+                                                   const CgState *st, CgAlpha *alpha_out,
+                                                   const double *d, const double *bd,
+                                                   AdjParams p, int64_t n, int ld, int64_t ntiles,
+                                                   double *sums) {
+  extern __shared__ d2 cg_lds[];
+  __shared__ double al[kMaxNev], wsum[kMaxNev], sb[kCgTile];
+  __shared__ double sh[3][256];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int nev = p.nev, h = ld / 2;
+  d2 *sV = cg_lds, *sR = sV + kCgTile * h, *sZ = sR + kCgTile * h;
+  const double *fV = reinterpret_cast<const double *>(sV);
+  const double *fR = reinterpret_cast<const double *>(sR);
+  const double *fZ = reinterpret_cast<const double *>(sZ);
+  const int np = nev * nev, ng = 256 / np;
+  const int grp = t / np, pr = t - grp * np;
+  const int j = pr / nev, k = pr - j * nev;
+  const bool live = grp < ng;
+  double m = 0.0, g = 0.0, rz = 0.0;
+  // this thread's column of the state, read ahead of the partials
+  const bool col = pap && t < nev;
+  const int done0 = col ? st->done[t] : 1;
+  const double rz0 = col ? st->rz[t] : 0.0;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int64_t r0 = tile * kCgTile;
+    const int rows = (int)min((int64_t)kCgTile, n - r0);
+    // all loads of the tile first: the first tile's are in flight while the
+    // alphas are formed
+    d2 r[kItems], v[kItems], x[kItems], pv[kItems], ap[kItems];
+    double di[kItems], bi[kItems];
+    int cc[kItems];
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      const int e = t + 256 * u;
+      if (e < rows * h) {
+        const int row = e / h;
+        const int64_t i = r0 + row, q = r0 * h + e;
+        cc[u] = 2 * (e - row * h);
+        r[u] = reinterpret_cast<const d2 *>(R)[q];
+        v[u] = reinterpret_cast<const d2 *>(Vp)[q];
+        di[u] = d[i];
+        bi[u] = bd ? bd[i] : 1.0;
+        if (pap) {
+          x[u] = reinterpret_cast<const d2 *>(MU)[q];
+          pv[u] = reinterpret_cast<const d2 *>(P)[q];
+          ap[u] = reinterpret_cast<const d2 *>(AP)[q];
         }
       }
-      st->alpha[c] = al;
     }
+    if (pap && tile == blockIdx.x) {
+      // one wave per column
+      for (int c = wave; c < nev; c += 4) {
+        const double *q = pap + (int64_t)c * kMaxNormBlocks;
+        double a = 0.0;
+#pragma unroll 4
+        for (int b = lane; b < nparts; b += 64) a += q[b];
+        for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
+        if (lane == 0) wsum[c] = a;
+      }
+      __syncthreads();
+      if (t < kMaxNev) {
+        double a = 0.0;
+        int broke = 0, any = 0;
+        if (!done0) {
+          const double q = wsum[t];
+          if (q > 0.0) {
+            a = rz0 / q;
+            any = 1;
+          } else {
+            broke = 1;
+          }
+        }
+        al[t] = a;
+        if (blockIdx.x == 0) {
+          alpha_out->broke[t] = broke;
+          const unsigned long long who = __ballot(any);
+          if (t == 0) alpha_out->any = who ? 1 : 0;
+        }
+      }
+      __syncthreads();
+    }
+    if (t < rows) sb[t] = bd ? bd[r0 + t] : 1.0;
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      const int e = t + 256 * u;
+      if (e < rows * h) {
+        const int c = cc[u];
+        const int64_t q = r0 * h + e;
+        if (pap) {
+          const d2 a = {al[c], al[c + 1]};
+          reinterpret_cast<d2 *>(MU)[q] = x[u] + a * pv[u];
+          r[u] -= a * ap[u];
+          reinterpret_cast<d2 *>(R)[q] = r[u];
+        }
+        sV[e] = v[u];
+        sR[e] = r[u];
+        // padding columns: r = 0 there
+        sZ[e] = d2{r[u][0] / cg_diag(di[u], bi[u], p.lam[c]),
+                   c + 1 < nev ? r[u][1] / cg_diag(di[u], bi[u], p.lam[c + 1]) : 0.0};
+      }
+    }
+    __syncthreads();
+    if (live) {
+#pragma unroll 4
+      for (int row = grp; row < rows; row += ng) {
+        const double vv = fV[row * ld + j], z = fZ[row * ld + k], rr = fR[row * ld + k];
+        m = fma(vv, sb[row] * z, m);
+        g = fma(vv, rr, g);
+        rz = fma(rr, z, rz);
+      }
+    }
+    __syncthreads();
   }
-  if (threadIdx.x == 0 && any) st->iters += 1;
+  sh[0][t] = live ? m : 0.0;
+  sh[1][t] = live ? g : 0.0;
+  sh[2][t] = live ? rz : 0.0;
+  __syncthreads();
+  if (t < np) {
+    double a = 0.0, b = 0.0, c = 0.0;
+#pragma unroll 4
+    for (int q = 0; q < ng; ++q) {
+      a += sh[0][q * np + t];
+      b += sh[1][q * np + t];
+      c += sh[2][q * np + t];
+    }
+    sums[(int64_t)t * gridDim.x + blockIdx.x] = a;
+    sums[(int64_t)(np + t) * gridDim.x + blockIdx.x] = b;
+    if (t < nev) sums[(int64_t)(2 * np + t) * gridDim.x + blockIdx.x] = c;
+  }
 }
 
-// p = z + beta p (first step: p = z)
-__global__ void k_cg_xpby(double *P, const double *Z, const CgState *st, int first,
-                          int64_t n, int ld, int nev) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * ld;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(e % ld);
-    if (k >= nev) { P[e] = 0.0; continue; }
-    P[e] = first ? Z[e] : Z[e] + st->beta[k] * P[e];
+// red[v] = sum of value v over the nb blocks, one block per value, fixed order
+__global__ __launch_bounds__(256) void k_cg_reduce(const double *sums, int nb, double *red) {
+  __shared__ double sh[4];
+  const double *x = sums + (int64_t)blockIdx.x * nb;
+  double a = 0.0;
+  for (int b = threadIdx.x; b < nb; b += 256) a += x[b];
+  for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) red[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// p = z - V M + beta p, and the state after the step: r^T z', beta and the
+// convergence test r^T z' <= tol^2 f^T J f (init: the first preconditioned
+// residual, p = z').
+__global__ __launch_bounds__(256) void k_cg_direction(double *P, const double *R,
+                                                      const double *Vp, const double *red,
+                                                      const CgState *st, const CgAlpha *alpha,
+                                                      CgState *st_out, const double *d,
+                                                      const double *bd, AdjParams p, int64_t n,
+                                                      int ld, double tol2, int init) {
+  __shared__ double sM[2 * kMaxNev * kMaxNev], beta[kMaxNev];
+  const int t = threadIdx.x, nev = p.nev, np = nev * nev, h = ld / 2;
+  // a block takes rc rows at a time, one pair of columns per thread; its
+  // first elements and the state are read ahead of the small sums
+  const int rc = 256 / h, row = t / h, c = 2 * (t - row * h);
+  const int64_t i0 = row < rc ? (int64_t)blockIdx.x * rc + row : n;
+  d2 r0 = {0.0, 0.0}, q0 = {0.0, 0.0};
+  double d0 = 1.0, b0 = 1.0;
+  if (i0 < n) {
+    r0 = reinterpret_cast<const d2 *>(R)[i0 * h + (c >> 1)];
+    if (!init) q0 = reinterpret_cast<const d2 *>(P)[i0 * h + (c >> 1)];
+    d0 = d[i0];
+    if (bd) b0 = bd[i0];
+  }
+  const bool col = !init && t < nev;
+  const double rz0_old = col ? st->rz0[t] : 0.0, rz_old = col ? st->rz[t] : 1.0;
+  const int done_old = col ? st->done[t] | alpha->broke[t] : 0;
+  for (int e = t; e < 2 * np; e += 256) sM[e] = red[e];
+  double rz = t < nev ? red[2 * np + t] : 0.0;
+  __syncthreads();
+  if (t < nev) {
+#pragma unroll 4
+    for (int j = 0; j < nev; ++j) rz = fma(-sM[np + j * nev + t], sM[j * nev + t], rz);
+    double rz0, b = 0.0;
+    int done;
+    if (init) {
+      rz0 = rz;
+      done = !(rz > 0.0);
+    } else {
+      rz0 = rz0_old;
+      done = done_old || rz <= tol2 * rz0;
+      b = done ? 0.0 : rz / rz_old;
+    }
+    beta[t] = b;
+    if (blockIdx.x == 0) {
+      st_out->rz[t] = rz;
+      st_out->rz0[t] = rz0;
+      st_out->done[t] = done;
+    }
+  } else if (t < kMaxNev) {
+    beta[t] = 0.0;
+  }
+  if (blockIdx.x == 0 && t == 0) {
+    int broke = init ? 0 : st->breakdown;
+    if (!init)
+      for (int c = 0; c < nev; ++c) broke |= alpha->broke[c];
+    st_out->breakdown = broke;
+    st_out->iters = init ? 0 : st->iters + alpha->any;
+  }
+  __syncthreads();
+  const bool two = c + 1 < nev;
+  for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * rc) {
+    const int64_t e = i * h + (c >> 1);
+    d2 r = r0, q = q0;
+    double di = d0, bi = b0;
+    if (i != i0) {
+      r = reinterpret_cast<const d2 *>(R)[e];
+      if (!init) q = reinterpret_cast<const d2 *>(P)[e];
+      di = d[i];
+      bi = bd ? bd[i] : 1.0;
+    }
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < nev; ++j) {
+      const double v = Vp[i * ld + j];
+      s0 = fma(v, sM[j * nev + c], s0);
+      if (two) s1 = fma(v, sM[j * nev + c + 1], s1);
+    }
+    d2 o = {r[0] / cg_diag(di, bi, p.lam[c]) - s0,
+            two ? r[1] / cg_diag(di, bi, p.lam[c + 1]) - s1 : 0.0};
+    if (!init) {
+      o[0] += beta[c] * q[0];
+      if (two) o[1] += beta[c + 1] * q[1];
+    }
+    reinterpret_cast<d2 *>(P)[e] = o;
   }
 }
 
@@ -365,7 +524,6 @@ __global__ __launch_bounds__(256) void k_add_vertex_terms(int64_t n, const IdxT 
 }
 
 constexpr int kSmallBlocks = 1024;
-constexpr int kDotBlocks = 1024;
 constexpr int kCgCheck = 8;   // CG steps between host reads of the flags
 
 }  // namespace
@@ -374,14 +532,15 @@ size_t adjoint_scratch_bytes(int64_t n, int nev) {
   const int ld = padded_ld(nev, 8);
   size_t blk = align_up(sizeof(double) * n * nev, 256);
   size_t blkp = align_up(sizeof(double) * n * ld, 256);
-  // 2 blocks of the normalized transform and t, 6 padded CG blocks (V, mu,
-  // r, z, p, Ap), the product's dot partials, Gram and r^T z partials
-  return 2 * blk + align_up(sizeof(double) * n, 256) + 6 * blkp +
+  // 2 blocks of the normalized transform and t, 5 padded CG blocks (V, mu,
+  // r, p, Ap), the product's dot partials, Gram and projection partials
+  return 2 * blk + align_up(sizeof(double) * n, 256) + 5 * blkp +
          align_up(sizeof(double) * 2 * kMaxNev * kMaxNormBlocks, 256) +
          align_up(sizeof(double) * kSmallBlocks * kMaxNev * kMaxNev, 256) +
-         align_up(sizeof(double) * kDotBlocks * kMaxNev, 256) +
+         align_up(sizeof(double) * kCgBlocks * cg_sums(kMaxNev), 256) +
+         align_up(sizeof(double) * cg_sums(kMaxNev), 256) +
          align_up(sizeof(double) * kMaxNev * kMaxNev, 256) * 2 +
-         align_up(sizeof(CgState), 256) + 4096;
+         align_up(2 * sizeof(CgState), 256) + align_up(sizeof(CgAlpha), 256) + 4096;
 }
 
 int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
@@ -425,17 +584,17 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
   double *Vp = a.take<double>(blkp);
   double *MU = a.take<double>(blkp);
   double *Rr = a.take<double>(blkp);
-  double *Z = a.take<double>(blkp);
   double *Pp = a.take<double>(blkp);
   double *AP = a.take<double>(blkp);
   double *pap_parts = a.take<double>((size_t)2 * kMaxNev * kMaxNormBlocks);
   double *parts = a.take<double>((size_t)kSmallBlocks * kMaxNev * kMaxNev);
-  double *rz_parts = a.take<double>((size_t)kDotBlocks * kMaxNev);
+  double *sums = a.take<double>((size_t)kCgBlocks * cg_sums(kMaxNev));
+  double *red = a.take<double>(cg_sums(kMaxNev));
   double *Mdev = a.take<double>(kMaxNev * kMaxNev);
   double *Mdev2 = a.take<double>(kMaxNev * kMaxNev);
-  CgState *st = a.take<CgState>(1);
+  CgState *st = a.take<CgState>(2);        // the state before and after a step
+  CgAlpha *alpha = a.take<CgAlpha>(1);
   (void)Mdev2;
-  double *host = static_cast<double *>(pinned);
   const int64_t rpb = ceil_div(n, kSmallBlocks);
   const int nsb = (int)ceil_div(n, rpb);
   const unsigned gew = grid_for((int64_t)blkp, 256, 4096);
@@ -485,25 +644,28 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
                        (const double *)Mdev, n, nev, ld, Rr);
     hipLaunchKernelGGL(k_pad_cols, dim3(gew), dim3(256), 0, s, (const double *)nullptr, 0, MU,
                        ld, n);
-    const unsigned gproj = grid_for(n, 256 / ld, kDotBlocks);
-    // z = (I - V V^T B) J r and r^T z; first == the step that has no update
-    auto precond = [&](bool update) {
-      hipLaunchKernelGGL(k_cg_step_jac, dim3(gew), dim3(256), 0, s, MU, Rr,
-                         (const double *)Pp, (const double *)AP,
-                         update ? (const CgState *)st : nullptr, d64, bd, prm, n, ld, Z);
-      gram_small(Vp, ld, Z, ld, bd, Mdev);   // V^T B Z
-      hipLaunchKernelGGL(k_cg_project, dim3(gproj), dim3(256), 0, s, Z, (const double *)Vp,
-                         (const double *)Mdev, (const double *)Rr, n, nev, ld, rz_parts);
-      hipLaunchKernelGGL(k_cg_rz, dim3(1), dim3(256), 0, s, (const double *)rz_parts,
-                         (int)gproj, nev, cg_tol * cg_tol, update ? 0 : 1, st);
+    const int64_t ntiles = ceil_div(n, kCgTile);
+    const unsigned gu = (unsigned)std::min<int64_t>(ntiles, kCgBlocks);
+    const size_t lds = 3 * sizeof(double) * kCgTile * ld;
+    const unsigned gd = grid_for(n, 256 / (ld / 2), 4096);
+    // after the product: np partials of p^T A p (0: the first residual)
+    auto step_tail = [&](int np, int cur) {
+      auto update = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(gu), dim3(256), lds, s, MU, Rr, (const double *)Pp,
+                           (const double *)AP, (const double *)Vp,
+                           np ? (const double *)pap_parts : (const double *)nullptr, np,
+                           (const CgState *)(st + cur), alpha, d64, bd, prm, n, ld, ntiles,
+                           sums);
+      };
+      if (ld <= 8) update(k_cg_update<1>);
+      else update(k_cg_update<2>);
+      hipLaunchKernelGGL(k_cg_reduce, dim3(cg_sums(nev)), dim3(256), 0, s, (const double *)sums,
+                         (int)gu, red);
+      hipLaunchKernelGGL(k_cg_direction, dim3(gd), dim3(256), 0, s, Pp, (const double *)Rr,
+                         (const double *)Vp, (const double *)red, (const CgState *)(st + cur),
+                         (const CgAlpha *)alpha, st + (np ? 1 - cur : cur), d64, bd, prm, n, ld,
+                         cg_tol * cg_tol, np ? 0 : 1);
     };
-    precond(false);
-    hipLaunchKernelGGL(k_cg_xpby, dim3(gew), dim3(256), 0, s, Pp, (const double *)Z,
-                       (const CgState *)st, 1, n, ld, nev);
-    if (hipGetLastError() != hipSuccess) {
-      *err = "adjoint CG launch failed";
-      return SPHX_E_HIP;
-    }
     EpiShiftDotP<double> ep{AP, ld, nullptr, bd};
     double *lam_dev = Mdev2;   // lam_k on the device for the product's epilogue
     if (hipMemcpyAsync(lam_dev, prm.lam, sizeof(double) * kMaxNev, hipMemcpyHostToDevice, s) !=
@@ -512,36 +674,69 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
       return SPHX_E_HIP;
     }
     ep.lam = lam_dev;
-    CgState hs{};
-    int it = 0;
-    bool all = false;
-    while (it < cg_max_iter) {
-      const int steps = std::min(kCgCheck, cg_max_iter - it);
-      for (int q = 0; q < steps; ++q) {
-        int np = 0;
-        int r = vspmm_shiftdot<double>(g, plan, Pp, ld, nev, ep, pap_parts, &np, s);
-        if (r != SPHX_OK) {
-          *err = "adjoint CG product failed";
-          return r;
-        }
-        hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(256), 0, s, (const double *)pap_parts, np,
-                           nev, st);
-        precond(true);
-        hipLaunchKernelGGL(k_cg_xpby, dim3(gew), dim3(256), 0, s, Pp, (const double *)Z,
-                           (const CgState *)st, 0, n, ld, nev);
+    int cur = 0;
+    step_tail(0, cur);
+    // Batches of kCgCheck steps; the state after a batch is copied to pinned
+    // memory behind it and read while the next batch runs (steps past the
+    // last column's convergence leave x as it is).
+    struct Events {
+      hipEvent_t e[2] = {nullptr, nullptr};
+      ~Events() {
+        for (auto x : e)
+          if (x) (void)hipEventDestroy(x);
       }
-      it += steps;
-      if (hipGetLastError() != hipSuccess ||
-          hipMemcpyAsync(&hs, st, sizeof(CgState), hipMemcpyDeviceToHost, s) != hipSuccess ||
-          hipStreamSynchronize(s) != hipSuccess) {
+    } evs;
+    for (auto &x : evs.e)
+      if (hipEventCreateWithFlags(&x, hipEventDisableTiming) != hipSuccess) {
+        *err = "adjoint: event creation failed";
+        return SPHX_E_HIP;
+      }
+    static_assert(2 * sizeof(CgState) <= kPinnedSmallBytes, "pinned states");
+    CgState *hp = static_cast<CgState *>(pinned);
+    CgState hs{};
+    int it = 0, batches = 0, seen = 0;
+    bool all = false;
+    while (seen < batches || it < cg_max_iter) {
+      if (it < cg_max_iter) {
+        const int steps = std::min(kCgCheck, cg_max_iter - it);
+        for (int q = 0; q < steps; ++q) {
+          int np = 0;
+          int r = vspmm_shiftdot<double>(g, plan, Pp, ld, nev, ep, pap_parts, &np, s);
+          if (r != SPHX_OK) {
+            (void)hipStreamSynchronize(s);
+            *err = "adjoint CG product failed";
+            return r;
+          }
+          if (np > kCgParts) {
+            hipLaunchKernelGGL(k_cg_pap, dim3(nev), dim3(1024), 0, s,
+                               (const double *)pap_parts, np, pap_parts);
+            np = 1;
+          }
+          step_tail(np, cur);
+          cur = 1 - cur;
+        }
+        it += steps;
+        const int slot = batches & 1;
+        if (hipGetLastError() != hipSuccess ||
+            hipMemcpyAsync(hp + slot, st + cur, sizeof(CgState), hipMemcpyDeviceToHost, s) !=
+                hipSuccess ||
+            hipEventRecord(evs.e[slot], s) != hipSuccess) {
+          *err = "adjoint CG failed";
+          return SPHX_E_HIP;
+        }
+        ++batches;
+        if (batches - seen < 2 && it < cg_max_iter) continue;
+      }
+      if (hipEventSynchronize(evs.e[seen & 1]) != hipSuccess) {
         *err = "adjoint CG failed";
         return SPHX_E_HIP;
       }
+      hs = hp[seen & 1];
+      ++seen;
       all = true;
       for (int k = 0; k < nev; ++k) all = all && hs.done[k];
       if (all) break;
     }
-    (void)host;
     double worst = 0.0;
     for (int k = 0; k < nev; ++k)
       if (hs.rz0[k] > 0.0) worst = std::max(worst, std::sqrt(std::max(0.0, hs.rz[k] / hs.rz0[k])));

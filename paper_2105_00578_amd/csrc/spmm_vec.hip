@@ -167,6 +167,7 @@ struct VResidual {
   int m;
   bool store_lx = true;   // false: L X is already in p.LX (streaming pass)
   static constexpr bool kNorms = true;
+  static constexpr bool kBoth = true;
   using V = typename Vec<T, VB>::type;
   static constexpr int E = Vec<T, VB>::E;
   __device__ void row(int64_t i, const V (&xi)[NV], const V (&acc)[NV], double *n1,
@@ -203,6 +204,7 @@ struct VShiftDot {
   EpiShiftDotP<T> p;
   int m;
   static constexpr bool kNorms = true;
+  static constexpr bool kBoth = false;
   using V = typename Vec<T, VB>::type;
   static constexpr int E = Vec<T, VB>::E;
   __device__ void row(int64_t i, const V (&xi)[NV], const V (&acc)[NV], double *n1,
@@ -286,7 +288,8 @@ struct VPoly {
 
 // Per-column block sums of the thread norms (columns < m), fixed order:
 // butterfly within each wavefront, then the 4 wavefronts in order.
-template <int LD>
+// kBoth false: only the first of the two sums is wanted and stored.
+template <int LD, bool kBoth>
 __device__ void block_norms(const double (&n1)[LD], const double (&n2)[LD], int m,
                             double *partials, int slot) {
   __shared__ double sh[4][2 * kMaxNev];
@@ -297,21 +300,23 @@ __device__ void block_norms(const double (&n1)[LD], const double (&n2)[LD], int 
     double a = n1[c], b = n2[c];
     for (int off = 32; off >= 1; off >>= 1) {
       a += __shfl_xor(a, off);
-      b += __shfl_xor(b, off);
+      if constexpr (kBoth) b += __shfl_xor(b, off);
     }
     if (lane == 0) {
       sh[wave][c] = a;
-      sh[wave][kMaxNev + c] = b;
+      if constexpr (kBoth) sh[wave][kMaxNev + c] = b;
     }
   }
   __syncthreads();
   const int t = threadIdx.x;
   if (t < m) {
     double a = sh[0][t] + sh[1][t] + sh[2][t] + sh[3][t];
-    double b = sh[0][kMaxNev + t] + sh[1][kMaxNev + t] + sh[2][kMaxNev + t] +
-               sh[3][kMaxNev + t];
     partials[(int64_t)t * kMaxNormBlocks + slot] = a;
-    partials[(int64_t)(kMaxNev + t) * kMaxNormBlocks + slot] = b;
+    if constexpr (kBoth) {
+      double b = sh[0][kMaxNev + t] + sh[1][kMaxNev + t] + sh[2][kMaxNev + t] +
+                 sh[3][kMaxNev + t];
+      partials[(int64_t)(kMaxNev + t) * kMaxNormBlocks + slot] = b;
+    }
   }
 }
 
@@ -340,7 +345,7 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, const int32_t *__
     vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, X, ldv, xi, acc);
     epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
 template <typename T, int VB, int NV>
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A,
     group_sum<T, VB, NV, G>(acc);
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
 // Rows of 13..48 neighbours in natural order (mesh-like graphs), G lanes per
@@ -471,7 +476,7 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
     }
     __syncthreads();
   }
-  if constexpr (Epi::kNorms) block_norms<LD>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
 // Hub rows, pass 1: one wavefront per chunk -> partial row sums (as double).
@@ -538,7 +543,7 @@ __global__ __launch_bounds__(256) void k_vhub_combine(const int32_t *__restrict_
         for (int e = 0; e < E; ++e) acc[v][e] += T(part[q * kMaxNev + v * E + e]);
     epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
 // The residual epilogue as a streaming pass over an L X that a store product
@@ -567,7 +572,7 @@ __global__ __launch_bounds__(256) void k_resid_rows(int64_t n, const T *__restri
     }
     epi.row(i, xi, acc, n1, n2);
   }
-  block_norms<LD>(n1, n2, m, partials, (int)blockIdx.x);
+  block_norms<LD, true>(n1, n2, m, partials, (int)blockIdx.x);
 }
 
 template <typename T>

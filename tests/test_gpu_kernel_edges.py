@@ -35,3 +35,35 @@ def test_rayleigh_ritz_orders(handle, w, m):
     assert np.allclose(th, ref, rtol=0, atol=1e-12 * scale)
     assert np.allclose(Y.T @ GB @ Y, np.eye(m), atol=1e-12)
     assert np.allclose(GA @ Y, GB @ Y @ np.diag(th), atol=1e-12 * np.linalg.norm(GA))
+
+
+@pytest.mark.parametrize("n,nev,gen", [(63, 1, 0), (64, 2, 1), (65, 3, 0), (128, 5, 1),
+                                       (129, 8, 0), (140, 9, 1), (90, 16, 1)])
+def test_adjoint_cg_edges(handle, n, nev, gen):
+    """Row counts around the CG's 64-row tiles, odd and even widths, one and
+    two pairs of columns per thread, against the dense gradient.  Both solves
+    stop at 1e-13 of the right-hand side and the gap terms of these spectra
+    are above 1e-4: 1e-8 of the largest entry."""
+    import torch
+    import paper_2105_00578_amd as sx
+    from oracle import adjoint
+    from tests.gpu_util import dev, random_graph, upload
+    g = random_graph(n, 6.0 / n, n + nev, np.float64)
+    rp, col, w = upload(g)
+    G = sx.Graph(handle, rp, col, w)
+    rng = np.random.default_rng(nev)
+    a = rng.standard_normal(nev)
+    C = rng.standard_normal((g.n, nev))
+    problem = sx.GENERALIZED if gen else sx.COMBINATORIAL
+    gd, lam, V = adjoint.grad_dense(g.rowptr, g.col, g.w, problem, nev, a, C)
+    args = (handle, G, problem, lam, torch.from_numpy(V).to(dev()), a,
+            torch.from_numpy(C).to(dev()))
+    grad = sx.eig_backward(*args, cg_tol=1e-13, cg_max_iter=5000).cpu().numpy()
+    assert np.abs(grad - gd).max() <= 1e-8 * np.abs(gd).max()
+    its, res = sx.backward_info(handle)
+    assert 0 < its <= 5000 and res <= 1e-13
+    # a limit inside a batch of steps is kept, and reported
+    if its > 3:
+        sx.eig_backward(*args, cg_tol=1e-13, cg_max_iter=3, allow_not_converged=True)
+        its3, res3 = sx.backward_info(handle)
+        assert its3 == 3 and res3 > 1e-13
