@@ -303,19 +303,23 @@ __global__ void k_expand_cols(const T *Hc, int lda, ColMap act, T *H, int ld, in
   }
 }
 
-// Row width of the compacted Chebyshev block for na active columns: even,
-// so that FP32 rows are whole 8-byte vectors and FP64 rows 16-byte ones.
-inline int compact_ld(int na) { return (na + 1) / 2 * 2; }
+// Row width of the compacted polynomial block for na active columns: exactly
+// those (the vector-row products take any width of at least 2).  The 25 steps
+// of an apply are bound by the bytes of their four blocks; rounding the width
+// up to whole vectors cost 1/7 of them at 7 FP32 columns.
+inline int compact_ld(int na) { return na < 2 ? 2 : na; }
 
 // H[:, cm] = p(L) R[:, cm]: returns the buffer holding the result (n x ld,
 // the columns of cm).  With `spare` (an n x ld buffer whose contents may be
 // destroyed, e.g. R itself) and fewer active columns than the padded width,
-// the iteration runs on a compacted block of the active columns only.
+// the iteration runs on a compacted block of the active columns only.  With
+// `dst` (n x ld, not overlapping the other buffers) the last step writes there
+// (without `spare` only).
 template <typename T>
 int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int ld,
                const ColMap &cm, const T *R, T *B1, T *B2, T *spare, const ChebCoef &k,
                const double *dinv, hipStream_t s, T **result, int64_t *calls,
-               int64_t *pcalls) {
+               int64_t *pcalls, T *dst = nullptr) {
   const int rd = dinv ? 1 : 0;
   const double b3 = spmm_bytes(g, plan, cm.count, sizeof(T), 3, rd);
   const double b4 = spmm_bytes(g, plan, cm.count, sizeof(T), 4, rd);
@@ -326,10 +330,10 @@ int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
   const int wd = compact ? lda : ld;     // row width of the iteration buffers
   const int mm = compact ? na : m;
   auto launch = [&](const T *src, EpiChebP<T> e, double bytes) -> int {
-    // padded rows (the solver's blocks) take the vector-row kernels; the
-    // column-lane kernels serve unpadded caller blocks
+    // rows of at least two values take the vector-row kernels; the
+    // column-lane kernels serve a caller's single column
     int st;
-    if (compact || ld != m || (m * (int)sizeof(T)) % 16 == 0) {
+    if (wd >= 2) {
       LaunchEvents ev;
       const bool timed = h->plog.begin_stamped(PH_PRECOND, bytes, &ev.start, &ev.stop);
       st = vspmm_cheb<T>(g, plan, src, wd, mm, e, s, timed ? &ev : nullptr);
@@ -385,20 +389,23 @@ int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
     h1 = B2;
     h1_scale = 1.0;
   }
-  SPHX_TRY(launch(h1, epi(nullptr, 1.0, it1, h1_scale, 0), b3));
-  T *cur = it1, *other = slot;
   const int deg = (int)k.alpha.size();
+  auto out = [&](int st, T *b) { return dst && !compact && st == deg - 1 ? dst : b; };
+  T *cur = out(0, it1), *other = slot;
+  SPHX_TRY(launch(h1, epi(nullptr, 1.0, cur, h1_scale, 0), b3));
   if (deg >= 2) {
     // step 2: the previous iterate is h1 (scaled, possibly in `slot`, which
     // is then overwritten in place by h3)
-    SPHX_TRY(launch(it1, epi(h1, h1_scale, slot, 1.0, 1), b4));
-    cur = slot;
+    cur = out(1, slot);
+    SPHX_TRY(launch(it1, epi(h1, h1_scale, cur, 1.0, 1), b4));
     other = it1;
     // later steps overwrite the older iterate in place (each element is read
     // and written by the same lane only)
     for (int st = 2; st < deg; ++st) {
-      SPHX_TRY(launch(cur, epi(other, 1.0, other, 1.0, st), b4));
-      std::swap(cur, other);
+      T *o = out(st, other);
+      SPHX_TRY(launch(cur, epi(other, 1.0, o, 1.0, st), b4));
+      other = cur;
+      cur = o;
     }
   }
   if (compact) {
@@ -1032,9 +1039,9 @@ int sphx_laplacian_apply(sphx_handle *h, sphx_graph *g, int problem, int m, int 
     src = tmp;
   }
   ColMap cm = identity_map(m);
-  // rows that are whole 16-byte vectors take the vector-row kernels
-  const bool vec = (m * bytes_of(dtype)) % 16 == 0 && ((uintptr_t)src % 16) == 0 &&
-                   ((uintptr_t)Y % 16) == 0;
+  // rows of at least two values take the vector-row kernels (their vectors
+  // need no more than the elements' alignment)
+  const bool vec = m >= 2;
   int r;
   if (dtype == SPHX_F32)
     r = vec ? vspmm_store<float>(g, plan, (const float *)src, m, m,
@@ -1128,25 +1135,23 @@ int sphx_precond_apply(sphx_handle *h, sphx_graph *g, const sphx_options *o, int
     h->plog.reset();
     h->plog.on = false;
     const double *post = norm ? sq : nullptr;
-    if (dtype == SPHX_F32) {
-      float *res = nullptr;
-      SPHX_TRY(cheb_apply<float>(h, g, plan, m, m, cm, (const float *)R, (float *)b1,
-                                 (float *)b2, nullptr, ck, dv, s, &res, &calls, &pcalls));
+    // the last step writes H itself unless H shares memory with R, which the
+    // steps still read
+    const uintptr_t ra = (uintptr_t)R, ha = (uintptr_t)H;
+    const bool direct = !post && (ha + blk <= ra || ra + blk <= ha);
+    auto go = [&](auto tag) -> int {
+      using T = decltype(tag);
+      T *res = nullptr;
+      SPHX_TRY(cheb_apply<T>(h, g, plan, m, m, cm, (const T *)R, (T *)b1, (T *)b2, nullptr, ck,
+                             dv, s, &res, &calls, &pcalls, direct ? (T *)H : nullptr));
       if (post)
-        hipLaunchKernelGGL(k_scale_rows<float>, dim3(grid_for(n * m, 256, 4096)), dim3(256), 0,
-                           s, (const float *)res, post, 1.0, (float *)H, n, m);
-      else
+        hipLaunchKernelGGL(k_scale_rows<T>, dim3(grid_for(n * m, 256, 4096)), dim3(256), 0, s,
+                           (const T *)res, post, 1.0, (T *)H, n, m);
+      else if (!direct)
         SPHX_HIP(h, hipMemcpyAsync(H, res, blk, hipMemcpyDeviceToDevice, s));
-    } else {
-      double *res = nullptr;
-      SPHX_TRY(cheb_apply<double>(h, g, plan, m, m, cm, (const double *)R, (double *)b1,
-                                  (double *)b2, nullptr, ck, dv, s, &res, &calls, &pcalls));
-      if (post)
-        hipLaunchKernelGGL(k_scale_rows<double>, dim3(grid_for(n * m, 256, 4096)), dim3(256),
-                           0, s, (const double *)res, post, 1.0, (double *)H, n, m);
-      else
-        SPHX_HIP(h, hipMemcpyAsync(H, res, blk, hipMemcpyDeviceToDevice, s));
-    }
+      return SPHX_OK;
+    };
+    SPHX_TRY(dtype == SPHX_F32 ? go(float{}) : go(double{}));
   }
   SPHX_HIP(h, hipGetLastError());
   return SPHX_OK;

@@ -1,8 +1,13 @@
 // Laplacian block product Y = L_C X over padded row-major blocks (Eq. 2 with
 // weights, difference form y_i = sum_j w_ij (x_i - x_j)).
 //
-// The LOBPCG blocks are n x ld with ld * sizeof(T) a multiple of 16 bytes,
-// so a row is NV = ld * sizeof(T) / 16 aligned 16-byte vectors.  Short rows
+// A row of ld values is read as NV vectors of E values: vector v starts at
+// value v E, the last one at ld - E, so that a width that is no multiple of E
+// makes the last two overlap (the shared values are computed twice, to the
+// same bits) and nothing outside the row is touched.  Vectors are only aligned
+// to their elements.  The LOBPCG blocks are padded to whole 16-byte vectors;
+// the polynomial's blocks and the caller's have exactly their columns.  Short
+// rows
 // are handled one thread per row: the thread keeps x_i and the NV-vector
 // accumulator in registers and gathers each neighbour row with NV vector
 // loads (adjacent threads take adjacent rows, so on mesh-like graphs the
@@ -32,16 +37,39 @@ namespace {
 template <typename T, int VB> struct Vec;
 template <> struct Vec<float, 16> {
   typedef float type __attribute__((ext_vector_type(4)));
+  typedef type mem __attribute__((aligned(4)));
   static constexpr int E = 4;
 };
 template <> struct Vec<float, 8> {
   typedef float type __attribute__((ext_vector_type(2)));
+  typedef type mem __attribute__((aligned(4)));
   static constexpr int E = 2;
 };
 template <> struct Vec<double, 16> {
   typedef double type __attribute__((ext_vector_type(2)));
+  typedef type mem __attribute__((aligned(8)));
   static constexpr int E = 2;
 };
+
+// The row of ld values at p, and its store; `last` = ld - E.
+template <typename T, int VB, int NV>
+__device__ __forceinline__ void load_row(const T *__restrict__ p, int last,
+                                         typename Vec<T, VB>::type (&x)[NV]) {
+  using M = typename Vec<T, VB>::mem;
+  constexpr int E = Vec<T, VB>::E;
+#pragma unroll
+  for (int v = 0; v < NV - 1; ++v) x[v] = *reinterpret_cast<const M *>(p + v * E);
+  x[NV - 1] = *reinterpret_cast<const M *>(p + last);
+}
+template <typename T, int VB, int NV>
+__device__ __forceinline__ void store_row(T *p, int last,
+                                          const typename Vec<T, VB>::type (&x)[NV]) {
+  using M = typename Vec<T, VB>::mem;
+  constexpr int E = Vec<T, VB>::E;
+#pragma unroll
+  for (int v = 0; v < NV - 1; ++v) *reinterpret_cast<M *>(p + v * E) = x[v];
+  *reinterpret_cast<M *>(p + last) = x[NV - 1];
+}
 
 // Unit weights with the column indices stored as int16 offsets from the row
 // (graphs whose every neighbour lies within 32767 rows: two bytes per entry
@@ -93,8 +121,8 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t nb) {
 // fixed order.
 template <typename T, int VB, int NV, typename WT, typename Src>
 __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, int64_t k1,
-                                         int step, const typename Vec<T, VB>::type *__restrict__ X,
-                                         int ldv, const typename Vec<T, VB>::type (&xi)[NV],
+                                         int step, const T *__restrict__ X, int ld, int last,
+                                         const typename Vec<T, VB>::type (&xi)[NV],
                                          typename Vec<T, VB>::type (&acc)[NV]) {
   using V = typename Vec<T, VB>::type;
   constexpr int U = NV <= 2 ? 4 : 2;
@@ -110,9 +138,7 @@ __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, in
     for (int u = 0; u < U; ++u) j[u] = A.nbr(i, k + u * step);
     V x[U][NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int v = 0; v < NV; ++v) x[u][v] = X[j[u] * ldv + v];
+    for (int u = 0; u < U; ++u) load_row<T, VB, NV>(X + j[u] * ld, last, x[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if constexpr (kUnitW<WT>) {
@@ -129,14 +155,15 @@ __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, in
 #pragma unroll
   for (int u = 0; u < U - 1; ++u) {
     if (k < k1) {
-      const int64_t j0 = A.nbr(i, k);
+      V x[NV];
+      load_row<T, VB, NV>(X + A.nbr(i, k) * ld, last, x);
       if constexpr (kUnitW<WT>) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) a[u][v] += xi[v] - X[j0 * ldv + v];
+        for (int v = 0; v < NV; ++v) a[u][v] += xi[v] - x[v];
       } else {
         const T w0 = T(A.wk(k));
 #pragma unroll
-        for (int v = 0; v < NV; ++v) a[u][v] += w0 * (xi[v] - X[j0 * ldv + v]);
+        for (int v = 0; v < NV; ++v) a[u][v] += w0 * (xi[v] - x[v]);
       }
       k += step;
     }
@@ -152,12 +179,11 @@ __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, in
 template <typename T, int VB, int NV>
 struct VStore {
   EpiStoreP<T> p;
+  int last;
   static constexpr bool kNorms = false;
   using V = typename Vec<T, VB>::type;
   __device__ void row(int64_t i, const V (&xi)[NV], const V (&acc)[NV], double *, double *) const {
-    V *y = reinterpret_cast<V *>(p.Y + i * p.ldy);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) y[v] = acc[v];
+    store_row<T, VB, NV>(p.Y + i * p.ldy, last, acc);
   }
 };
 
@@ -228,61 +254,68 @@ struct VShiftDot {
   }
 };
 
+// The polynomial epilogues read every vector of a row before they write one:
+// outputs may overwrite the previous iterate (or the sum) in place, and the
+// last two vectors may overlap.
 template <typename T, int VB, int NV>
 struct VCheb {
   EpiChebP<T> p;
+  int last;
   static constexpr bool kNorms = false;
   using V = typename Vec<T, VB>::type;
   static constexpr int E = Vec<T, VB>::E;
   __device__ void row(int64_t i, const V (&xi)[NV], const V (&acc)[NV], double *, double *) const {
     const double si = p.dinv ? p.dinv[i] : 1.0;
-    const V *rr = reinterpret_cast<const V *>(p.R + i * p.ld);
-    const V *pp = p.prev ? reinterpret_cast<const V *>(p.prev + i * p.ld) : nullptr;
-    V *out = reinterpret_cast<V *>(p.OUT + i * p.ld);
+    V r[NV], pv[NV], o[NV];
+    load_row<T, VB, NV>(p.R + i * p.ld, last, r);
+    if (p.prev) {
+      load_row<T, VB, NV>(p.prev + i * p.ld, last, pv);
+    } else {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const V r = rr[v];
-      const V pv = pp ? pp[v] : V(0);
-      V o;
+      for (int v = 0; v < NV; ++v) pv[v] = V(0);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const double xs = p.src_scale * double(xi[v][e]);
-        const double pr = p.prev_scale * double(pv[e]);
-        const double res = double(r[e]) - p.src_scale * double(acc[v][e]);
-        o[e] = T(xs + p.alpha * (xs - pr) + p.beta * si * res);
+        const double pr = p.prev_scale * double(pv[v][e]);
+        const double res = double(r[v][e]) - p.src_scale * double(acc[v][e]);
+        o[v][e] = T(xs + p.alpha * (xs - pr) + p.beta * si * res);
       }
-      out[v] = o;
-    }
+    store_row<T, VB, NV>(p.OUT + i * p.ld, last, o);
   }
 };
 
 template <typename T, int VB, int NV>
 struct VPoly {
   EpiPolyP<T> p;
+  int last;
   static constexpr bool kNorms = false;
   using V = typename Vec<T, VB>::type;
   static constexpr int E = Vec<T, VB>::E;
   __device__ void row(int64_t i, const V (&xi)[NV], const V (&acc)[NV], double *, double *) const {
     const double si = p.dinv ? p.dinv[i] : 1.0;
-    const V *yi = p.Yin ? reinterpret_cast<const V *>(p.Yin + i * p.ld) : nullptr;
-    V *yo = reinterpret_cast<V *>(p.Yout + i * p.ld);
-    V *po = p.last ? nullptr : reinterpret_cast<V *>(p.Pout + i * p.ld);
+    V y[NV], pn[NV];
+    if (p.Yin) {
+      load_row<T, VB, NV>(p.Yin + i * p.ld, last, y);
+    } else {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const V y0 = yi ? yi[v] : V(0);
-      V y, pn;
+      for (int v = 0; v < NV; ++v) y[v] = V(0);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const double pv = double(xi[v][e]);
         const double pnew = pv - si * double(acc[v][e]) * p.inv_t;
-        double yv = double(y0[e]) + pv * p.inv_t;
+        double yv = double(y[v][e]) + pv * p.inv_t;
         if (p.last) yv += pnew * p.inv_t_next;
-        y[e] = T(yv);
-        pn[e] = T(pnew);
+        y[v][e] = T(yv);
+        pn[v][e] = T(pnew);
       }
-      yo[v] = y;
-      if (po) po[v] = pn;
-    }
+    store_row<T, VB, NV>(p.Yout + i * p.ld, last, y);
+    if (!p.last) store_row<T, VB, NV>(p.Pout + i * p.ld, last, pn);
   }
 };
 
@@ -329,8 +362,7 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, const int32_t *__
                                               int m) {
   using V = typename Vec<T, VB>::type;
   constexpr int LD = NV * Vec<T, VB>::E;
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const int ldv = ld / Vec<T, VB>::E;
+  const int last = ld - Vec<T, VB>::E;
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   double n1[LD], n2[LD];
 #pragma unroll
@@ -340,9 +372,8 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, const int32_t *__
     if (r >= nrows) break;
     const int64_t i = rows ? rows[r] : r;
     V xi[NV], acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) xi[v] = X[i * ldv + v];
-    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, X, ldv, xi, acc);
+    load_row<T, VB, NV>(Xs + i * ld, last, xi);
+    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, Xs, ld, last, xi, acc);
     epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
@@ -395,8 +426,7 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A,
   using V = typename Vec<T, VB>::type;
   constexpr int LD = NV * Vec<T, VB>::E;
   constexpr int GPB = 256 / G;   // groups per block
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const int ldv = ld / Vec<T, VB>::E;
+  const int last = ld - Vec<T, VB>::E;
   const int gl = threadIdx.x & (G - 1);
   const bool strided = rpb == 0;
   const int64_t b = strided ? (int64_t)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
@@ -408,9 +438,8 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A,
   for (int64_t r = (strided ? b * GPB : b * rpb) + threadIdx.x / G; r < rend; r += step) {
     const int64_t i = rows ? rows[r] : r;
     V xi[NV], acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) xi[v] = X[i * ldv + v];
-    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, X, ldv, xi, acc);
+    load_row<T, VB, NV>(Xs + i * ld, last, xi);
+    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last, xi, acc);
     group_sum<T, VB, NV, G>(acc);
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
@@ -440,8 +469,7 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
   constexpr int R = 256 / G;   // rows per chunk
   __shared__ typename L::CT scol[kLdsEntries];
   __shared__ typename L::WS sw[kUnitW<WT> ? 1 : kLdsEntries];
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const int ldv = ld / Vec<T, VB>::E;
+  const int last = ld - Vec<T, VB>::E;
   const int gl = threadIdx.x & (G - 1);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t rend = min(nrows, (b + 1) * rpb);
@@ -462,14 +490,13 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
     const int64_t i = r0 + threadIdx.x / G;
     if (i < r1) {                       // uniform over each group of G lanes
       V xi[NV], acc[NV];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) xi[v] = X[i * ldv + v];
+      load_row<T, VB, NV>(Xs + i * ld, last, xi);
       const int64_t ka = (int64_t)A.rp[i] + gl, kb = (int64_t)A.rp[i + 1];
       if (staged) {
         const L S{scol, sw, k0};
-        vrow_acc<T, VB, NV, WT>(S, i, ka, kb, G, X, ldv, xi, acc);
+        vrow_acc<T, VB, NV, WT>(S, i, ka, kb, G, Xs, ld, last, xi, acc);
       } else {
-        vrow_acc<T, VB, NV, WT>(A, i, ka, kb, G, X, ldv, xi, acc);
+        vrow_acc<T, VB, NV, WT>(A, i, ka, kb, G, Xs, ld, last, xi, acc);
       }
       group_sum<T, VB, NV, G>(acc);
       if (gl == 0) epi.row(i, xi, acc, n1, n2);
@@ -488,8 +515,7 @@ __global__ __launch_bounds__(256) void k_vhub_partial(
     const T *__restrict__ Xs, int ld, double *out) {
   using V = typename Vec<T, VB>::type;
   constexpr int E = Vec<T, VB>::E;
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const int ldv = ld / E;
+  const int last = ld - E;
   const int lane = threadIdx.x & 63;
   for (int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < n_chunks;
        q += (int64_t)gridDim.x * 4) {
@@ -500,15 +526,15 @@ __global__ __launch_bounds__(256) void k_vhub_partial(
     }
     const int64_t i = hub_rows[lo];
     V xi[NV], acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) xi[v] = X[i * ldv + v];
-    vrow_acc<T, VB, NV, WT>(A, i, k0s[q] + lane, k1s[q], 64, X, ldv, xi, acc);
+    load_row<T, VB, NV>(Xs + i * ld, last, xi);
+    vrow_acc<T, VB, NV, WT>(A, i, k0s[q] + lane, k1s[q], 64, Xs, ld, last, xi, acc);
     wave_sum<T, VB, NV>(acc);
     if (lane == 0)
 #pragma unroll
       for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int e = 0; e < E; ++e) out[q * kMaxNev + v * E + e] = double(acc[v][e]);
+        for (int e = 0; e < E; ++e)
+          out[q * kMaxNev + (v < NV - 1 ? v * E : last) + e] = double(acc[v][e]);
   }
 }
 
@@ -522,8 +548,7 @@ __global__ __launch_bounds__(256) void k_vhub_combine(const int32_t *__restrict_
   using V = typename Vec<T, VB>::type;
   constexpr int E = Vec<T, VB>::E;
   constexpr int LD = NV * E;
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const int ldv = ld / E;
+  const int last = ld - E;
   double n1[LD], n2[LD];
 #pragma unroll
   for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
@@ -531,16 +556,15 @@ __global__ __launch_bounds__(256) void k_vhub_combine(const int32_t *__restrict_
        h += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = hub_rows[h];
     V xi[NV], acc[NV];
+    load_row<T, VB, NV>(Xs + i * ld, last, xi);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      xi[v] = X[i * ldv + v];
-      acc[v] = V(0);
-    }
+    for (int v = 0; v < NV; ++v) acc[v] = V(0);
     for (int64_t q = hub_chunk_begin[h]; q < hub_chunk_begin[h + 1]; ++q)
 #pragma unroll
       for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[v][e] += T(part[q * kMaxNev + v * E + e]);
+        for (int e = 0; e < E; ++e)
+          acc[v][e] += T(part[q * kMaxNev + (v < NV - 1 ? v * E : last) + e]);
     epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
@@ -727,6 +751,7 @@ int dispatch_types(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, cons
     else col = g->col;
     Csr<IdxT, WT> A{static_cast<const IdxT *>(g->rowptr), col, static_cast<const WT *>(g->w)};
     EpiT<T, VB, NV> epi{p};
+    if constexpr (!EpiT<T, VB, NV>::kNorms) epi.last = ld - Vec<T, VB>::E;
     if constexpr (std::is_same_v<EpiT<T, VB, NV>, VResidual<T, VB, NV>> ||
                   std::is_same_v<EpiT<T, VB, NV>, VShiftDot<T, VB, NV>>)
       epi.m = m;
@@ -749,29 +774,31 @@ template <typename T, template <typename, int, int> class EpiT, typename P>
 int dispatch_nv(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, const P &p, int m,
                 double *partials, int *nparts, hipStream_t s,
                 const LaunchEvents *ev = nullptr) {
-  if (ld < m || ld > kMaxNev || m < 1) return SPHX_E_INVALID_ARG;
-  const int row_bytes = ld * (int)sizeof(T);
+  if (ld < m || ld > kMaxNev || ld < 2) return SPHX_E_INVALID_ARG;
 #define SPHX_NV(VB_, NV_)                                                                 \
   case NV_:                                                                               \
     return dispatch_types<T, VB_, NV_, EpiT>(g, plan, X, ld, p, m, partials, nparts, s, ev);
-  if (row_bytes % 16 == 0) {
-    switch (row_bytes / 16) {
-      SPHX_NV(16, 1) SPHX_NV(16, 2) SPHX_NV(16, 3) SPHX_NV(16, 4)
+  if constexpr (EpiT<T, 16, 1>::kNorms)   // padded blocks only
+    if ((ld * (int)sizeof(T)) % 16) return SPHX_E_INVALID_ARG;
+  // FP32 rows of 2, 3, 5, 6, 10 or 14 values: 8-byte vectors (no 16-byte
+  // vector fits, or 8-byte ones fetch less than overlapping 16-byte ones)
+  if constexpr (std::is_same_v<T, float>) {
+    if (ld == 3 || ld == 5 || ld % 4 == 2) {
+      switch ((ld + 1) / 2) {
+        SPHX_NV(8, 1) SPHX_NV(8, 2) SPHX_NV(8, 3) SPHX_NV(8, 5) SPHX_NV(8, 7)
+        default: return SPHX_E_INVALID_ARG;
+      }
+    }
+  }
+  constexpr int E = 16 / (int)sizeof(T);
+  switch ((ld + E - 1) / E) {
+    SPHX_NV(16, 1) SPHX_NV(16, 2) SPHX_NV(16, 3) SPHX_NV(16, 4)
+    default: break;
+  }
+  if constexpr (std::is_same_v<T, double>) {
+    switch ((ld + E - 1) / E) {
+      SPHX_NV(16, 5) SPHX_NV(16, 6) SPHX_NV(16, 7) SPHX_NV(16, 8)
       default: break;
-    }
-    if constexpr (std::is_same_v<T, double>) {
-      switch (row_bytes / 16) {
-        SPHX_NV(16, 5) SPHX_NV(16, 6) SPHX_NV(16, 7) SPHX_NV(16, 8)
-        default: break;
-      }
-    }
-  } else if constexpr (std::is_same_v<T, float>) {
-    // FP32 rows of 2, 6, 10 or 14 values: 8-byte vectors
-    if (row_bytes % 8 == 0) {
-      switch (row_bytes / 8) {
-        SPHX_NV(8, 1) SPHX_NV(8, 3) SPHX_NV(8, 5) SPHX_NV(8, 7)
-        default: break;
-      }
     }
   }
 #undef SPHX_NV

@@ -67,3 +67,63 @@ def test_adjoint_cg_edges(handle, n, nev, gen):
         sx.eig_backward(*args, cg_tol=1e-13, cg_max_iter=3, allow_not_converged=True)
         its3, res3 = sx.backward_info(handle)
         assert its3 == 3 and res3 > 1e-13
+
+
+def _graph_of(kind):
+    import graphgen
+    from tests.gpu_util import star_graph
+    if kind == "grid":            # one lane per row, int16 offsets
+        n, (u, v) = graphgen.grid3d_7pt(9, 8, 7)
+        return graphgen.csr_from_edges(n, u, v, None)
+    if kind == "brick":           # staged rows, weights
+        n, (u, v) = graphgen.brick27(8, 7, 6)
+        return graphgen.csr_from_edges(n, u, v, graphgen.uniform_weights(u.size, 4,
+                                                                         dtype=np.float64))
+    if kind == "rmat":            # every degree class
+        return graphgen.rmat_graph(11, seed=2, weight_seed=3, weight_dtype=np.float64)
+    return star_graph(17000)      # a hub row in chunks
+
+
+@pytest.mark.parametrize("m", range(1, 17))
+@pytest.mark.parametrize("kind", ["grid", "brick", "rmat", "hub"])
+def test_products_every_width(handle, kind, m):
+    """Every block width on every row class, from a base that is only aligned
+    to its elements: L X, five Chebyshev steps (also in place) and the GMRES
+    polynomial against FP64 numpy.  Errors of a product are at most some
+    deg u ||x|| (deg 17000 for the hub); a polynomial of 5 steps multiplies
+    them by less than 100 on these spectra."""
+    import torch
+    import paper_2105_00578_amd as sx
+    from oracle import laplacian as lap, precond
+    from tests.gpu_util import dev, upload
+    g = _graph_of(kind)
+    rp, col, w = upload(g)
+    G = sx.Graph(handle, rp, col, w)
+    rng = np.random.default_rng(m)
+    X64 = rng.standard_normal((g.n, m))
+    roots = [1.9, 0.1, 1.0, 0.4]
+    for npd, td, tol in ((np.float32, torch.float32, 3e-6), (np.float64, torch.float64, 1e-14)):
+        Xh = X64.astype(npd)
+        buf = torch.zeros(g.n * m + 1, dtype=td, device=dev())
+        X = buf[1:].view(g.n, m)
+        X.copy_(torch.from_numpy(Xh))
+        ref = Xh.astype(np.float64)
+        LX = lap.apply(g.rowptr, g.col, g.w, ref)
+        Y = sx.laplacian_apply(handle, G, X).cpu().numpy()
+        assert np.abs(Y - LX).max() <= tol * np.abs(LX).max()
+        d = lap.degrees(g.rowptr, g.col, g.w)
+        for problem in (sx.COMBINATORIAL, sx.GENERALIZED):
+            gen = problem == sx.GENERALIZED
+            hi = 2.0 if gen else 2.0 * d.max()
+            H0 = precond.chebyshev(g.rowptr, g.col, g.w, ref, 5, hi / 20, hi,
+                                   dinv=1.0 / d if gen else None, problem=problem)
+            o = sx.Options(problem=problem, precond=sx.PRECOND_CHEBYSHEV, cheb_degree=5,
+                           cheb_ratio=20.0)
+            H = sx.precond_apply(handle, G, o, X).cpu().numpy()
+            assert np.abs(H - H0).max() <= 100 * tol * np.abs(H0).max()
+            Xc = X.clone()
+            sx.precond_apply(handle, G, o, Xc, out=Xc)     # in place
+            assert np.array_equal(Xc.cpu().numpy(), H)
+        P0 = precond.gmres_poly_apply(g.rowptr, g.col, g.w, sx.GENERALIZED, ref, roots)
+        P = sx.poly_apply(handle, G, sx.GENERALIZED, roots, X).cpu().numpy()
+        assert np.abs(P - P0).max() <= 100 * tol * np.abs(P0).max()
