@@ -1019,10 +1019,13 @@ int sphx_laplacian_apply(sphx_handle *h, sphx_graph *g, int problem, int m, int 
   double *rsq = a.take<double>(g->n);
   double *degs = a.take<double>(4 * kDegBlocksMax);
   char *tmp = norm ? a.take<char>(blk) : nullptr;
+  // L_C needs the row classes only; one product does not earn back the pass
+  // that builds int16 offsets
   DegreeStats ds;
-  SPHX_TRY(compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s));
+  SPHX_TRY(norm ? compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s)
+                : pattern_stats(g, degs, &ds, h->pinned_small, s));
   SpmmPlan plan;
-  SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s));
+  SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s, false));
   const int64_t n = g->n;
   const void *src = X;
   if (norm) {
@@ -1086,12 +1089,19 @@ int sphx_precond_apply(sphx_handle *h, sphx_graph *g, const sphx_options *o, int
   double *degs = a.take<double>(4 * kDegBlocksMax);
   char *b1 = a.take<char>(blk);
   char *b2 = a.take<char>(blk);
-  DegreeStats ds;
-  SPHX_TRY(compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s));
-  SpmmPlan plan;
-  SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s));
   const int64_t n = g->n;
   const bool norm = o->problem == SPHX_NORMALIZED;
+  const bool cheb = o->precond == SPHX_PRECOND_CHEBYSHEV;
+  // the degrees are read by Jacobi and by the generalized and normalized
+  // polynomials; the combinatorial one needs their maximum, which a unit
+  // graph's pattern gives
+  const bool need_d = (o->precond == SPHX_PRECOND_JACOBI && !norm) ||
+                      (cheb && (o->problem != SPHX_COMBINATORIAL || g->wdt != SPHX_UNIT));
+  DegreeStats ds;
+  SPHX_TRY(need_d ? compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s)
+                  : pattern_stats(g, degs, &ds, h->pinned_small, s));
+  SpmmPlan plan;
+  if (cheb) SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s));
   if (o->precond == SPHX_PRECOND_NONE || (norm && o->precond == SPHX_PRECOND_JACOBI)) {
     // diag(L_N) = I: Jacobi is the identity for the normalized problem
     SPHX_HIP(h, hipMemcpyAsync(H, R, blk, hipMemcpyDeviceToDevice, s));
@@ -1235,13 +1245,15 @@ int sphx_poly_apply(sphx_handle *h, sphx_graph *g, int problem, int nroots,
   char *b2 = a.take<char>(blk);
   char *b3 = a.take<char>(blk);
   DegreeStats ds;
-  SPHX_TRY(compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s));
-  SpmmPlan plan;
-  SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s));
   const bool gen = problem != SPHX_COMBINATORIAL;
   const bool norm = problem == SPHX_NORMALIZED;
+  SPHX_TRY(gen ? compute_degrees(g, d64, nullptr, degs, &ds, h->pinned_small, s)
+               : pattern_stats(g, degs, &ds, h->pinned_small, s));
+  SpmmPlan plan;
+  SPHX_TRY(build_plan(g, a, &plan, ds, h->pinned_small, s));
   if (gen && !(ds.min_wdeg > 0)) return set_err(h, SPHX_E_INVALID_ARG, "isolated vertex");
-  hipLaunchKernelGGL(k_inverse, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, d64, dinv, n);
+  if (gen)
+    hipLaunchKernelGGL(k_inverse, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, d64, dinv, n);
   if (norm)
     hipLaunchKernelGGL(k_sqrt_pair, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, d64, sq, rsq,
                        n);

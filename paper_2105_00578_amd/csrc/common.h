@@ -129,7 +129,9 @@ struct sphx_graph {
   // cached statistics (computed on first use)
   int stats_valid = 0;
   int64_t max_deg = 0;
+  int64_t min_deg = 0;
   int64_t sum_deg = 0;
+  int offsets16 = 0;               // int16 column offsets: 0 not tried, 1 fit, 2 do not
   double max_wdeg = 0.0;
   double wmin = 0.0, wmax = 0.0;   // edge weight range (weighted graphs)
   int wrange_valid = 0;            // wmin / wmax computed

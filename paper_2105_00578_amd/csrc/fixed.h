@@ -33,15 +33,26 @@ inline int fixed_exponent(double wmin) {
   return ex - (std::is_same_v<WT, float> ? 24 : 53);
 }
 
-// w / 2^e0 as a 128-bit integer (w > 0 finite, 2^e0 divides w)
+// w / 2^e0 as a 128-bit integer (w > 0 finite, 2^e0 divides w): the mantissa
+// and the exponent of its last bit come from the bits of w (subnormals have
+// the smallest exponent and no implicit bit)
 template <typename WT>
 __device__ __forceinline__ void fixed_of(WT w, int e0, unsigned long long &lo,
                                          unsigned long long &hi) {
-  int ex;
-  double f = frexp(double(w), &ex);   // w = f 2^ex, f in [0.5, 1)
-  constexpr int MB = std::is_same_v<WT, float> ? 24 : 53;
-  unsigned long long M = (unsigned long long)ldexp(f, MB);   // exact
-  int sh = ex - MB - e0;                                      // >= 0
+  unsigned long long M;
+  int e;
+  if constexpr (std::is_same_v<WT, float>) {
+    const unsigned u = __float_as_uint(w);
+    const int x = (int)((u >> 23) & 255u);
+    M = (u & 0x7fffffu) | (x ? 0x800000u : 0u);
+    e = (x ? x : 1) - 150;
+  } else {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(w);
+    const int x = (int)((u >> 52) & 2047ull);
+    M = (u & 0xfffffffffffffull) | (x ? 0x10000000000000ull : 0ull);
+    e = (x ? x : 1) - 1075;
+  }
+  const int sh = e - e0;                                      // >= 0
   if (sh <= 0) { lo = M >> (-sh); hi = 0; }                   // sh < 0 only if misuse
   else if (sh < 64) { lo = M << sh; hi = M >> (64 - sh); }
   else { lo = 0; hi = M << (sh - 64); }

@@ -10,8 +10,12 @@ namespace sphx {
 // holds rows with at most bin_max_deg(c) neighbours (and more than the class
 // below), served by bin_group(c) lanes per row; rows beyond kHubDeg are hubs,
 // split into kHubChunk-entry chunks of one wavefront each.
-constexpr int kHubDeg = 16384;
-constexpr int kHubChunk = 4096;
+// A row served by one wavefront takes degree / 64 dependent trips to memory per
+// lane, so a few long rows decide a product's time: on R-MAT 17 (5 FP32
+// columns) the wavefront rows took 63 of a product's 98 us with hubs above
+// 16384 entries in chunks of 4096; with these limits all rows take 43 us.
+constexpr int kHubDeg = 1024;
+constexpr int kHubChunk = 512;
 constexpr int kNumBins = 4;
 __host__ __device__ constexpr int bin_max_deg(int c) {
   return c == 0 ? 12 : (c == 1 ? 48 : (c == 2 ? 192 : kHubDeg));
@@ -38,7 +42,7 @@ struct SpmmPlan {
   const int64_t *chunk_k0 = nullptr;     // per chunk: first entry
   const int64_t *chunk_k1 = nullptr;     // per chunk: one past last entry
   const int32_t *hub_chunk_begin = nullptr;  // per hub: first chunk (n_hub+1)
-  int64_t n_chunks = 0;
+  int64_t n_chunks = 0;                  // at most (hub_chunk_begin[n_hub] of them)
   double *hub_partial = nullptr;         // n_chunks * kMaxNev scratch (T-sized)
 };
 
@@ -59,8 +63,14 @@ constexpr int kWrangeBlocks = 1024;
 int weight_range(sphx_graph *g, void *scratch, void *pinned, hipStream_t s);
 int compute_degrees(sphx_graph *g, double *d64, float *d32, void *scratch,
                     DegreeStats *out, void *pinned, hipStream_t s);
+// Neighbour counts only (out's weighted degrees are those of unit weights),
+// with compute_degrees' errors: from the graph's record when it has one (the
+// pattern of a graph does not change), else by a pass over row_ptr.
+int pattern_stats(sphx_graph *g, void *scratch, DegreeStats *out, void *pinned, hipStream_t s);
+// offsets: whether int16 column offsets are worth building (for several
+// products over the plan)
 int build_plan(sphx_graph *g, Arena &ws, SpmmPlan *plan, const DegreeStats &st,
-               void *pinned, hipStream_t s);
+               void *pinned, hipStream_t s, bool offsets = true);
 size_t plan_bytes(sphx_graph *g);
 // Degree order of a graph: rows sorted by floor(log2 degree), descending,
 // ties in increasing id.  *out is a copy of g over permuted arrays in

@@ -215,8 +215,7 @@ template <typename T, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_spmm_hub_partial(
     Csr<IdxT, WT> A, const int32_t *__restrict__ hub_rows,
     const int32_t *__restrict__ hub_chunk_begin, int64_t n_hub,
-    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s,
-    int64_t n_chunks, const T *__restrict__ X, int ldx, ColMap cm, double *out) {
+    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s, const T *__restrict__ X, int ldx, ColMap cm, double *out) {
   const int G = cm.count;
   const int ng = kWave / G;
   const int lane = threadIdx.x & (kWave - 1);
@@ -225,6 +224,7 @@ __global__ __launch_bounds__(256) void k_spmm_hub_partial(
   const int c = lane % G;
   const int col = cm.col[c];
   const int wpb = blockDim.x / kWave;
+  const int64_t n_chunks = hub_chunk_begin[n_hub];
   for (int64_t q = (int64_t)blockIdx.x * wpb + wave; q < n_chunks;
        q += (int64_t)gridDim.x * wpb) {
     // hub row owning chunk q: last h with hub_chunk_begin[h] <= q
@@ -309,7 +309,7 @@ void run_all(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan,
       unsigned gb = grid_for(plan.n_chunks, 4, kWaveBlocks);
       hipLaunchKernelGGL((k_spmm_hub_partial<T, IdxT, WT>), dim3(gb), dim3(256), 0, s,
                          A, plan.hub_rows, plan.hub_chunk_begin, plan.n_hub,
-                         plan.chunk_k0, plan.chunk_k1, plan.n_chunks, X, ldx, cm,
+                         plan.chunk_k0, plan.chunk_k1, X, ldx, cm,
                          plan.hub_partial);
       unsigned gc = grid_for(plan.n_hub, 4, kHubBlocks);
       hipLaunchKernelGGL((k_spmm_hub_combine<T, Epi>), dim3(gc), dim3(256), 0, s,

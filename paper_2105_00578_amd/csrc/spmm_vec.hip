@@ -14,9 +14,9 @@
 // gathers of a wavefront are contiguous).  Blocks of rows are mapped so that
 // each of the 8 XCDs (hardware places consecutive workgroups round robin on
 // them) works on one contiguous eighth of the rows, which keeps the gathered
-// neighbours of a mesh in that XCD's L2.  Mid-degree rows use a wavefront
-// per row (lanes over the neighbours, butterfly reduction in a fixed order),
-// hub rows fixed-size chunks combined in a second pass.  All sums are in a
+// neighbours of a mesh in that XCD's L2.  Longer rows of power-law graphs use
+// groups of 4, 16 or 64 lanes (lanes over the neighbours, butterfly reduction
+// in a fixed order), hub rows fixed-size chunks combined in a second pass.  All sums are in a
 // fixed order, so results are bitwise reproducible.
 //
 // Epilogues (whole rows): Store, Residual (r = acc - b_i theta_c x_i, output r
@@ -356,10 +356,9 @@ __device__ void block_norms(const double (&n1)[LD], const double (&n2)[LD], int 
 // ----------------------------------------------------------------- kernels
 // Short rows, one thread per row; `rpt` rows per thread, 256-row strides.
 template <typename T, int VB, int NV, typename IdxT, typename WT, typename Epi>
-__global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, const int32_t *__restrict__ rows,
-                                              int64_t nrows, const T *__restrict__ Xs, int ld,
-                                              int rpt, Epi epi, double *partials, int slot0,
-                                              int m) {
+__global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, int64_t nrows,
+                                              const T *__restrict__ Xs, int ld, int rpt, Epi epi,
+                                              double *partials, int m) {
   using V = typename Vec<T, VB>::type;
   constexpr int LD = NV * Vec<T, VB>::E;
   const int last = ld - Vec<T, VB>::E;
@@ -368,28 +367,15 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, const int32_t *__
 #pragma unroll
   for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
   for (int q = 0; q < rpt; ++q) {
-    const int64_t r = (b * rpt + q) * 256 + threadIdx.x;
-    if (r >= nrows) break;
-    const int64_t i = rows ? rows[r] : r;
+    const int64_t i = (b * rpt + q) * 256 + threadIdx.x;
+    if (i >= nrows) break;
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
     vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, Xs, ld, last, xi, acc);
     epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
-}
-
-template <typename T, int VB, int NV>
-__device__ __forceinline__ void wave_sum(typename Vec<T, VB>::type (&acc)[NV]) {
-  constexpr int E = Vec<T, VB>::E;
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      T a = acc[v][e];
-      for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
-      acc[v][e] = a;
-    }
+  if constexpr (Epi::kNorms)
+    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)blockIdx.x);
 }
 
 template <typename T, int VB, int NV, int G>
@@ -406,44 +392,37 @@ __device__ __forceinline__ void group_sum(typename Vec<T, VB>::type (&acc)[NV]) 
     }
 }
 
-// G lanes per row (G = 2, 4, 16 or 64): the lanes of a group take every G-th
-// neighbour of the row, so a group reads a contiguous run of the column
-// indices; the group's partial sums are combined by a butterfly in a fixed
-// order and the group's first lane runs the epilogue.  rows = null: natural
-// order over all n rows.
-// rpb > 0: each block takes a contiguous range of rpb rows (a multiple of the
-// groups per block), and block ids are remapped so that each XCD works on one
+// G lanes per row (G = 2 or 4), natural order over all n rows: the lanes of a
+// group take every G-th neighbour of the row, so a group reads a contiguous
+// run of the column indices; the group's partial sums are combined by a
+// butterfly in a fixed order and the group's first lane runs the epilogue.
+// Each block takes a contiguous range of rpb rows (a multiple of the groups
+// per block), and block ids are remapped so that each XCD works on one
 // contiguous stretch of ranges (as the one-lane kernel does): the gathered
-// neighbour rows of a mesh then stay in that XCD's L2.  rpb == 0: blocks
-// stride over the rows (the degree-binned lists of power-law graphs, whose
-// neighbours are random anyway and whose row costs vary within a bin).
+// neighbour rows of a mesh then stay in that XCD's L2.
 template <typename T, int VB, int NV, int G, typename IdxT, typename WT, typename Epi>
-__global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A,
-                                                const int32_t *__restrict__ rows,
-                                                int64_t nrows, const T *__restrict__ Xs,
-                                                int ld, int64_t rpb, Epi epi, double *partials,
-                                                int slot0, int m) {
+__global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A, int64_t nrows,
+                                                const T *__restrict__ Xs, int ld, int64_t rpb,
+                                                Epi epi, double *partials, int m) {
   using V = typename Vec<T, VB>::type;
   constexpr int LD = NV * Vec<T, VB>::E;
   constexpr int GPB = 256 / G;   // groups per block
   const int last = ld - Vec<T, VB>::E;
   const int gl = threadIdx.x & (G - 1);
-  const bool strided = rpb == 0;
-  const int64_t b = strided ? (int64_t)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t rend = strided ? nrows : min(nrows, (b + 1) * rpb);
-  const int64_t step = strided ? (int64_t)gridDim.x * GPB : GPB;
+  const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t rend = min(nrows, (b + 1) * rpb);
   double n1[LD], n2[LD];
 #pragma unroll
   for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
-  for (int64_t r = (strided ? b * GPB : b * rpb) + threadIdx.x / G; r < rend; r += step) {
-    const int64_t i = rows ? rows[r] : r;
+  for (int64_t i = b * rpb + threadIdx.x / G; i < rend; i += GPB) {
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
     vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last, xi, acc);
     group_sum<T, VB, NV, G>(acc);
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms)
+    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)blockIdx.x);
 }
 
 // Rows of 13..48 neighbours in natural order (mesh-like graphs), G lanes per
@@ -462,10 +441,10 @@ constexpr int kLdsEntries = 4096;
 template <typename T, int VB, int NV, int G, typename IdxT, typename WT, typename Epi>
 __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
                                               const T *__restrict__ Xs, int ld, int64_t rpb,
-                                              Epi epi, double *partials, int slot0, int m) {
+                                              Epi epi) {
+  static_assert(!Epi::kNorms, "the epilogue takes no norms");
   using V = typename Vec<T, VB>::type;
   using L = LdsCsr<WT>;
-  constexpr int LD = NV * Vec<T, VB>::E;
   constexpr int R = 256 / G;   // rows per chunk
   __shared__ typename L::CT scol[kLdsEntries];
   __shared__ typename L::WS sw[kUnitW<WT> ? 1 : kLdsEntries];
@@ -473,9 +452,6 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
   const int gl = threadIdx.x & (G - 1);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t rend = min(nrows, (b + 1) * rpb);
-  double n1[LD], n2[LD];
-#pragma unroll
-  for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
   for (int64_t r0 = b * rpb; r0 < rend; r0 += R) {
     const int64_t r1 = min(rend, r0 + (int64_t)R);
     const int64_t k0 = A.rp[r0], k1 = A.rp[r1];
@@ -499,75 +475,135 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
         vrow_acc<T, VB, NV, WT>(A, i, ka, kb, G, Xs, ld, last, xi, acc);
       }
       group_sum<T, VB, NV, G>(acc);
-      if (gl == 0) epi.row(i, xi, acc, n1, n2);
+      if (gl == 0) epi.row(i, xi, acc, nullptr, nullptr);
     }
     __syncthreads();
   }
-  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
-// Hub rows, pass 1: one wavefront per chunk -> partial row sums (as double).
-template <typename T, int VB, int NV, typename IdxT, typename WT>
-__global__ __launch_bounds__(256) void k_vhub_partial(
-    Csr<IdxT, WT> A, const int32_t *__restrict__ hub_rows,
-    const int32_t *__restrict__ hub_chunk_begin, int64_t n_hub,
-    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s, int64_t n_chunks,
-    const T *__restrict__ Xs, int ld, double *out) {
+// Degree-binned rows (power-law graphs), one launch: consecutive ranges of
+// blocks take the chunks of the hub rows, then the row classes from the
+// widest group down, so that the long rows start first and the short ones
+// fill the chip behind them (one launch per class ran them one after the
+// other: 24 products of 5 FP32 columns on R-MAT 17 took 2.3 ms, now 1.03).
+// Hub chunks write partial row sums (as double), which k_vhub_combine adds.
+struct BinRows {
+  const int32_t *rows[kNumBins];
+  int64_t nrows[kNumBins];
+  unsigned end[kNumBins + 1];     // end[0]: hub blocks; then class 3, 2, 1, 0
+  const int32_t *hub_rows, *hub_chunk_begin;
+  int64_t n_hub;
+  const int64_t *k0, *k1;
+  double *hub_partial;
+};
+
+template <typename T, int VB, int NV, int G, typename IdxT, typename WT, typename Epi>
+__device__ __forceinline__ void bin_rows(const Csr<IdxT, WT> &A, const int32_t *rows,
+                                         int64_t nrows, unsigned b, unsigned nb, const T *Xs,
+                                         int ld, const Epi &epi,
+                                         double (&n1)[NV * Vec<T, VB>::E],
+                                         double (&n2)[NV * Vec<T, VB>::E]) {
   using V = typename Vec<T, VB>::type;
-  constexpr int E = Vec<T, VB>::E;
-  const int last = ld - E;
-  const int lane = threadIdx.x & 63;
-  for (int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < n_chunks;
-       q += (int64_t)gridDim.x * 4) {
-    int64_t lo = 0, hi = n_hub - 1;
-    while (lo < hi) {
-      int64_t mid = (lo + hi + 1) / 2;
-      if (hub_chunk_begin[mid] <= q) lo = mid; else hi = mid - 1;
-    }
-    const int64_t i = hub_rows[lo];
+  constexpr int GPB = 256 / G;   // groups per block
+  const int last = ld - Vec<T, VB>::E;
+  const int gl = threadIdx.x & (G - 1);
+  for (int64_t r = (int64_t)b * GPB + threadIdx.x / G; r < nrows; r += (int64_t)nb * GPB) {
+    const int64_t i = rows[r];
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
-    vrow_acc<T, VB, NV, WT>(A, i, k0s[q] + lane, k1s[q], 64, Xs, ld, last, xi, acc);
-    wave_sum<T, VB, NV>(acc);
-    if (lane == 0)
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-          out[q * kMaxNev + (v < NV - 1 ? v * E : last) + e] = double(acc[v][e]);
+    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last,
+                            xi, acc);
+    if constexpr (G > 1) group_sum<T, VB, NV, G>(acc);
+    if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
 }
 
-// Hub rows, pass 2: one thread per hub row sums its chunks in order.
+template <typename T, int VB, int NV, typename IdxT, typename WT, typename Epi>
+__global__ __launch_bounds__(256) void k_vbin(Csr<IdxT, WT> A, BinRows B,
+                                              const T *__restrict__ Xs, int ld, Epi epi,
+                                              double *partials, int m) {
+  using V = typename Vec<T, VB>::type;
+  constexpr int E = Vec<T, VB>::E;
+  constexpr int LD = NV * E;
+  const unsigned b = blockIdx.x;
+  if (b < B.end[0]) {
+    const int last = ld - E;
+    const int lane = threadIdx.x & 63;
+    const int64_t n_chunks = B.hub_chunk_begin[B.n_hub];
+    for (int64_t q = (int64_t)b * 4 + (threadIdx.x >> 6); q < n_chunks;
+         q += (int64_t)B.end[0] * 4) {
+      int64_t lo = 0, hi = B.n_hub - 1;
+      while (lo < hi) {
+        int64_t mid = (lo + hi + 1) / 2;
+        if (B.hub_chunk_begin[mid] <= q) lo = mid; else hi = mid - 1;
+      }
+      const int64_t i = B.hub_rows[lo];
+      V xi[NV], acc[NV];
+      load_row<T, VB, NV>(Xs + i * ld, last, xi);
+      vrow_acc<T, VB, NV, WT>(A, i, B.k0[q] + lane, B.k1[q], 64, Xs, ld, last, xi, acc);
+      group_sum<T, VB, NV, 64>(acc);
+      if (lane == 0)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            B.hub_partial[q * kMaxNev + (v < NV - 1 ? v * E : last) + e] = double(acc[v][e]);
+    }
+    return;
+  }
+  double n1[LD], n2[LD];
+#pragma unroll
+  for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
+  static_assert(kNumBins == 4 && bin_group(0) == 1 && bin_group(1) == 4 && bin_group(2) == 16 &&
+                    bin_group(3) == 64, "row classes");
+  if (b < B.end[1])
+    bin_rows<T, VB, NV, 64>(A, B.rows[3], B.nrows[3], b - B.end[0], B.end[1] - B.end[0], Xs, ld,
+                            epi, n1, n2);
+  else if (b < B.end[2])
+    bin_rows<T, VB, NV, 16>(A, B.rows[2], B.nrows[2], b - B.end[1], B.end[2] - B.end[1], Xs, ld,
+                            epi, n1, n2);
+  else if (b < B.end[3])
+    bin_rows<T, VB, NV, 4>(A, B.rows[1], B.nrows[1], b - B.end[2], B.end[3] - B.end[2], Xs, ld,
+                           epi, n1, n2);
+  else
+    bin_rows<T, VB, NV, 1>(A, B.rows[0], B.nrows[0], b - B.end[3], B.end[4] - B.end[3], Xs, ld,
+                           epi, n1, n2);
+  if constexpr (Epi::kNorms)
+    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)(b - B.end[0]));
+}
+
+// Hub rows: one wavefront per hub row, lanes over its chunks, combined by a
+// butterfly in a fixed order.
 template <typename T, int VB, int NV, typename Epi>
-__global__ __launch_bounds__(256) void k_vhub_combine(const int32_t *__restrict__ hub_rows,
-                                                      const int32_t *__restrict__ hub_chunk_begin,
-                                                      int64_t n_hub, const double *part,
-                                                      const T *__restrict__ Xs, int ld, Epi epi,
-                                                      double *partials, int slot0, int m) {
+__global__ __launch_bounds__(256) void k_vhub_combine(BinRows B, const T *__restrict__ Xs, int ld,
+                                                      Epi epi, double *partials, int slot0,
+                                                      int m) {
   using V = typename Vec<T, VB>::type;
   constexpr int E = Vec<T, VB>::E;
   constexpr int LD = NV * E;
   const int last = ld - E;
+  const int lane = threadIdx.x & 63;
   double n1[LD], n2[LD];
 #pragma unroll
   for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
-  for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h < n_hub;
-       h += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = hub_rows[h];
+  for (int64_t h = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); h < B.n_hub;
+       h += (int64_t)gridDim.x * 4) {
+    const int64_t i = B.hub_rows[h];
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = V(0);
-    for (int64_t q = hub_chunk_begin[h]; q < hub_chunk_begin[h + 1]; ++q)
+    for (int64_t q = B.hub_chunk_begin[h] + lane; q < B.hub_chunk_begin[h + 1]; q += 64)
 #pragma unroll
       for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int e = 0; e < E; ++e)
-          acc[v][e] += T(part[q * kMaxNev + (v < NV - 1 ? v * E : last) + e]);
-    epi.row(i, xi, acc, n1, n2);
+          acc[v][e] += T(B.hub_partial[q * kMaxNev + (v < NV - 1 ? v * E : last) + e]);
+    group_sum<T, VB, NV, 64>(acc);
+    if (lane == 0) epi.row(i, xi, acc, n1, n2);
   }
-  if constexpr (Epi::kNorms) block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+  if constexpr (Epi::kNorms)
+    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
 }
 
 // The residual epilogue as a streaming pass over an L X that a store product
@@ -636,13 +672,10 @@ int resid_stream(int64_t n, const T *X, int ld, int m, const EpiResidualP<T> &p,
 // ----------------------------------------------------------------- dispatch
 constexpr int kMaxShortBlocks = 8192;
 constexpr int kGroupBlocks = 8192;
-constexpr int kBinnedShortBlocks = 4096;
-constexpr int kBinnedGroupBlocks = 1536;
-constexpr int kWaveBlocks = 1024;
-constexpr int kHubBlocks = 16;
+constexpr int kBinBlocks = 2048;    // per row class of a binned plan, and for the hub chunks
+constexpr int kHubBlocks = 256;
 static_assert(kMaxShortBlocks <= kMaxNormBlocks && kGroupBlocks <= kMaxNormBlocks &&
-                  kBinnedShortBlocks + (kNumBins - 1) * kBinnedGroupBlocks + kHubBlocks <=
-                      kMaxNormBlocks,
+                  kNumBins * kBinBlocks + kHubBlocks <= kMaxNormBlocks,
               "norm partial slots");
 
 template <typename T, int VB, int NV, typename IdxT, typename WT, typename Epi>
@@ -656,52 +689,19 @@ void run_vec(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X
   const bool stamp = ev && !plan.binned;
   hipEvent_t e0 = stamp ? ev->start : nullptr, e1 = stamp ? ev->stop : nullptr;
   if (ev && !stamp) (void)hipEventRecord(ev->start, s);
-  auto short_rows = [&](const int32_t *rows, int64_t nr, int64_t maxb) {
+  auto short_rows = [&](int64_t nr) {
     int64_t nb = ceil_div(nr, 256);
-    int rpt = (int)ceil_div(nb, maxb);
+    int rpt = (int)ceil_div(nb, kMaxShortBlocks);
     nb = ceil_div(nr, 256 * (int64_t)rpt);
     hipExtLaunchKernelGGL((k_vrow<T, VB, NV, IdxT, WT, Epi>), dim3((unsigned)nb), dim3(256), 0,
-                          s, e0, e1, 0, A, rows, nr, X, ld, rpt, epi, partials, used, m);
+                          s, e0, e1, 0, A, nr, X, ld, rpt, epi, partials, m);
     used += (int)nb;
   };
-  auto grouped = [&](int G, const int32_t *rows, int64_t nr, int64_t maxb) {
-    // natural order: contiguous ranges of whole group-steps per block;
-    // row lists (binned): blocks stride over the list.  At most maxb blocks.
+  // contiguous ranges of whole group-steps per block, at most kGroupBlocks
+  auto ranges = [&](int G, int64_t nr, int64_t &rpb) {
     const int64_t gpb = 256 / G;
-    int64_t rpb = 0;
-    unsigned gb = grid_for(nr, gpb, maxb);
-    if (!rows) {
-      const int64_t steps = ceil_div(nr, gpb);
-      rpb = ceil_div(steps, maxb) * gpb;
-      gb = (unsigned)std::max<int64_t>(1, ceil_div(nr, rpb));
-    }
-    if (G == 2)
-      hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                            e0, e1, 0, A, rows, nr, X, ld, rpb, epi, partials, used, m);
-    else if (G == 4)
-      hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                            e0, e1, 0, A, rows, nr, X, ld, rpb, epi, partials, used, m);
-    else if (G == 16)
-      hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 16, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
-                            s, e0, e1, 0, A, rows, nr, X, ld, rpb, epi, partials, used, m);
-    else
-      hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 64, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
-                            s, e0, e1, 0, A, rows, nr, X, ld, rpb, epi, partials, used, m);
-    used += (int)gb;
-  };
-  auto staged = [&](int G, int64_t nr, int64_t maxb) {
-    const int64_t R = 256 / G;
-    const int64_t chunks = ceil_div(nr, R);
-    const int64_t cpb = ceil_div(chunks, maxb);
-    const int64_t rpb = cpb * R;
-    const unsigned gb = (unsigned)std::max<int64_t>(1, ceil_div(nr, rpb));
-    if (G == 2)
-      hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                            e0, e1, 0, A, nr, X, ld, rpb, epi, partials, used, m);
-    else
-      hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                            e0, e1, 0, A, nr, X, ld, rpb, epi, partials, used, m);
-    used += (int)gb;
+    rpb = ceil_div(ceil_div(nr, gpb), kGroupBlocks) * gpb;
+    return (unsigned)std::max<int64_t>(1, ceil_div(nr, rpb));
   };
   if (!plan.binned) {
     // rows of 13..48 neighbours: wide gathered rows (>= 32 bytes) take two
@@ -709,29 +709,57 @@ void run_vec(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X
     // lanes, FP32 and FP64), narrow rows four
     int G = plan.group;
     if (G > 1 && VB * NV >= 32) G = 2;
-    // the LDS-staged index stream pays off for the light epilogues (store,
-    // polynomial steps: 8..20 % faster on the weighted 27-point mesh); with
-    // the residual epilogue's per-thread norm sums the extra LDS costs more
-    // occupancy than it saves (measured 11..30 % slower), so that one reads
-    // its indices per lane
-    if (G == 1) short_rows(nullptr, n, kMaxShortBlocks);
-    else if (Epi::kNorms) grouped(G, nullptr, n, kGroupBlocks);
-    else staged(G, n, kGroupBlocks);
-  } else {
-    for (int c = 0; c < kNumBins; ++c) {
-      if (plan.nrows[c] == 0) continue;
-      if (bin_group(c) == 1) short_rows(plan.rows[c], plan.nrows[c], kBinnedShortBlocks);
-      else grouped(bin_group(c), plan.rows[c], plan.nrows[c], kBinnedGroupBlocks);
+    int64_t rpb = 0;
+    if (G == 1) {
+      short_rows(n);
+    } else {
+      const unsigned gb = ranges(G, n, rpb);
+      // the LDS-staged index stream pays off for the light epilogues (store,
+      // polynomial steps: 8..20 % faster on the weighted 27-point mesh); with
+      // the residual epilogue's per-thread norm sums the extra LDS costs more
+      // occupancy than it saves (measured 11..30 % slower), so that one reads
+      // its indices per lane
+      if constexpr (Epi::kNorms) {
+        if (G == 2)
+          hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
+                                s, e0, e1, 0, A, n, X, ld, rpb, epi, partials, m);
+        else
+          hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
+                                s, e0, e1, 0, A, n, X, ld, rpb, epi, partials, m);
+      } else {
+        if (G == 2)
+          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
+                                e0, e1, 0, A, n, X, ld, rpb, epi);
+        else
+          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
+                                e0, e1, 0, A, n, X, ld, rpb, epi);
+      }
+      used += (int)gb;
     }
+  } else if constexpr (!std::is_same_v<WT, UnitD16>) {   // (offsets: unbinned plans only)
+    BinRows B{};
+    B.hub_rows = plan.hub_rows;
+    B.hub_chunk_begin = plan.hub_chunk_begin;
+    B.n_hub = plan.n_hub;
+    B.k0 = plan.chunk_k0;
+    B.k1 = plan.chunk_k1;
+    B.hub_partial = plan.hub_partial;
+    // n_chunks is an upper bound: blocks without a chunk end at once
+    B.end[0] = plan.n_hub > 0 ? grid_for(plan.n_chunks, 4, kBinBlocks) : 0;
+    for (int c = kNumBins - 1, q = 1; c >= 0; --c, ++q) {
+      B.rows[c] = plan.rows[c];
+      B.nrows[c] = plan.nrows[c];
+      B.end[q] = B.end[q - 1] +
+                 (plan.nrows[c] ? grid_for(plan.nrows[c], 256 / bin_group(c), kBinBlocks) : 0);
+    }
+    if (B.end[kNumBins] > 0)
+      hipLaunchKernelGGL((k_vbin<T, VB, NV, IdxT, WT, Epi>), dim3(B.end[kNumBins]), dim3(256),
+                         0, s, A, B, X, ld, epi, partials, m);
+    used += (int)(B.end[kNumBins] - B.end[0]);
     if (plan.n_hub > 0) {
-      unsigned gb = grid_for(plan.n_chunks, 4, kWaveBlocks);
-      hipLaunchKernelGGL((k_vhub_partial<T, VB, NV, IdxT, WT>), dim3(gb), dim3(256), 0, s, A,
-                         plan.hub_rows, plan.hub_chunk_begin, plan.n_hub, plan.chunk_k0,
-                         plan.chunk_k1, plan.n_chunks, X, ld, plan.hub_partial);
-      unsigned gc = grid_for(plan.n_hub, 256, kHubBlocks);
-      hipLaunchKernelGGL((k_vhub_combine<T, VB, NV, Epi>), dim3(gc), dim3(256), 0, s,
-                         plan.hub_rows, plan.hub_chunk_begin, plan.n_hub,
-                         (const double *)plan.hub_partial, X, ld, epi, partials, used, m);
+      const unsigned gc = grid_for(plan.n_hub, 4, kHubBlocks);
+      hipLaunchKernelGGL((k_vhub_combine<T, VB, NV, Epi>), dim3(gc), dim3(256), 0, s, B, X, ld,
+                         epi, partials, used, m);
       used += (int)gc;
     }
   }
