@@ -16,7 +16,22 @@
 // itself is included iff that brings |p C - j W| strictly down.  Integer
 // vertex weights make every histogram exact, so the result does not depend
 // on the order of the atomic additions.
+//
+// Levels of up to kFastSections sections and kFastCuts cuts narrow each target
+// down first (split_levels): the composite keys of a sorted random sample cut
+// the coordinate into bins of about equal weight (2048 over all sections),
+// one pass bins every member, the bin that holds a target is found from the
+// sections' histograms, and only its members (about n / 2048) go through the
+// radix select, in one workgroup's LDS.  The bins are intervals of the
+// composite order, so ties and any distribution of the values are as good as
+// another; a target whose bin is too full for one workgroup raises a flag,
+// and the radix passes over all members (in split_mj, also for more sections
+// or cuts) are run instead.  2 M members, K = 64, FP32: 1.13 ms by the radix
+// passes (8 per level, each over all members, the first ones with most
+// members in a few counters), 0.35 ms by sample bins, of which the strided
+// reads of the coordinates take about a third.
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "kernels.h"
@@ -237,30 +252,440 @@ __global__ void k_reset(int nsec, K *pord, uint32_t *pid, long long *base) {
   if (s < nsec) { pord[s] = 0; pid[s] = 0; base[s] = 0; }
 }
 
-__global__ void k_wsum(int64_t n, const int32_t *vwgt, long long *out) {
+__global__ __launch_bounds__(256) void k_wsum(int64_t n, const int32_t *vwgt, long long *out) {
   long long acc = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     acc += vwgt ? vwgt[i] : 1;
-  atomicAdd((unsigned long long *)out, (unsigned long long)acc);
+  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+  if ((threadIdx.x & 63) == 0) atomicAdd((unsigned long long *)out, (unsigned long long)acc);
+}
+
+__global__ __launch_bounds__(256) void k_split_clear(unsigned long long *hist, int *flag) {
+  for (int q = threadIdx.x; q < 2048; q += 256) hist[q] = 0ull;
+  if (threadIdx.x < 4) flag[threadIdx.x] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_zero_parts(int64_t n, int32_t *part) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    part[i] = 0;
+}
+
+// ---- sample bins
+constexpr int kSample = 2048;         // sorted sample keys per coordinate
+constexpr int kBins = 2048;           // bins of a level over all its sections
+constexpr int kFastSections = 256;
+constexpr int kFastCuts = 63;         // cuts per section
+constexpr int kFastTargets = 4096;
+constexpr int kFastLds = 4096;        // candidates kept in LDS
+constexpr int kFastCap = 65536;       // candidates per target, at most
+constexpr int kCutThreads = 1024;
+// Candidates of a target are appended through kSub counters, a cache line
+// each, to kSub runs of its list: appends to one counter go one after the
+// other at about 0.2 us (with one counter per target the pass over 2 M members
+// took 218 us).
+constexpr int kSub = 32;
+constexpr int kSubStride = 16;
+enum : int { F_NAN = 1, F_CROWDED = 2 };
+
+__device__ __forceinline__ uint64_t mix64(uint64_t z) {
+  z += 0x9E3779B97F4A7C15ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return z ^ (z >> 31);
+}
+
+template <typename K>
+__device__ __forceinline__ bool before(K ao, uint32_t ai, K bo, uint32_t bi) {
+  return (ao < bo) | ((ao == bo) & (ai < bi));
+}
+
+// Sorted composite keys of kSample random members, one block per coordinate
+// (a bitonic sort in LDS).  Random positions: a fixed stride meets one plane
+// of a lattice only.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_sample(const T *coords, int ld, int64_t n,
+                                                 typename Ord<T>::K *sord, uint32_t *sid) {
+  using K = typename Ord<T>::K;
+  __shared__ K o[kSample];
+  __shared__ uint32_t id[kSample];
+  const int c = blockIdx.x, t = threadIdx.x;
+  for (int q = t; q < kSample; q += 1024) {
+    const int64_t i = (int64_t)(mix64((uint64_t)q * 977 + c) % (uint64_t)n);
+    bool nan = false;
+    o[q] = Ord<T>::map(coords[i * ld + c], nan);
+    id[q] = (uint32_t)i;
+  }
+  // pairs up to 64 apart lie within the 128 values of one wave, whose LDS
+  // operations are in order: only wider steps need the block's barrier
+  bool wide = true;
+  for (int w = 2; w <= kSample; w <<= 1)
+    for (int j = w >> 1; j >= 1; j >>= 1) {
+      if (wide || j > 64) __syncthreads();
+      else __builtin_amdgcn_wave_barrier();
+      wide = j > 64;
+      const int a = 2 * t - (t & (j - 1)), b = a + j;   // pairs j apart
+      const bool up = (a & w) == 0;
+      const K oa = o[a], ob = o[b];
+      const uint32_t ia = id[a], ib = id[b];
+      if (before(ob, ib, oa, ia) == up) {
+        o[a] = ob;
+        id[a] = ib;
+        o[b] = oa;
+        id[b] = ia;
+      }
+    }
+  __syncthreads();
+  for (int q = t; q < kSample; q += 1024) {
+    sord[(int64_t)c * kSample + q] = o[q];
+    sid[(int64_t)c * kSample + q] = id[q];
+  }
+}
+
+// Targets of a level: cut keys (ord, id), whether the member at the key is
+// before the cut, and the weight before the cut.
+template <typename K>
+struct Cuts {
+  int p;             // children per section (0: no level before)
+  K *ord;
+  uint32_t *id;
+  int *incl;
+  long long *lo;
+  long long *W;      // weights of the level's sections
+};
+
+// One pass over the members: the child of the level before (if any), the key
+// of this level's coordinate, its bin, and the sections' bin weights (in LDS
+// first).  Bound by the strided reads of the coordinate column (a row of the
+// block per member).  H: LDS counter type (unsigned for unit weights).
+template <typename T, typename H>
+__global__ __launch_bounds__(512) void k_level(const T *__restrict__ coords, int ld, int c,
+                                               int64_t n, typename Ord<T>::K *keys,
+                                               uint16_t *bins, int32_t *part,
+                                               const int32_t *__restrict__ vwgt,
+                                               Cuts<typename Ord<T>::K> prev, int first,
+                                               const typename Ord<T>::K *__restrict__ sord,
+                                               const uint32_t *__restrict__ sid, int B, int nsec,
+                                               unsigned long long *hist, int *flag) {
+  using K = typename Ord<T>::K;
+  __shared__ K so[kSample];
+  __shared__ uint32_t si[kSample];
+  __shared__ H h[kBins];
+  for (int q = threadIdx.x; q < B - 1; q += 512) {
+    const int at = (int)((int64_t)(q + 1) * kSample / B);
+    so[q] = sord[at];
+    si[q] = sid[at];
+  }
+  for (int q = threadIdx.x; q < B * nsec; q += 512) h[q] = 0;
+  __syncthreads();
+  bool nan = false;
+  for (int64_t i = (int64_t)blockIdx.x * 512 + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * 512) {
+    const uint32_t id = (uint32_t)i;
+    const K o = Ord<T>::map(coords[i * ld + c], nan);
+    int s = 0;
+    if (prev.p) {
+      const int s0 = first ? 0 : part[i];
+      const K ko = keys[i];
+      const int pm = prev.p - 1;
+      int child = 0;
+      for (int j = 0; j < pm; ++j) {
+        const int t = s0 * pm + j;
+        const K po = prev.ord[t];
+        const uint32_t pi = prev.id[t];
+        const bool low = before(ko, id, po, pi) | ((ko == po) & (id == pi) & (prev.incl[t] != 0));
+        child += low ? 0 : 1;
+      }
+      s = s0 * prev.p + child;
+      part[i] = s;
+    }
+    keys[i] = o;
+    // bin: the number of splitters at or before the member
+    int lo = 0, len = B - 1;
+    while (len > 0) {
+      const int half = len >> 1, mid = lo + half;
+      const bool right = !before(o, id, so[mid], si[mid]);
+      lo = right ? mid + 1 : lo;
+      len = right ? len - half - 1 : half;
+    }
+    bins[i] = (uint16_t)lo;
+    atomicAdd(&h[s * B + lo], (H)(vwgt ? vwgt[i] : 1));
+  }
+  if (nan) atomicOr(flag, F_NAN);
+  __syncthreads();
+  for (int q = threadIdx.x; q < B * nsec; q += 512)
+    if (h[q]) atomicAdd(&hist[q], (unsigned long long)h[q]);
+}
+
+// One block per section: its weight (from the level before), and for each of
+// its cuts j the first bin whose end reaches j W / p, with the weight before
+// it; clears the section's bins and the cuts' candidate counters.
+template <typename K>
+__global__ __launch_bounds__(256) void k_find_bins(int B, int p, Cuts<K> prev, long long total,
+                                                   unsigned long long *hist, long long *W,
+                                                   int *tbin, long long *base, int *cnt) {
+  __shared__ long long sh[4];
+  const int s = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  long long Ws = total;
+  if (prev.p) {
+    const int par = s / prev.p, ch = s - par * prev.p;
+    const long long *lo = prev.lo + (int64_t)par * (prev.p - 1);
+    const long long a = ch ? lo[ch - 1] : 0;
+    Ws = (ch < prev.p - 1 ? lo[ch] : prev.W[par]) - a;
+  }
+  if (t == 0) W[s] = Ws;
+  for (int j = t; j < p - 1; j += 256) {
+    const int tg = s * (p - 1) + j;
+    tbin[tg] = -1;
+    base[tg] = 0;
+  }
+  for (int q = t; q < (p - 1) * kSub; q += 256)
+    cnt[((int64_t)s * (p - 1) * kSub + q) * kSubStride] = 0;
+  const int per = (B + 255) / 256;
+  const int b0 = min(B, t * per), b1 = min(B, b0 + per);
+  long long own = 0;
+  for (int b = b0; b < b1; ++b) own += (long long)hist[(int64_t)s * B + b];
+  long long incl = own;
+  for (int off = 1; off < 64; off <<= 1) {
+    const long long y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  if (lane == 63) sh[wave] = incl;
+  __syncthreads();
+  long long cum = incl - own;
+  for (int q = 0; q < wave; ++q) cum += sh[q];
+  if (Ws <= 0) return;          // uniform; an empty section's bins are zero
+  for (int b = b0; b < b1; ++b) {
+    const long long v = (long long)hist[(int64_t)s * B + b];
+    hist[(int64_t)s * B + b] = 0;
+    if (v > 0) {
+      // the cuts j with p cum < j W <= p (cum + v)
+      const long long jl = (long long)p * cum / Ws + 1, jh = (long long)p * (cum + v) / Ws;
+      for (long long j = jl; j <= jh && j < p; ++j) {
+        const int tg = s * (p - 1) + (int)j - 1;
+        tbin[tg] = b;
+        base[tg] = cum;
+      }
+    }
+    cum += v;
+  }
+}
+
+// the members of every target's bin (in no particular order); cap: of a run
+__global__ __launch_bounds__(256) void k_candidates(int64_t n, const uint16_t *__restrict__ bins,
+                                                    const int32_t *__restrict__ part, int first,
+                                                    int p, int ntgt, const int *__restrict__ tbin,
+                                                    int cap, int *cnt, uint32_t *list,
+                                                    int *flag) {
+  __shared__ int tb[kFastTargets];
+  for (int q = threadIdx.x; q < ntgt; q += 256) tb[q] = tbin[q];
+  __syncthreads();
+  const int pm = p - 1;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * 256) {
+    const int b = bins[i], t0 = (first ? 0 : part[i]) * pm;
+    for (int j = 0; j < pm; ++j)
+      if (tb[t0 + j] == b) {
+        const int64_t run = (int64_t)(t0 + j) * kSub + (blockIdx.x & (kSub - 1));
+        const int at = atomicAdd(&cnt[run * kSubStride], 1);
+        if (at < cap) list[run * cap + at] = (uint32_t)i;
+        else atomicOr(flag, F_CROWDED);
+      }
+  }
+}
+
+// One block per target: radix select of the cut's member among the bin's
+// members, 8 bits at a time of the keys less their minimum, then of the ids
+// (a bin is a narrow range of the order, so its raw leading bytes would put
+// nearly all members into one or two counters); a bucket with one member ends
+// the search.  Then the cut: whether that member is before it, and the weight
+// before it.  Measured at 1000 members: 15 us (raw bytes: 19 us).
+template <typename K>
+__global__ __launch_bounds__(kCutThreads) void k_cut_bin(int64_t n, int p, const K *__restrict__ keys,
+                                                  const int32_t *__restrict__ vwgt,
+                                                  uint32_t *list, int cap,
+                                                  const int *__restrict__ cnt,
+                                                  const long long *__restrict__ base_in,
+                                                  Cuts<K> out) {
+  __shared__ K ck[kFastLds];
+  __shared__ uint32_t ci[kFastLds];
+  __shared__ unsigned long long h[256];
+  __shared__ unsigned hc[256];
+  __shared__ int at[kSub + 1];
+  __shared__ K pord, pref, kmn[kCutThreads / 64], kmx[kCutThreads / 64];
+  __shared__ uint32_t pid, ipref, imn[kCutThreads / 64], imx[kCutThreads / 64];
+  __shared__ long long base, hit;
+  __shared__ int one;
+  const int tg = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int s = tg / (p - 1);
+  const long long Ws = out.W[s];
+  const long long jW = (long long)(tg - s * (p - 1) + 1) * Ws;
+  // the runs' starts among the target's candidates
+  if (t < 64) {
+    const int own = t < kSub ? min(cnt[((int64_t)tg * kSub + t) * kSubStride], cap) : 0;
+    int incl = own;
+    for (int off = 1; off < kSub; off <<= 1) {
+      const int y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    if (t < kSub) at[t + 1] = incl;
+    if (t == 0) {
+      at[0] = 0;
+      pord = 0;
+      pid = 0;
+      pref = 0;
+      ipref = 0;
+      base = base_in[tg];
+      hit = 0;
+      one = 0;
+    }
+  }
+  __syncthreads();
+  const int c = at[kSub];
+  const uint32_t *mine = list + (int64_t)tg * kSub * cap;
+  const bool lds = c <= kFastLds;
+  auto member = [&](int q) -> uint32_t {       // candidate q: run by bisection
+    int lo = 0, hi = kSub - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (at[mid] <= q) lo = mid; else hi = mid - 1;
+    }
+    return mine[(int64_t)lo * cap + (q - at[lo])];
+  };
+  K ka = ~K(0), kb = 0;
+  uint32_t ia = ~0u, ib = 0;
+  for (int q = t; q < c; q += kCutThreads) {
+    const uint32_t i = member(q);
+    const K o = keys[i];
+    if (lds) {
+      ci[q] = i;
+      ck[q] = o;
+    }
+    ka = min(ka, o);
+    kb = max(kb, o);
+    ia = min(ia, i);
+    ib = max(ib, i);
+  }
+  for (int off = 32; off >= 1; off >>= 1) {
+    ka = min(ka, (K)__shfl_xor((unsigned long long)ka, off));
+    kb = max(kb, (K)__shfl_xor((unsigned long long)kb, off));
+    ia = min(ia, (uint32_t)__shfl_xor((int)ia, off));
+    ib = max(ib, (uint32_t)__shfl_xor((int)ib, off));
+  }
+  if (lane == 0) {
+    kmn[wave] = ka;
+    kmx[wave] = kb;
+    imn[wave] = ia;
+    imx[wave] = ib;
+  }
+  __syncthreads();
+  for (int q = 0; q < kCutThreads / 64; ++q) {
+    ka = min(ka, kmn[q]);
+    kb = max(kb, kmx[q]);
+    ia = min(ia, imn[q]);
+    ib = max(ib, imx[q]);
+  }
+  // bits left of the keys (less ka), then of the ids (less ia)
+  int kbits = c > 0 && kb > ka ? 64 - __clzll((long long)(uint64_t)(kb - ka)) : 0;
+  int ibits = c > 0 ? max(1, 32 - __clz((int)(ib - ia))) : 0;
+  while (kbits + ibits > 0) {
+    const bool on_key = kbits > 0;
+    const int w = min(8, on_key ? kbits : ibits);
+    const int sh = (on_key ? kbits : ibits) - w;
+    if (t < 256) {
+      h[t] = 0;
+      hc[t] = 0;
+    }
+    __syncthreads();
+    const K kp = pref;
+    const uint32_t ip = ipref;
+    // bucket of a candidate that matches the prefix, or -1
+    auto bucket = [&](K o, uint32_t i) -> int {
+      const uint64_t x = on_key ? (uint64_t)(o - ka) : (uint64_t)(i - ia);
+      if (!on_key && o - ka != kp) return -1;
+      const uint64_t want = on_key ? (uint64_t)kp : (uint64_t)ip;
+      // (shifts of w + sh <= 64 in two steps)
+      return ((x >> sh) >> w) == want ? (int)((x >> sh) & ((1u << w) - 1)) : -1;
+    };
+    for (int q = t; q < c; q += kCutThreads) {
+      const uint32_t i = lds ? ci[q] : member(q);
+      const int b = bucket(lds ? ck[q] : keys[i], i);
+      if (b >= 0) {
+        atomicAdd(&h[b], (unsigned long long)(vwgt ? vwgt[i] : 1));
+        atomicAdd(&hc[b], 1u);
+      }
+    }
+    __syncthreads();
+    if (t < 64) {
+      // the first bucket where p C reaches j W (as in k_select)
+      long long v[4], local = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = (long long)h[4 * lane + u];
+        local += v[u];
+      }
+      long long incl = local;
+      for (int off = 1; off < 64; off <<= 1) {
+        const long long y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
+      }
+      long long cum = base + (incl - local);
+      int pick = -1;
+      long long hb = 0, bb = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (pick < 0) {
+          if (v[u] > 0 && (long long)p * (cum + v[u]) >= jW) {
+            pick = 4 * lane + u;
+            hb = v[u];
+            bb = cum;
+          } else {
+            cum += v[u];
+          }
+        }
+      }
+      const unsigned long long mask = __ballot(pick >= 0);
+      if (mask) {
+        const int first = __ffsll((long long)mask) - 1;
+        if (lane == first) {
+          base = bb;
+          hit = hb;
+          one = hc[pick] == 1u;
+          if (on_key) pref = (kp << w) | (K)pick;
+          else ipref = (ip << w) | (uint32_t)pick;
+        }
+      }
+    }
+    __syncthreads();
+    (on_key ? kbits : ibits) = sh;
+    if (one || kbits + ibits == 0) {           // uniform: the member itself
+      const uint64_t kw = pref, iw = ipref;
+      for (int q = t; q < c; q += kCutThreads) {
+        const uint32_t i = lds ? ci[q] : member(q);
+        const K o = lds ? ck[q] : keys[i];
+        const bool is = on_key ? ((uint64_t)(o - ka) >> sh) == kw
+                               : ((o - ka) == (K)kw) & (((uint64_t)(i - ia) >> sh) == iw);
+        if (is) {
+          pord = o;
+          pid = i;
+        }
+      }
+      __syncthreads();
+      break;
+    }
+  }
+  if (t == 0) {
+    const long long b = base, ws = hit;
+    int inc = 0;
+    if (Ws > 0) inc = ((long long)p * (b + ws) - jW) < (jW - (long long)p * b) ? 1 : 0;
+    out.ord[tg] = pord;
+    out.id[tg] = pid;
+    out.incl[tg] = inc;
+    out.lo[tg] = Ws > 0 ? b + (inc ? ws : 0) : 0;
+  }
 }
 
 }  // namespace
-
-size_t split_scratch_bytes(int64_t n, int K) {
-  // targets of a level (nsec * (p - 1)), sections and children all fit in K
-  int64_t ns = K < 1 ? 1 : K;
-  size_t b = 0;
-  b += align_up(sizeof(uint64_t) * n, 256);                 // keys
-  b += align_up(sizeof(unsigned long long) * ns * 256, 256); // hist (one row per target)
-  b += align_up(sizeof(uint64_t) * ns, 256);                // pord
-  b += align_up(sizeof(uint32_t) * ns, 256);                // pid
-  b += align_up(sizeof(long long) * ns, 256) * 4;           // base, wstar, W, lo
-  b += align_up(sizeof(long long) * ns, 256);               // Wnext
-  b += align_up(sizeof(int) * ns, 256);                     // incl
-  b += 1024;
-  return b;
-}
 
 std::vector<int> section_counts(int K) {
   std::vector<int> f;
@@ -275,12 +700,159 @@ std::vector<int> section_counts(int K) {
   return f;
 }
 
+// candidates per run (kSub of them per target) of a level with ntgt targets
+static int fast_cap(int64_t n, int ntgt) {
+  return (int)std::min<int64_t>(kFastCap, std::max<int64_t>(256, 4 * n / ntgt)) / kSub;
+}
+
+// every level of K within the sample bins' limits
+static bool fast_levels(const std::vector<int> &counts) {
+  int64_t nsec = 1;
+  for (int p : counts) {
+    if (nsec > kFastSections || p - 1 > kFastCuts || nsec * (p - 1) > kFastTargets) return false;
+    nsec *= p;
+  }
+  return !counts.empty();
+}
+
+size_t split_scratch_bytes(int64_t n, int K) {
+  // targets of a level (nsec * (p - 1)), sections and children all fit in K
+  int64_t ns = K < 1 ? 1 : K;
+  size_t b = 0;
+  b += align_up(sizeof(uint64_t) * n, 256);                 // keys
+  b += align_up(sizeof(unsigned long long) * ns * 256, 256); // hist (one row per target)
+  b += align_up(sizeof(uint64_t) * ns, 256);                // pord
+  b += align_up(sizeof(uint32_t) * ns, 256);                // pid
+  b += align_up(sizeof(long long) * ns, 256) * 4;           // base, wstar, W, lo
+  b += align_up(sizeof(long long) * ns, 256);               // Wnext
+  b += align_up(sizeof(int) * ns, 256);                     // incl
+  size_t f = 0;                                             // sample bins
+  if (fast_levels(section_counts((int)ns))) {
+    f += align_up(sizeof(uint64_t) * n, 256);               // keys
+    f += align_up(sizeof(uint16_t) * n, 256);               // bins
+    f += align_up(sizeof(uint32_t) * (4 * n + 256 * ns), 256);   // candidates
+    f += align_up(sizeof(unsigned long long) * kBins, 256);
+    f += align_up(sizeof(uint64_t) * kSample * 64, 256) +   // samples: a coordinate per level
+         align_up(sizeof(uint32_t) * kSample * 64, 256);
+    f += 2 * (align_up(sizeof(uint64_t) * ns, 256) * 3 + align_up(sizeof(int) * ns, 256) * 2);
+    f += align_up(sizeof(int) * ns, 256) + align_up(sizeof(long long) * ns, 256) +
+         align_up(sizeof(int) * ns * kSub * kSubStride, 256);
+  }
+  return std::max(b, f) + 1024;
+}
+
+// The levels by sample bins.  *flags: F_NAN, F_CROWDED (part is then not
+// usable).
+template <typename T>
+static int split_levels(sphx_graph *g, const T *coords, int ld, int ncoord, int K,
+                        const std::vector<int> &counts, int32_t *part, void *scratch,
+                        void *pinned, hipStream_t s, std::string *err, int *flags) {
+  using KT = typename Ord<T>::K;
+  const int64_t n = g->n;
+  const int nlev = (int)counts.size();
+  const int nc = std::min(ncoord, nlev);      // coordinates in use
+  Arena a;
+  a.base = static_cast<char *>(scratch);
+  KT *keys = a.take<KT>(n);
+  uint16_t *bins = a.take<uint16_t>(n);
+  uint32_t *list = a.take<uint32_t>(4 * n + 256 * (int64_t)K);
+  unsigned long long *hist = a.take<unsigned long long>(kBins);
+  KT *sord = a.take<KT>(kSample * 64);
+  uint32_t *sid = a.take<uint32_t>(kSample * 64);
+  Cuts<KT> cut[2];
+  for (auto &x : cut) {
+    x.p = 0;
+    x.ord = a.take<KT>(K);
+    x.lo = a.take<long long>(K);
+    x.W = a.take<long long>(K);
+    x.id = a.take<uint32_t>(K);
+    x.incl = a.take<int>(K);
+  }
+  int *tbin = a.take<int>(K);
+  int *cnt = a.take<int>((int64_t)K * kSub * kSubStride);
+  long long *base = a.take<long long>(K);
+  int *flag = a.take<int>(4);
+  long long *total = reinterpret_cast<long long *>(flag + 2);
+  int *fh = static_cast<int *>(pinned);
+  hipLaunchKernelGGL(k_split_clear, dim3(1), dim3(256), 0, s, hist, flag);
+  long long W = n;
+  if (g->vwgt) {
+    hipLaunchKernelGGL(k_wsum, dim3(grid_for(n, 256 * 8, 1024)), dim3(256), 0, s, n, g->vwgt,
+                       total);
+    if (hipMemcpyAsync(fh + 2, total, sizeof(long long), hipMemcpyDeviceToHost, s) !=
+            hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess) {
+      *err = "split: stream error";
+      return SPHX_E_HIP;
+    }
+    std::memcpy(&W, fh + 2, sizeof(W));
+  }
+  hipLaunchKernelGGL((k_sample<T>), dim3(nc), dim3(1024), 0, s, coords, ld, n, sord, sid);
+  const unsigned gl = grid_for(n, 512 * 8, 512), gn = grid_for(n, 256 * 4, 2048);
+  int nsec = 1;
+  for (int l = 0; l < nlev; ++l) {
+    const int p = counts[l], ntgt = nsec * (p - 1), c = l % ncoord;
+    int B = kBins;
+    while (B * nsec > kBins) B >>= 1;
+    const Cuts<KT> &prev = cut[(l + 1) & 1];
+    Cuts<KT> &now = cut[l & 1];
+    const int cap = fast_cap(n, ntgt);
+    const KT *so = sord + (int64_t)c * kSample;
+    const uint32_t *si = sid + (int64_t)c * kSample;
+    if (g->vwgt)
+      hipLaunchKernelGGL((k_level<T, unsigned long long>), dim3(gl), dim3(512), 0, s, coords, ld,
+                         c, n, keys, bins, part, g->vwgt, prev, l == 1 ? 1 : 0, so, si, B, nsec,
+                         hist, flag);
+    else
+      hipLaunchKernelGGL((k_level<T, unsigned>), dim3(gl), dim3(512), 0, s, coords, ld, c, n,
+                         keys, bins, part, g->vwgt, prev, l == 1 ? 1 : 0, so, si, B, nsec, hist,
+                         flag);
+    hipLaunchKernelGGL((k_find_bins<KT>), dim3(nsec), dim3(256), 0, s, B, p, prev, W, hist,
+                       now.W, tbin, base, cnt);
+    hipLaunchKernelGGL(k_candidates, dim3(gn), dim3(256), 0, s, n, (const uint16_t *)bins,
+                       (const int32_t *)part, l == 0 ? 1 : 0, p, ntgt, (const int *)tbin, cap,
+                       cnt, list, flag);
+    now.p = p;
+    hipLaunchKernelGGL((k_cut_bin<KT>), dim3(ntgt), dim3(kCutThreads), 0, s, n, p, (const KT *)keys,
+                       g->vwgt, list, cap, (const int *)cnt,
+                       (const long long *)base, now);
+    nsec *= p;
+  }
+  const Cuts<KT> &z = cut[(nlev - 1) & 1];
+  if (nlev == 1) hipLaunchKernelGGL(k_zero_parts, dim3(gn), dim3(256), 0, s, n, part);
+  hipLaunchKernelGGL((k_assign<KT>), dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n, keys,
+                     part, z.p, z.ord, z.id, z.incl, z.W);
+  if (hipGetLastError() != hipSuccess) {
+    *err = "split kernel launch failed";
+    return SPHX_E_HIP;
+  }
+  if (hipMemcpyAsync(fh, flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess) {
+    *err = "split: stream error";
+    return SPHX_E_HIP;
+  }
+  *flags = *fh;
+  return SPHX_OK;
+}
+
 template <typename T>
 int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K, int32_t *part,
              void *scratch, void *pinned, hipStream_t s, std::string *err) {
   using KT = typename Ord<T>::K;
   const int64_t n = g->n;
   const std::vector<int> counts = section_counts(K);
+  if (fast_levels(counts)) {
+    int flags = 0;
+    const int r = split_levels<T>(g, coords, ld, ncoord, K, counts, part, scratch, pinned, s,
+                                  err, &flags);
+    if (r != SPHX_OK) return r;
+    if (flags & F_NAN) {
+      *err = "NaN coordinate";
+      return SPHX_E_INVALID_ARG;
+    }
+    if (!(flags & F_CROWDED)) return SPHX_OK;
+  }
+  // radix passes over all members
   Arena a;
   a.base = static_cast<char *>(scratch);
   a.cap = split_scratch_bytes(n, K);

@@ -127,3 +127,47 @@ def test_products_every_width(handle, kind, m):
         P0 = precond.gmres_poly_apply(g.rowptr, g.col, g.w, sx.GENERALIZED, ref, roots)
         P = sx.poly_apply(handle, G, sx.GENERALIZED, roots, X).cpu().numpy()
         assert np.abs(P - P0).max() <= 100 * tol * np.abs(P0).max()
+
+
+def _split_case(kind, n, rng):
+    if kind == "normal":
+        return rng.standard_normal((n, 3))
+    if kind == "ties":                # a few values: the order is by id
+        return rng.integers(0, 3, (n, 3)).astype(np.float64)
+    if kind == "constant":
+        return np.zeros((n, 3))
+    if kind == "sorted":              # sections are ranges of one coordinate
+        return np.sort(rng.standard_normal((n, 1)), axis=0)
+    x = rng.standard_normal((n, 3)) * 10.0 ** rng.integers(-30, 30, (n, 3))   # localised
+    x[rng.random((n, 3)) < 0.3] = 0.0
+    x[rng.random((n, 3)) < 0.1] = -0.0
+    x[0, 0], x[1, 0] = np.inf, -np.inf
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "constant", "sorted", "wide"])
+@pytest.mark.parametrize("n,K", [(2, 2), (5, 4), (2047, 64), (2049, 24), (70000, 48), (70000, 61),
+                                 (70000, 64 * 63), (40000, 256)])
+def test_split_bins_vs_oracle(handle, kind, n, K):
+    """Sizes around the sample's, section and cut counts on both sides of the
+    sample bins' limits (61 and 4032 = 7 3 3 2^6 cuts at once or by levels),
+    ties, one value, localised values and infinities, with and without vertex
+    weights, both types: the oracle's parts, exactly."""
+    import graphgen
+    import torch
+    import paper_2105_00578_amd as sx
+    from oracle import split as osplit
+    from tests.gpu_util import dev
+    rng = np.random.default_rng(n + K)
+    x = _split_case(kind, n, rng)
+    g = graphgen.csr_from_edges(n, np.arange(n - 1), np.arange(1, n))
+    for weighted in (False, True):
+        vw = rng.integers(1, 50, n).astype(np.int32) if weighted else None
+        G = sx.Graph(handle, torch.from_numpy(g.rowptr.astype(np.int32)),
+                     torch.from_numpy(g.col.astype(np.int32)), None,
+                     None if vw is None else torch.from_numpy(vw))
+        for dt in (np.float32, np.float64):
+            xc = x.astype(dt)
+            ref = osplit.split_mj(xc, K, vwgt=vw)
+            got = sx.split(handle, G, torch.from_numpy(xc).to(dev()), K).cpu().numpy()
+            assert np.array_equal(got, ref), (weighted, dt)
