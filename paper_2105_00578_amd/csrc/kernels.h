@@ -279,7 +279,7 @@ int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K,
 // ---------------------------------------------------------------- quality
 size_t quality_scratch_bytes(int K);
 // 64-bit words of the pinned host buffer `quality` reads its results through
-// (the handle's kPinnedSmallBytes): the 2 x 1024 cut partials and a flag fit,
+// (the handle's kPinnedSmallBytes): the 2 x 2048 cut partials and a flag fit,
 // part weights come back in chunks of this many
 constexpr int kQualityPinnedWords = (int)(kPinnedSmallBytes / 8);
 // cut_fixed (optional): the exact cut as an integer multiple of 2^e0 (unit

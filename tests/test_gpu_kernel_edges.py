@@ -1,5 +1,7 @@
 """Kernels at the edges of their ranges: first and last tile, remainders, and
 both sides of every size rule, against numpy / scipy in FP64."""
+import math
+
 import numpy as np
 import pytest
 import scipy.linalg
@@ -171,3 +173,46 @@ def test_split_bins_vs_oracle(handle, kind, n, K):
             ref = osplit.split_mj(xc, K, vwgt=vw)
             got = sx.split(handle, G, torch.from_numpy(xc).to(dev()), K).cpu().numpy()
             assert np.array_equal(got, ref), (weighted, dt)
+
+
+@pytest.mark.parametrize("kind", ["rows", "empty_runs", "one_row", "hub_edges"])
+@pytest.mark.parametrize("wd", [None, np.float32, np.float64])
+def test_cut_chunks_vs_numpy(handle, kind, wd):
+    """Chunks of 4096 entries whose rows number few, none (a row over several
+    chunks) or more than the 4096 staged ones (runs of empty rows, also at a
+    chunk's first and last entry): the exact cut and part weights."""
+    import graphgen
+    import torch
+    import paper_2105_00578_amd as sx
+    rng = np.random.default_rng(5)
+    if kind == "rows":
+        n, (u, v) = graphgen.brick27(17, 13, 11)
+    elif kind == "empty_runs":        # 3 x 9000 isolated vertices between three rings
+        u, v, n = [], [], 0
+        for size in (4096, 2048, 700):
+            a = n + np.arange(size)
+            u.append(a)
+            v.append(np.roll(a, -1))
+            n += size + 9000
+        u, v = np.concatenate(u), np.concatenate(v)
+    elif kind == "one_row":
+        n = 13000
+        u, v = np.zeros(n - 1, dtype=np.int64), np.arange(1, n)
+    else:                             # hubs of 4096 entries: rows end with chunks
+        n = 4 * 4097
+        u = np.repeat(np.arange(4) * 4097, 4096)
+        v = u + 1 + np.tile(np.arange(4096), 4)
+    w = None if wd is None else graphgen.uniform_weights(u.size, 3, dtype=wd)
+    g = graphgen.csr_from_edges(n, u, v, w)
+    for rpt in (np.int32, np.int64):
+        G = sx.Graph(handle, torch.from_numpy(g.rowptr.astype(rpt)),
+                     torch.from_numpy(g.col.astype(np.int32)),
+                     None if w is None else torch.from_numpy(g.w), validate=True)
+        for K in (2, 9000):
+            part = rng.integers(0, K, n).astype(np.int32)
+            cross = part[u] != part[v]
+            want = math.fsum(w[cross].astype(np.float64)) if w is not None else float(cross.sum())
+            cut, cut2, imb, pw = sx.quality(handle, G, torch.from_numpy(part).cuda(), K)
+            cnt = np.bincount(part, minlength=K)
+            assert cut == want and cut2 == 2 * want and pw == cnt.tolist()
+            assert imb == cnt.max() * K / n
