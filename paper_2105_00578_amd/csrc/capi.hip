@@ -1484,7 +1484,10 @@ int sphx_refine(sphx_handle *h, sphx_graph *g, int K, int32_t *part, double eps,
   char *ws = nullptr;
   SPHX_TRY(get_workspace(h, refine_scratch_bytes(g->n, K), &ws));
   // fixed-point exponent of the exact gains and cuts: the weight range
-  SPHX_TRY(weight_range(g, ws, h->pinned_small, h->stream));
+  // (pattern_stats includes it); the row lengths decide whether long rows are
+  // looked for
+  DegreeStats ds;
+  SPHX_TRY(pattern_stats(g, ws, &ds, h->pinned_small, h->stream));
   std::string err;
   int r = refine(g, part, K, eps, max_passes, cut, imbalance, passes, moves, ws,
                  h->pinned_small, h->stream, &err);

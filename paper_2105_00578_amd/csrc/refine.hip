@@ -17,8 +17,10 @@
 //     exact cut drops, and passes repeat while it does.
 //
 // Every sum is exact (edge counts for unit weights; for float weights the
-// 128-bit fixed point of the quality kernel, in units of 2^e0), so every
-// comparison is exact and independent of the order of the additions.
+// fixed point of the quality kernel, in units of 2^e0), so every comparison is
+// exact and independent of the order of the additions.  A row's sums have
+// 64 bits where the weights' mantissa, their range and 2^12 terms fit (unit
+// weights, and FP32 ones of a range up to 2^25), else 128.
 #include <cmath>
 #include <vector>
 
@@ -28,37 +30,153 @@
 namespace sphx {
 namespace {
 
-using S = __int128;
+using S128 = __int128;
 
 constexpr int kThreadDeg = 32;        // rows up to this degree: one thread each
 constexpr int kRefineMaxDeg = 2048;   // rows above this degree never move
 constexpr int kScanBlocks = 1024;
 
-template <typename WT>
-__device__ __forceinline__ S wfix(const WT *w, int64_t k, int e0) {
+template <typename S, typename WT>
+__device__ __forceinline__ S wfix_of(WT w, int e0) {
   if constexpr (std::is_same_v<WT, Unit>) {
     return 1;
   } else {
     unsigned long long lo, hi;
-    fixed_of(w[k], e0, lo, hi);
-    return (S)(((unsigned __int128)hi << 64) | lo);
+    fixed_of(w, e0, lo, hi);
+    if constexpr (sizeof(S) == 8) return (S)lo;
+    else return (S)(((unsigned __int128)hi << 64) | lo);
   }
+}
+template <typename S, typename WT>
+__device__ __forceinline__ S wfix(const WT *w, int64_t k, int e0) {
+  if constexpr (std::is_same_v<WT, Unit>) return 1;
+  else return wfix_of<S, WT>(w[k], e0);
 }
 
 // (c, p) beats (best, t): a larger connection, the smaller part on ties
+template <typename S>
 __device__ __forceinline__ bool better(S c, int p, S best, int t) {
   return p >= 0 && (t < 0 || c > best || (c == best && p < t));
 }
 
-// Step 1 for rows of degree <= kThreadDeg (one thread per row, the row's
-// neighbour parts in this thread's LDS column).  Rows of larger degree are
+// Step 1 with 64-bit sums for rows of degree <= kThreadDeg: four lanes per
+// row, lane l holding the parts and weights of entries l, l + 4, ... in
+// registers (all gathers of a row in flight together; a thread per row
+// walked them one by one, 317 us per pass on a weighted 27-point mesh of
+// 883,200 rows, now 45).  A row whose neighbours all share its part is
+// done; else its parts are taken in increasing order: the group's smallest
+// part not taken yet, the connection to it, and the largest kept.  Rows of
+// larger degree are flagged for k_gain_block; empty rows are no candidates.
+constexpr int kRowLanes = 4;
+constexpr int kRowPer = kThreadDeg / kRowLanes;
+
+template <typename T>
+__device__ __forceinline__ T quad_sum(T x) {
+  x += __shfl_xor(x, 1);
+  x += __shfl_xor(x, 2);
+  return x;
+}
+
+template <typename IdxT, typename WT>
+__global__ __launch_bounds__(256) void k_gain_quad(int64_t n, const IdxT *__restrict__ rp,
+                                                   const int32_t *__restrict__ col,
+                                                   const WT *__restrict__ w, int e0,
+                                                   const int32_t *__restrict__ part,
+                                                   int32_t *tgt, long long *gain, uint8_t *big) {
+  using S = long long;
+  const int gl = threadIdx.x & (kRowLanes - 1);
+  constexpr int R = 256 / kRowLanes;
+  constexpr int kNone = 0x7fffffff;
+  // the row loop is uniform over each wave (shuffles within the quads)
+  const int64_t step = (int64_t)gridDim.x * R;
+  for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < n; r0 += step) {
+    const int64_t v = r0 + threadIdx.x / kRowLanes;
+    int64_t lo = 0, d = 0;
+    int a = 0;
+    if (v < n) {
+      lo = rp[v];
+      d = (int64_t)rp[v + 1] - lo;
+      a = part[v];
+    }
+    const bool mine = d >= 1 && d <= kThreadDeg;
+    int p[kRowPer];
+    WT x[kRowPer];
+#pragma unroll
+    for (int q = 0; q < kRowPer; ++q) {
+      const int e = gl + q * kRowLanes;
+      p[q] = mine && e < d ? col[lo + e] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < kRowPer; ++q) p[q] = p[q] >= 0 ? part[p[q]] : kNone;
+    bool edge = false;
+#pragma unroll
+    for (int q = 0; q < kRowPer; ++q) edge |= p[q] != kNone && p[q] != a;
+    S g = 0;
+    int t = -1;
+    // rows with another part: uniform over the quad
+    const unsigned long long who = __ballot(edge);
+    const bool on = ((who >> (threadIdx.x & 60)) & 15ull) != 0;
+    if (who) {                          // uniform over the wave
+      if constexpr (!std::is_same_v<WT, Unit>) {
+#pragma unroll
+        for (int q = 0; q < kRowPer; ++q)
+          x[q] = on && p[q] != kNone ? w[lo + gl + q * kRowLanes] : WT(1);
+      }
+      S f[kRowPer];
+      S ca = 0;
+#pragma unroll
+      for (int q = 0; q < kRowPer; ++q) {
+        if constexpr (std::is_same_v<WT, Unit>) f[q] = 1;
+        else f[q] = wfix_of<S, WT>(x[q], e0);
+        if (p[q] == a) {
+          ca += f[q];
+          p[q] = kNone;
+        }
+      }
+      ca = quad_sum(ca);
+      S best = 0;
+      while (true) {
+        int m = kNone;
+#pragma unroll
+        for (int q = 0; q < kRowPer; ++q) m = min(m, p[q]);
+        m = min(m, __shfl_xor(m, 1));
+        m = min(m, __shfl_xor(m, 2));
+        if (!on) m = kNone;
+        if (__ballot(m != kNone) == 0ull) break;   // uniform over the wave
+        S c = 0;
+#pragma unroll
+        for (int q = 0; q < kRowPer; ++q)
+          if (p[q] == m) {
+            c += f[q];
+            p[q] = kNone;
+          }
+        c = quad_sum(c);
+        if (m != kNone && (t < 0 || c > best)) {   // increasing parts: ties keep the smaller
+          best = c;
+          t = m;
+        }
+      }
+      if (t >= 0 && best - ca > 0) g = best - ca;
+      else t = -1;
+    }
+    if (gl == 0 && v < n) {
+      tgt[v] = t;
+      gain[v] = g;
+      big[v] = (d > kThreadDeg && d <= kRefineMaxDeg) ? 1 : 0;
+    }
+  }
+}
+
+// Step 1 with 128-bit sums for rows of degree <= kThreadDeg (one thread per
+// row, the row's neighbour parts in this thread's LDS column).  Rows of larger degree are
 // flagged for k_gain_block; empty rows are no candidates.
 template <typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_gain_thread(int64_t n, const IdxT *__restrict__ rp,
                                                      const int32_t *__restrict__ col,
                                                      const WT *__restrict__ w, int e0,
                                                      const int32_t *__restrict__ part,
-                                                     int32_t *tgt, S *gain, uint8_t *big) {
+                                                     int32_t *tgt, S128 *gain, uint8_t *big) {
+  using S = S128;
   __shared__ int32_t sp[kThreadDeg * 256];
   const int tid = threadIdx.x;
   for (int64_t v = (int64_t)blockIdx.x * 256 + tid; v < n; v += (int64_t)gridDim.x * 256) {
@@ -74,7 +192,7 @@ __global__ __launch_bounds__(256) void k_gain_thread(int64_t n, const IdxT *__re
       for (int j = 0; j < dd; ++j) {
         const int p = sp[j * 256 + tid];
         if (p == a) {
-          ca += wfix(w, lo + j, e0);
+          ca += wfix<S>(w, lo + j, e0);
           continue;
         }
         bool first = true;
@@ -86,7 +204,7 @@ __global__ __launch_bounds__(256) void k_gain_thread(int64_t n, const IdxT *__re
         if (!first) continue;
         S c = 0;
         for (int q = j; q < dd; ++q)
-          if (sp[q * 256 + tid] == p) c += wfix(w, lo + q, e0);
+          if (sp[q * 256 + tid] == p) c += wfix<S>(w, lo + q, e0);
         if (better(c, p, best, t)) {
           best = c;
           t = p;
@@ -109,7 +227,7 @@ __global__ __launch_bounds__(256) void k_gain_thread(int64_t n, const IdxT *__re
 // of the part owns the sum).
 constexpr int kLdsParts = 8192;
 
-template <typename IdxT, typename WT>
+template <typename S, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_gain_block(const int32_t *__restrict__ rows,
                                                     const int32_t *__restrict__ nrows,
                                                     const IdxT *__restrict__ rp,
@@ -158,7 +276,7 @@ __global__ __launch_bounds__(256) void k_gain_block(const int32_t *__restrict__ 
       for (int j = tid; j < d; j += 256) {
         const int p = sp[j];
         if (p == a) {
-          ca += wfix(w, lo + j, e0);
+          ca += wfix<S>(w, lo + j, e0);
           continue;
         }
         bool first = true;
@@ -170,7 +288,7 @@ __global__ __launch_bounds__(256) void k_gain_block(const int32_t *__restrict__ 
         if (!first) continue;
         S c = 0;
         for (int q = j; q < d; ++q)
-          if (sp[q] == p) c += wfix(w, lo + q, e0);
+          if (sp[q] == p) c += wfix<S>(w, lo + q, e0);
         if (better(c, p, best, t)) {
           best = c;
           t = p;
@@ -210,7 +328,7 @@ __global__ __launch_bounds__(256) void k_gain_block(const int32_t *__restrict__ 
 
 // Step 2: a candidate stays a mover when its gain, with every higher-ranked
 // candidate neighbour at its target, is positive.
-template <typename IdxT, typename WT>
+template <typename S, typename IdxT, typename WT>
 __device__ __forceinline__ S moved_gain(int64_t v, int64_t k0, int64_t k1, int64_t step,
                                         const int32_t *__restrict__ col,
                                         const WT *__restrict__ w, int e0,
@@ -226,14 +344,15 @@ __device__ __forceinline__ S moved_gain(int64_t v, int64_t k0, int64_t k1, int64
       const S gu = gain[u];
       if (gu > gv || (gu == gv && u < v)) pu = tu;
     }
-    if (pu == t) g2 += wfix(w, k, e0);
-    else if (pu == a) g2 -= wfix(w, k, e0);
+    if (pu == t) g2 += wfix<S>(w, k, e0);
+    else if (pu == a) g2 -= wfix<S>(w, k, e0);
   }
   return g2;
 }
 
-// rows of degree <= kThreadDeg (and the rows that never move): one thread each
-template <typename IdxT, typename WT>
+// 128-bit sums: rows of degree <= kThreadDeg (and the rows that never move),
+// one thread each
+template <typename S, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_movers(int64_t n, const IdxT *__restrict__ rp,
                                                 const int32_t *__restrict__ col,
                                                 const WT *__restrict__ w, int e0,
@@ -248,7 +367,7 @@ __global__ __launch_bounds__(256) void k_movers(int64_t n, const IdxT *__restric
     const int t = tgt[v];
     uint8_t f = 0;
     if (t >= 0)
-      f = moved_gain<IdxT, WT>(v, k0, k1, 1, col, w, e0, part, tgt, gain, part[v], t,
+      f = moved_gain<S, IdxT, WT>(v, k0, k1, 1, col, w, e0, part, tgt, gain, part[v], t,
                                gain[v]) > 0
               ? 1
               : 0;
@@ -256,8 +375,70 @@ __global__ __launch_bounds__(256) void k_movers(int64_t n, const IdxT *__restric
   }
 }
 
-// the listed rows (kThreadDeg < degree <= kRefineMaxDeg): one wave each
+// Step 2 with 64-bit sums for rows of degree <= kThreadDeg: four lanes per
+// row, as k_gain_quad; only candidates read their row.  (One thread per row:
+// 77 us per pass on the 27-point mesh, now 37.)
 template <typename IdxT, typename WT>
+__global__ __launch_bounds__(256) void k_movers_quad(int64_t n, const IdxT *__restrict__ rp,
+                                                     const int32_t *__restrict__ col,
+                                                     const WT *__restrict__ w, int e0,
+                                                     const int32_t *__restrict__ part,
+                                                     const int32_t *__restrict__ tgt,
+                                                     const long long *__restrict__ gain,
+                                                     uint8_t *mv) {
+  using S = long long;
+  const int gl = threadIdx.x & (kRowLanes - 1);
+  constexpr int R = 256 / kRowLanes;
+  const int64_t step = (int64_t)gridDim.x * R;
+  for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < n; r0 += step) {
+    const int64_t v = r0 + threadIdx.x / kRowLanes;
+    const int t = v < n ? tgt[v] : -1;
+    int64_t lo = 0, d = 0;
+    int a = 0;
+    S gv = 0;
+    if (t >= 0) {
+      lo = rp[v];
+      d = (int64_t)rp[v + 1] - lo;
+      a = part[v];
+      gv = gain[v];
+    }
+    if (d > kThreadDeg) {               // k_movers_wave (uniform over the quad)
+      d = -1;
+    }
+    if (__ballot(d > 0) != 0ull) {      // uniform over the wave
+      int u[kRowPer], pu[kRowPer], tu[kRowPer];
+#pragma unroll
+      for (int q = 0; q < kRowPer; ++q) {
+        const int e = gl + q * kRowLanes;
+        u[q] = e < d ? col[lo + e] : -1;
+      }
+#pragma unroll
+      for (int q = 0; q < kRowPer; ++q) {
+        pu[q] = u[q] >= 0 ? part[u[q]] : -1;
+        tu[q] = u[q] >= 0 ? tgt[u[q]] : -1;
+      }
+      S g2 = 0;
+#pragma unroll
+      for (int q = 0; q < kRowPer; ++q) {
+        if (tu[q] >= 0) {
+          const S gu = gain[u[q]];
+          if (gu > gv || (gu == gv && u[q] < v)) pu[q] = tu[q];
+        }
+        if (u[q] >= 0 && (pu[q] == t || pu[q] == a)) {
+          const S f = wfix<S>(w, lo + gl + q * kRowLanes, e0);
+          g2 += pu[q] == t ? f : -f;
+        }
+      }
+      g2 = quad_sum(g2);
+      if (gl == 0 && v < n && d >= 0) mv[v] = (d > 0 && g2 > 0) ? 1 : 0;
+    } else if (gl == 0 && v < n && d >= 0) {
+      mv[v] = 0;
+    }
+  }
+}
+
+// the listed rows (kThreadDeg < degree <= kRefineMaxDeg): one wave each
+template <typename S, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_movers_wave(const int32_t *__restrict__ rows,
                                                      const int32_t *__restrict__ nrows,
                                                      const IdxT *__restrict__ rp,
@@ -282,7 +463,7 @@ __global__ __launch_bounds__(256) void k_movers_wave(const int32_t *__restrict__
       t = tgt[v];
       if (t >= 0) {
         const int64_t k0 = rp[v], k1 = rp[v + 1];
-        g2 = moved_gain<IdxT, WT>(v, k0 + lane, k1, 64, col, w, e0, part, tgt, gain, part[v],
+        g2 = moved_gain<S, IdxT, WT>(v, k0 + lane, k1, 64, col, w, e0, part, tgt, gain, part[v],
                                   t, gain[v]);
       }
     }
@@ -539,7 +720,7 @@ __global__ void k_copy_i32(const int32_t *__restrict__ a, int32_t *b, int64_t n)
 size_t refine_scratch_bytes(int64_t n, int K) {
   size_t b = 0;
   b += align_up(sizeof(int32_t) * n, 256) * 4;                       // nxt, tgt, list, rows
-  b += align_up(sizeof(S) * n, 256);                                 // gain
+  b += align_up(sizeof(S128) * n, 256);                              // gain
   b += align_up(n, 256) * 2;                                         // flags (big, mover)
   b += align_up(sizeof(int32_t) * (kScanBlocks + 1), 256) * 2;       // block counts
   b += align_up(sizeof(unsigned long long) * (size_t)K, 256) * 2;    // W, arrivals
@@ -561,7 +742,7 @@ int refine(sphx_graph *g, int32_t *part, int K, double eps, int max_passes, doub
   int32_t *tgt = a.take<int32_t>(n);
   int32_t *list = a.take<int32_t>(n);
   int32_t *rows = a.take<int32_t>(n);
-  S *gain = a.take<S>(n);
+  S128 *gain128 = a.take<S128>(n);   // long long where 64 bits hold the sums
   uint8_t *big = a.take<uint8_t>(n);
   uint8_t *mv = a.take<uint8_t>(n);
   int32_t *cnt_rows = a.take<int32_t>(kScanBlocks + 1);
@@ -597,30 +778,47 @@ int refine(sphx_graph *g, int32_t *part, int K, double eps, int max_passes, doub
   int kept = 0;
   int64_t nmoves = 0;
   const unsigned gv = grid_for(n, 256, 8192);
-  auto go = [&](auto idx_tag, auto w_tag) -> int {
+  // rows above kThreadDeg are listed and take the block kernels
+  const bool long_rows = !(g->stats_valid && g->max_deg <= kThreadDeg);
+  auto go = [&](auto s_tag, auto idx_tag, auto w_tag) -> int {
+    using S = decltype(s_tag);
     using IdxT = decltype(idx_tag);
     using WT = decltype(w_tag);
     const IdxT *rp = static_cast<const IdxT *>(g->rowptr);
     const WT *w = static_cast<const WT *>(g->w);
+    S *gain = reinterpret_cast<S *>(gain128);
+    const unsigned gq = grid_for(n, 256 / kRowLanes, 16384);
     for (int pass = 0; pass < max_passes; ++pass) {
       // 1. gains
-      hipLaunchKernelGGL((k_gain_thread<IdxT, WT>), dim3(gv), dim3(256), 0, s, n, rp, g->col, w,
-                         e0, (const int32_t *)cur, tgt, gain, big);
-      hipLaunchKernelGGL(k_flag_count, dim3(kScanBlocks), dim3(256), 0, s, n,
-                         (const uint8_t *)big, cnt_rows);
-      hipLaunchKernelGGL(k_flag_scan, dim3(1), dim3(kScanBlocks), 0, s, cnt_rows);
-      hipLaunchKernelGGL(k_flag_scatter, dim3(kScanBlocks), dim3(256), 0, s, n,
-                         (const uint8_t *)big, (const int32_t *)cnt_rows, rows);
+      if constexpr (sizeof(S) == 8)
+        hipLaunchKernelGGL((k_gain_quad<IdxT, WT>), dim3(gq), dim3(256), 0, s, n, rp, g->col, w,
+                           e0, (const int32_t *)cur, tgt, gain, big);
+      else
+        hipLaunchKernelGGL((k_gain_thread<IdxT, WT>), dim3(gv), dim3(256), 0, s, n, rp, g->col,
+                           w, e0, (const int32_t *)cur, tgt, gain, big);
       const int32_t *nbig = cnt_rows + kScanBlocks;
-      hipLaunchKernelGGL((k_gain_block<IdxT, WT>), dim3(2048), dim3(256), 0, s,
-                         (const int32_t *)rows, nbig, rp, g->col, w, e0, (const int32_t *)cur, K,
-                         tgt, gain);
+      if (long_rows) {
+        hipLaunchKernelGGL(k_flag_count, dim3(kScanBlocks), dim3(256), 0, s, n,
+                           (const uint8_t *)big, cnt_rows);
+        hipLaunchKernelGGL(k_flag_scan, dim3(1), dim3(kScanBlocks), 0, s, cnt_rows);
+        hipLaunchKernelGGL(k_flag_scatter, dim3(kScanBlocks), dim3(256), 0, s, n,
+                           (const uint8_t *)big, (const int32_t *)cnt_rows, rows);
+        hipLaunchKernelGGL((k_gain_block<S, IdxT, WT>), dim3(2048), dim3(256), 0, s,
+                           (const int32_t *)rows, nbig, rp, g->col, w, e0, (const int32_t *)cur,
+                           K, tgt, gain);
+      }
       // 2. conflicts
-      hipLaunchKernelGGL((k_movers<IdxT, WT>), dim3(gv), dim3(256), 0, s, n, rp, g->col, w, e0,
-                         (const int32_t *)cur, (const int32_t *)tgt, (const S *)gain, mv);
-      hipLaunchKernelGGL((k_movers_wave<IdxT, WT>), dim3(2048), dim3(256), 0, s,
-                         (const int32_t *)rows, nbig, rp, g->col, w, e0, (const int32_t *)cur,
-                         (const int32_t *)tgt, (const S *)gain, mv);
+      if constexpr (sizeof(S) == 8)
+        hipLaunchKernelGGL((k_movers_quad<IdxT, WT>), dim3(gq), dim3(256), 0, s, n, rp, g->col,
+                           w, e0, (const int32_t *)cur, (const int32_t *)tgt, (const S *)gain,
+                           mv);
+      else
+        hipLaunchKernelGGL((k_movers<S, IdxT, WT>), dim3(gv), dim3(256), 0, s, n, rp, g->col, w,
+                           e0, (const int32_t *)cur, (const int32_t *)tgt, (const S *)gain, mv);
+      if (long_rows)
+        hipLaunchKernelGGL((k_movers_wave<S, IdxT, WT>), dim3(2048), dim3(256), 0, s,
+                           (const int32_t *)rows, nbig, rp, g->col, w, e0, (const int32_t *)cur,
+                           (const int32_t *)tgt, (const S *)gain, mv);
       hipLaunchKernelGGL(k_flag_count, dim3(kScanBlocks), dim3(256), 0, s, n,
                          (const uint8_t *)mv, cnt_mv);
       hipLaunchKernelGGL(k_flag_scan, dim3(1), dim3(kScanBlocks), 0, s, cnt_mv);
@@ -687,16 +885,21 @@ int refine(sphx_graph *g, int32_t *part, int K, double eps, int max_passes, doub
     }
     return SPHX_OK;
   };
-  int r;
-  if (g->rp64) {
-    if (g->wdt == SPHX_UNIT) r = go(int64_t{}, Unit{});
-    else if (g->wdt == SPHX_F32) r = go(int64_t{}, float{});
-    else r = go(int64_t{}, double{});
-  } else {
-    if (g->wdt == SPHX_UNIT) r = go(int32_t{}, Unit{});
-    else if (g->wdt == SPHX_F32) r = go(int32_t{}, float{});
-    else r = go(int32_t{}, double{});
+  // 24 mantissa bits, the range, and 2^12 terms of either sign
+  bool narrow = g->wdt == SPHX_UNIT;
+  if (g->wdt == SPHX_F32 && g->nnz > 0) {
+    int ea, eb;
+    std::frexp(g->wmax, &ea);
+    std::frexp(g->wmin, &eb);
+    narrow = ea - eb <= 25;
   }
+  int r;
+  auto with_idx = [&](auto idx_tag) -> int {
+    if (g->wdt == SPHX_UNIT) return go((long long)0, idx_tag, Unit{});
+    if (g->wdt == SPHX_F64) return go(S128(0), idx_tag, double{});
+    return narrow ? go((long long)0, idx_tag, float{}) : go(S128(0), idx_tag, float{});
+  };
+  r = g->rp64 ? with_idx(int64_t{}) : with_idx(int32_t{});
   if (r != SPHX_OK) return r;
   if (cur != part) {
     hipLaunchKernelGGL(k_copy_i32, dim3(gv), dim3(256), 0, s, (const int32_t *)cur, part, n);

@@ -216,3 +216,33 @@ def test_cut_chunks_vs_numpy(handle, kind, wd):
             cnt = np.bincount(part, minlength=K)
             assert cut == want and cut2 == 2 * want and pw == cnt.tolist()
             assert imb == cnt.max() * K / n
+
+
+@pytest.mark.parametrize("log_range", [0, 24, 25, 26, 39])
+@pytest.mark.parametrize("deg", [4, 32, 34])
+def test_refine_sum_widths(handle, log_range, deg):
+    """Rows at the four-lane kernels' degree limit and past it, and FP32
+    weight ranges on both sides of what 64-bit sums hold: the oracle's parts,
+    exactly."""
+    import graphgen
+    import torch
+    import paper_2105_00578_amd as sx
+    from oracle import refine
+    from tests.gpu_util import dev, upload
+    n, half = 700, deg // 2
+    u = np.repeat(np.arange(n), half)          # a circulant graph of degree `deg`
+    v = (u + 1 + np.tile(np.arange(half), n)) % n
+    rng = np.random.default_rng(deg + log_range)
+    w = ((1.0 + rng.random(u.size)) * 2.0 ** rng.integers(0, log_range + 1, u.size) * 0.7)
+    w = w.astype(np.float32)
+    w[0], w[1] = 0.7, np.float32(0.7) * np.float32(2.0) ** log_range
+    g = graphgen.csr_from_edges(n, u, v, w)
+    rp, col, wd = upload(g)
+    G = sx.Graph(handle, rp, col, wd)
+    K = 6
+    part0 = ((np.arange(n) * K // n + (rng.random(n) < 0.3)) % K).astype(np.int32)
+    pd = torch.from_numpy(part0.copy()).to(dev())
+    cut, imb, kept, moves = sx.refine(handle, G, pd, K, eps=0.2)
+    ref, kept_ref, moves_ref = refine.refine(g.rowptr, g.col, g.w, part0, K, eps=0.2)
+    assert np.array_equal(pd.cpu().numpy(), ref) and (kept, moves) == (kept_ref, moves_ref)
+    assert moves > 0
