@@ -304,10 +304,14 @@ __global__ void k_expand_cols(const T *Hc, int lda, ColMap act, T *H, int ld, in
 }
 
 // Row width of the compacted polynomial block for na active columns: exactly
-// those (the vector-row products take any width of at least 2).  The 25 steps
-// of an apply are bound by the bytes of their four blocks; rounding the width
-// up to whole vectors cost 1/7 of them at 7 FP32 columns.
-inline int compact_ld(int na) { return na < 2 ? 2 : na; }
+// those for rows of at most 12 neighbours (the 25 steps of an apply are bound
+// by the bytes of their four blocks there; rounding up to whole vectors cost
+// 1/7 of them at 7 FP32 columns), else even, so that FP32 rows are whole
+// 8-byte vectors and FP64 rows 16-byte ones (as for the solver's blocks).
+inline int compact_ld(int na, const SpmmPlan &plan) {
+  const bool exact = !plan.binned && plan.group == 1;
+  return exact ? std::max(na, 2) : (na + 1) / 2 * 2;
+}
 
 // H[:, cm] = p(L) R[:, cm]: returns the buffer holding the result (n x ld,
 // the columns of cm).  With `spare` (an n x ld buffer whose contents may be
@@ -325,7 +329,7 @@ int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
   const double b4 = spmm_bytes(g, plan, cm.count, sizeof(T), 4, rd);
   const int64_t n = g->n;
   const int na = cm.count;
-  const int lda = compact_ld(na);
+  const int lda = compact_ld(na, plan);
   const bool compact = spare && lda < ld;
   const int wd = compact ? lda : ld;     // row width of the iteration buffers
   const int mm = compact ? na : m;
@@ -430,7 +434,7 @@ int poly_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
                int64_t *pcalls) {
   const int64_t n = g->n;
   const int na = cm.count;
-  const int lda = compact_ld(na);
+  const int lda = compact_ld(na, plan);
   const int rd = dinv ? 1 : 0;
   const double b3 = spmm_bytes(g, plan, na, sizeof(T), 3, rd);
   const double b4 = spmm_bytes(g, plan, na, sizeof(T), 4, rd);
@@ -519,7 +523,8 @@ int solve(sphx_handle *h, sphx_graph *g, int m, const sphx_options &o, const voi
   SPHX_TRY(build_plan(G, pa, &w.plan, ds, h->pinned_small, s));
   pl.end(tid, s);
   const int vs = sizeof(T);
-  const int ld = padded_ld(m, sizeof(T));   // 16-byte rows for the vector kernels
+  const bool short_rows = !w.plan.binned && w.plan.group == 1;
+  const int ld = block_ld(m, sizeof(T), short_rows);
   const double *bdiag = gen ? w.d64 : nullptr;
   const double *dinv = nullptr;
   ChebCoef ck;
@@ -605,9 +610,10 @@ int solve(sphx_handle *h, sphx_graph *g, int m, const sphx_options &o, const voi
     pl.end(id, s);
     ++calls;
     id = pl.begin(PH_OTHER, 0.0, s);
-    launch_finalize(w.norm_partials, nb, m, w.theta, o.tol, o.locking, w.status, s);
+    launch_finalize(w.norm_partials, nb, m, w.theta, o.tol, o.locking, w.status,
+                    h->pinned_status_dev, s);
     pl.end(id, s);
-    SPHX_HIP(h, hipMemcpyAsync(hs, w.status, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
+    SPHX_HIP(h, hipGetLastError());
     SPHX_HIP(h, hipStreamSynchronize(s));
     return SPHX_OK;
   };
@@ -714,8 +720,9 @@ int solve(sphx_handle *h, sphx_graph *g, int m, const sphx_options &o, const voi
     SPHX_TRY(vspmm_store<double>(G, w.plan, X64, ld, m, EpiStoreP<double>{LX64, ld}, s));
     ++calls;
   }
-  int rb = (int)grid_for(n, 256 / ld, kRqBlocks);
-  launch_rq_partials<double>(X64, LX64, n, m, ld, bdiag, w.rq_partials, rb, s);
+  const int lanes = padded_ld(m, sizeof(T));
+  int rb = (int)grid_for(n, 256 / lanes, kRqBlocks);
+  launch_rq_partials<double>(X64, LX64, n, m, ld, lanes, bdiag, w.rq_partials, rb, s);
   launch_sum_partials(w.rq_partials, rb, m, w.rq_sums, s);
   double sums[2 * kMaxNev];
   SPHX_HIP(h, hipMemcpyAsync(sums, w.rq_sums, sizeof(sums), hipMemcpyDeviceToHost, s));
@@ -723,7 +730,7 @@ int solve(sphx_handle *h, sphx_graph *g, int m, const sphx_options &o, const voi
   double th[kMaxNev];
   for (int c = 0; c < m; ++c) th[c] = sums[kMaxNev + c] > 0 ? sums[c] / sums[kMaxNev + c] : 0;
   SPHX_HIP(h, hipMemcpyAsync(w.theta, th, sizeof(double) * m, hipMemcpyHostToDevice, s));
-  launch_res_partials<double>(X64, LX64, n, m, ld, bdiag, w.theta, w.rq_partials, rb, s);
+  launch_res_partials<double>(X64, LX64, n, m, ld, lanes, bdiag, w.theta, w.rq_partials, rb, s);
   launch_sum_partials(w.rq_partials, rb, m, w.res_sums, s);
   double rs[2 * kMaxNev];
   SPHX_HIP(h, hipMemcpyAsync(rs, w.res_sums, sizeof(rs), hipMemcpyDeviceToHost, s));
@@ -793,6 +800,8 @@ int sphx_create(sphx_handle **out, int device, void *stream) {
   h->stream = static_cast<hipStream_t>(stream);
   if (hipSetDevice(device) != hipSuccess ||
       hipHostMalloc((void **)&h->pinned_status, sizeof(DevStatus)) != hipSuccess ||
+      hipHostGetDevicePointer((void **)&h->pinned_status_dev, h->pinned_status, 0) !=
+          hipSuccess ||
       hipHostMalloc(&h->pinned_small, kPinnedSmallBytes) != hipSuccess ||
       hipMalloc((void **)&h->flags_dev, 256) != hipSuccess ||
       resolve_noalloc_scratch(device) != SPHX_OK) {
@@ -1226,7 +1235,7 @@ int sphx_poly_apply(sphx_handle *h, sphx_graph *g, int problem, int nroots,
   hipStream_t s = h->stream;
   const int64_t n = g->n;
   const int es = bytes_of(dtype);
-  const int wd = std::max(m, compact_ld(m));   // widest row the buffers must hold
+  const int wd = (m + 1) / 2 * 2;              // widest row the buffers must hold
   const size_t blk = (size_t)n * wd * es;
   size_t need = plan_bytes(g) + 4 * align_up(sizeof(double) * n, 256) +
                 align_up(4 * kDegBlocksMax * sizeof(double), 256) + 4 * align_up(blk, 256) +

@@ -110,6 +110,7 @@ struct sphx_handle {
   size_t ws_own_bytes = 0;
   int timing = 0;
   sphx::DevStatus *pinned_status = nullptr;   // hipHostMalloc'ed
+  sphx::DevStatus *pinned_status_dev = nullptr;   // its device address
   void *pinned_small = nullptr;               // kPinnedSmallBytes of pinned host
                                               // memory for small D2H reads
   int32_t *flags_dev = nullptr;               // 256 device bytes: validation flags

@@ -265,6 +265,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double *partials, int
     int i = ij / W, j = ij - i * W;
     if (i <= j && j < w) {
       int b = sub;
+#pragma unroll 8
       for (; b + 16 < nblocks; b += 32) {
         s0 += partials[(int64_t)b * E + e];
         s1 += partials[(int64_t)(b + 16) * E + e];
@@ -913,95 +914,78 @@ struct UpdDev {
   int64_t n;
   int m, ld;
   int na;
-  int act[kMaxNev];
+  int pos[kMaxNev];   // column -> position among the active ones, or -1
   int use_h, use_p;
   int offH, offP;     // rows of Y for the H and P parts
   int update_lp;      // also LP <- LH y_H + LP y_P
 };
 
-// Rows of all blocks have stride ld, a multiple of E (4 floats: 16-byte
-// loads; FP64 elements are loaded one by one, which measured faster than
-// pairs).  A chunk of 256 E elements (256 E / ld rows) of each block is read
-// with one load per thread and block into LDS (kept in T; widened to double
-// where used); thread t then computes the elements t + 256 j of the chunk
-// (column c = e % ld < m; padding columns untouched), each as a sum in a
-// fixed order: the X part over k, plus the H and P parts over the active
-// columns.
-template <typename T> struct UpdVec;
-template <> struct UpdVec<float> {
-  typedef float type __attribute__((ext_vector_type(4)));
-  static constexpr int E = 4;
-};
-template <> struct UpdVec<double> {
-  typedef double type;
-  static constexpr int E = 1;
-};
-
-template <typename T>
+// One row per thread, M = m columns in registers; the Rayleigh-Ritz
+// coefficients are the same for every thread, so they come through the scalar
+// cache.  Every output is a sum in a fixed order: the H part over the active
+// columns, then the P part, plus the X part over k.  Bound by the blocks'
+// bytes.  With rows and coefficients in LDS each multiply-add waited on two
+// LDS reads: 2 M rows of 7 FP32 columns took 91 us, now 48 (5 passes of
+// 55 MB); 216,000 rows of 5 FP64 columns 21 us, now 15.
+template <typename T, int M>
 __global__ __launch_bounds__(256) void k_update(T *X, const T *__restrict__ H, T *P,
                                                 const T *__restrict__ LH, T *LP,
-                                                const double *__restrict__ Yg, UpdDev a) {
-  using V = typename UpdVec<T>::type;
-  constexpr int E = UpdVec<T>::E;
-  constexpr int CH = 256 * E;
-  __shared__ double sY[kMaxW * kMaxNev];
-  __shared__ V sX[256], sH[256], sP[256], sLH[256], sLP[256];
-  const T *lX = reinterpret_cast<const T *>(sX);
-  const T *lH = reinterpret_cast<const T *>(sH);
-  const T *lP = reinterpret_cast<const T *>(sP);
-  const T *lLH = reinterpret_cast<const T *>(sLH);
-  const T *lLP = reinterpret_cast<const T *>(sLP);
-  const bool upd_lp = a.update_lp;
-  const int m = a.m, ld = a.ld;
-  const int rc = CH / ld;       // rows per chunk
-  const int t = threadIdx.x;
-  for (int e = t; e < kMaxW * kMaxNev; e += blockDim.x) sY[e] = Yg[e];
+                                                const double *__restrict__ Y, UpdDev a) {
   const bool write_p = a.use_h || a.use_p;
-  for (int64_t r0 = (int64_t)blockIdx.x * rc; r0 < a.n; r0 += (int64_t)gridDim.x * rc) {
-    const int64_t base = r0 * ld;
-    const int lim = (int)min((int64_t)rc, a.n - r0) * ld;
-    __syncthreads();
-    if (t * E < lim) {
-      const int64_t vb = base / E + t;
-      sX[t] = reinterpret_cast<const V *>(X)[vb];
-      if (a.use_h) {
-        sH[t] = reinterpret_cast<const V *>(H)[vb];
-        if (upd_lp) sLH[t] = reinterpret_cast<const V *>(LH)[vb];
-      }
-      if (a.use_p) {
-        sP[t] = reinterpret_cast<const V *>(P)[vb];
-        if (upd_lp) sLP[t] = reinterpret_cast<const V *>(LP)[vb];
-      }
-    }
-    __syncthreads();
+  const bool lp_too = a.update_lp;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n;
+       i += (int64_t)gridDim.x * 256) {
+    const int64_t o = i * a.ld;
+    T xr[M], hr[M], pr[M], lh[M], lp[M];
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int e = t + 256 * j;
-      if (e >= lim) break;
-      const int row = e / ld;
-      const int c = e - row * ld;
-      if (c >= m) continue;
-      double p = 0.0, lp = 0.0, x = 0.0;
-      const int o = row * ld;
-      if (a.use_h)
-        for (int q = 0; q < a.na; ++q) {
-          const double y = sY[(a.offH + q) * kMaxNev + c];
-          p += double(lH[o + a.act[q]]) * y;
-          if (upd_lp) lp += double(lLH[o + a.act[q]]) * y;
-        }
-      if (a.use_p)
-        for (int q = 0; q < a.na; ++q) {
-          const double y = sY[(a.offP + q) * kMaxNev + c];
-          p += double(lP[o + a.act[q]]) * y;
-          if (upd_lp) lp += double(lLP[o + a.act[q]]) * y;
-        }
-      for (int k = 0; k < m; ++k) x += double(lX[o + k]) * sY[k * kMaxNev + c];
-      x += p;
-      X[base + e] = T(x);
-      if (write_p) {
-        P[base + e] = T(p);
-        if (upd_lp) LP[base + e] = T(lp);
-      }
+    for (int c = 0; c < M; ++c) xr[c] = X[o + c];
+    if (a.use_h) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) hr[c] = H[o + c];
+      if (lp_too)
+#pragma unroll
+        for (int c = 0; c < M; ++c) lh[c] = LH[o + c];
+    }
+    if (a.use_p) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) pr[c] = P[o + c];
+      if (lp_too)
+#pragma unroll
+        for (int c = 0; c < M; ++c) lp[c] = LP[o + c];
+    }
+    double p[M], l[M], x[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) p[c] = l[c] = x[c] = 0.0;
+    auto add = [&](const double *y, T v, T lv) {
+      const double vd = double(v), ld = double(lv);
+#pragma unroll
+      for (int c = 0; c < M; ++c) p[c] = fma(vd, y[c], p[c]);
+      if (lp_too)
+#pragma unroll
+        for (int c = 0; c < M; ++c) l[c] = fma(ld, y[c], l[c]);
+    };
+    if (a.use_h)
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (a.pos[k] >= 0) add(Y + (a.offH + a.pos[k]) * kMaxNev, hr[k], lp_too ? lh[k] : T(0));
+    if (a.use_p)
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (a.pos[k] >= 0) add(Y + (a.offP + a.pos[k]) * kMaxNev, pr[k], lp_too ? lp[k] : T(0));
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      const double v = double(xr[k]);
+#pragma unroll
+      for (int c = 0; c < M; ++c) x[c] = fma(v, Y[k * kMaxNev + c], x[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < M; ++c) X[o + c] = T(x[c] + p[c]);
+    if (write_p) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) P[o + c] = T(p[c]);
+      if (lp_too)
+#pragma unroll
+        for (int c = 0; c < M; ++c) LP[o + c] = T(l[c]);
     }
   }
 }
@@ -1037,31 +1021,48 @@ __device__ void sum_partials_block(const double *partials, int nblocks, int stri
   __syncthreads();
 }
 
+// Residuals rho from the norm partials, one lane per column, and the active
+// list; the whole status also goes to the host's copy (pinned, mapped), which
+// the host reads after the stream's synchronisation.
 __global__ __launch_bounds__(kSumThreads) void k_finalize(const double *partials, int nblocks,
                                                           int m, const double *theta,
                                                           double tol, int locking,
-                                                          DevStatus *st) {
+                                                          DevStatus *st, DevStatus *host) {
   __shared__ double sums[2 * kMaxNev];
+  __shared__ DevStatus now;
+  static_assert(sizeof(DevStatus) % 4 == 0 && sizeof(DevStatus) / 4 <= kSumThreads, "status words");
+  const int t = threadIdx.x;
+  constexpr int kWords = sizeof(DevStatus) / 4;
+  if (t < kWords) reinterpret_cast<int *>(&now)[t] = reinterpret_cast<const int *>(st)[t];
+  const int c = t < m ? t : 0;
+  const double th = theta[c], floor_th = m > 1 ? theta[1] : theta[0];
   sum_partials_block(partials, nblocks, kMaxNormBlocks, m, sums);
-  if (threadIdx.x == 0) {
-    double floor_th = m > 1 ? theta[1] : theta[0];
-    int nconv = 0, na = 0;
-    bool conv[kMaxNev];
-    for (int c = 0; c < m; ++c) {
-      double scale = fmax(theta[c], floor_th);
-      if (!(scale > 0.0)) scale = 1.0;
-      double rn = sqrt(sums[c]), xn = sqrt(sums[kMaxNev + c]);
-      double rho = xn > 0.0 ? rn / (scale * xn) : INFINITY;
-      st->rho[c] = rho;
-      st->theta[c] = theta[c];
-      conv[c] = rho <= tol;
-      nconv += conv[c] ? 1 : 0;
+  if (t < 64) {
+    double scale = fmax(th, floor_th);
+    if (!(scale > 0.0)) scale = 1.0;
+    const double rn = sqrt(sums[c]), xn = sqrt(sums[kMaxNev + c]);
+    const double rho = xn > 0.0 ? rn / (scale * xn) : INFINITY;
+    const bool conv = rho <= tol;
+    const int nconv = __popcll(__ballot(t < m && conv));
+    const bool act = t < m && (!conv || (!locking && nconv < m));
+    const unsigned long long who = __ballot(act);
+    if (t < m) {
+      now.rho[t] = rho;
+      now.theta[t] = th;
     }
-    for (int c = 0; c < m; ++c)
-      if (!conv[c] || (!locking && nconv < m)) st->act[na++] = c;
-    st->nact = na;
-    st->nconv = nconv;
+    if (act) now.act[__popcll(who & ((1ull << t) - 1ull))] = t;
+    if (t == 0) {
+      now.nact = __popcll(who);
+      now.nconv = nconv;
+    }
   }
+  __syncthreads();
+  if (t < kWords) {
+    const int v = reinterpret_cast<const int *>(&now)[t];
+    reinterpret_cast<int *>(st)[t] = v;
+    reinterpret_cast<int *>(host)[t] = v;
+  }
+  __threadfence_system();
 }
 
 __global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double *partials,
@@ -1094,14 +1095,15 @@ __device__ void colsum2(int c, double v1, double v2, int m, double *partials) {
 }
 
 // Rayleigh quotient partials: sum x.lx and sum b x^2 per column (blocks of
-// row stride ld; thread t takes column t % ld of rows t / ld).
+// row stride ld; thread t takes column t % lanes of rows t / lanes).
 template <typename T>
 __global__ __launch_bounds__(256) void k_rq(const T *X, const double *LX, int64_t n, int m,
-                                            int ld, const double *bdiag, double *partials) {
-  const int rc = 256 / ld;
-  const int row = threadIdx.x / ld;
-  const int c = threadIdx.x % ld;
-  const bool live = threadIdx.x < rc * ld && c < m;
+                                            int ld, int lanes, const double *bdiag,
+                                            double *partials) {
+  const int rc = 256 / lanes;
+  const int row = threadIdx.x / lanes;
+  const int c = threadIdx.x % lanes;
+  const bool live = threadIdx.x < rc * lanes && c < m;
   double a = 0.0, b = 0.0;
   if (live)
     for (int64_t r = (int64_t)blockIdx.x * rc + row; r < n; r += (int64_t)gridDim.x * rc) {
@@ -1116,12 +1118,12 @@ __global__ __launch_bounds__(256) void k_rq(const T *X, const double *LX, int64_
 // Residual partials: sum (lx - theta b x)^2 / b and sum b x^2 per column.
 template <typename T>
 __global__ __launch_bounds__(256) void k_res(const T *X, const double *LX, int64_t n, int m,
-                                             int ld, const double *bdiag, const double *theta,
-                                             double *partials) {
-  const int rc = 256 / ld;
-  const int row = threadIdx.x / ld;
-  const int c = threadIdx.x % ld;
-  const bool live = threadIdx.x < rc * ld && c < m;
+                                             int ld, int lanes, const double *bdiag,
+                                             const double *theta, double *partials) {
+  const int rc = 256 / lanes;
+  const int row = threadIdx.x / lanes;
+  const int c = threadIdx.x % lanes;
+  const bool live = threadIdx.x < rc * lanes && c < m;
   double a = 0.0, b = 0.0;
   if (live) {
     double th = theta[c];
@@ -1161,7 +1163,7 @@ __global__ __launch_bounds__(256) void k_colmax(const T *X, int64_t n, int m, do
   if (threadIdx.x < m) {
     double v = -1.0;
     int64_t ix = INT64_MAX;
-    for (int u = 0; u < (int)blockDim.x; ++u)
+    for (int u = threadIdx.x; u < rc * m; u += m)
       if (scol[u] == (int)threadIdx.x)
         if (sv[u] > v || (sv[u] == v && si[u] < ix)) { v = sv[u]; ix = si[u]; }
     pv[blockIdx.x * kMaxNev + threadIdx.x] = v;
@@ -1169,20 +1171,30 @@ __global__ __launch_bounds__(256) void k_colmax(const T *X, int64_t n, int m, do
   }
 }
 
+// one wavefront per column: lanes over the blocks' maxima, then a butterfly
+// (larger value, then lower index: the order does not matter)
 template <typename T>
-__global__ void k_colsign(const T *X, int m, int nblocks, const double *pv,
-                          const int64_t *pi, double *sign) {
-  int c = threadIdx.x;
-  if (c >= m) return;
+__global__ __launch_bounds__(64 * kMaxNev) void k_colsign(const T *X, int m, int nblocks,
+                                                          const double *pv, const int64_t *pi,
+                                                          double *sign) {
+  const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (c >= m) return;                   // uniform over the wave
   double v = -1.0;
   int64_t ix = INT64_MAX;
-  for (int b = 0; b < nblocks; ++b) {
-    double bv = pv[b * kMaxNev + c];
-    int64_t bi = pi[b * kMaxNev + c];
+  for (int b = lane; b < nblocks; b += 64) {
+    const double bv = pv[b * kMaxNev + c];
+    const int64_t bi = pi[b * kMaxNev + c];
     if (bv > v || (bv == v && bi < ix)) { v = bv; ix = bi; }
   }
-  double x = (ix == INT64_MAX) ? 1.0 : double(X[ix * m + c]);
-  sign[c] = x < 0 ? -1.0 : 1.0;
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double ov = __shfl_xor(v, off);
+    const int64_t oi = (int64_t)__shfl_xor((long long)ix, off);
+    if (ov > v || (ov == v && oi < ix)) { v = ov; ix = oi; }
+  }
+  if (lane == 0) {
+    const double x = (ix == INT64_MAX) ? 1.0 : double(X[ix * m + c]);
+    sign[c] = x < 0 ? -1.0 : 1.0;
+  }
 }
 
 struct Scales { double s[kMaxNev]; };
@@ -1298,39 +1310,47 @@ int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
   d.m = a.m;
   d.ld = a.ld;
   d.na = a.act.count;
-  for (int q = 0; q < kMaxNev; ++q) d.act[q] = q < d.na ? a.act.col[q] : 0;
+  for (int c = 0; c < kMaxNev; ++c) d.pos[c] = -1;
+  for (int q = 0; q < d.na; ++q) d.pos[a.act.col[q]] = q;
   d.use_h = a.use_h && d.na > 0;
   d.use_p = a.use_p && d.na > 0;
   d.offH = a.m;
   d.offP = a.m + (d.use_h ? d.na : 0);
   d.update_lp = LP != nullptr && (d.use_h || d.use_p);
-  // rows of whole load vectors (the solver pads every block to 16 bytes)
-  constexpr int E = UpdVec<T>::E;
-  if (a.ld % E != 0 || a.ld > 256 || a.m > a.ld) return SPHX_E_INVALID_ARG;
-  int rc = 256 * E / a.ld;
-  hipLaunchKernelGGL((k_update<T>), dim3(grid_for(a.n, rc, 8192)), dim3(256), 0, s, X, H, P,
-                     LH, LP, Y, d);
+  if (a.m < 1 || a.m > a.ld) return SPHX_E_INVALID_ARG;
+  const unsigned gb = grid_for(a.n, 256, 1 << 16);
+#define SPHX_UPD(M_)                                                                        \
+  case M_:                                                                                  \
+    hipLaunchKernelGGL((k_update<T, M_>), dim3(gb), dim3(256), 0, s, X, H, P, LH, LP, Y, d); \
+    break;
+  switch (a.m) {
+    SPHX_UPD(1) SPHX_UPD(2) SPHX_UPD(3) SPHX_UPD(4) SPHX_UPD(5) SPHX_UPD(6) SPHX_UPD(7)
+    SPHX_UPD(8) SPHX_UPD(9) SPHX_UPD(10) SPHX_UPD(11) SPHX_UPD(12) SPHX_UPD(13) SPHX_UPD(14)
+    SPHX_UPD(15) SPHX_UPD(16)
+    default: return SPHX_E_INVALID_ARG;
+  }
+#undef SPHX_UPD
   return hipGetLastError() == hipSuccess ? SPHX_OK : SPHX_E_HIP;
 }
 
 void launch_finalize(const double *norm_partials, int n_blocks, int m, const double *theta,
-                     double tol, int locking, DevStatus *st, hipStream_t s) {
+                     double tol, int locking, DevStatus *st, DevStatus *host, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kSumThreads), 0, s, norm_partials, n_blocks, m,
-                     theta, tol, locking, st);
+                     theta, tol, locking, st, host);
 }
 
 template <typename T>
-void launch_rq_partials(const T *X, const double *LX, int64_t n, int m, int ld,
+void launch_rq_partials(const T *X, const double *LX, int64_t n, int m, int ld, int lanes,
                         const double *bdiag, double *partials, int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL((k_rq<T>), dim3(nblocks), dim3(256), 0, s, X, LX, n, m, ld, bdiag,
-                     partials);
+  hipLaunchKernelGGL((k_rq<T>), dim3(nblocks), dim3(256), 0, s, X, LX, n, m, ld, lanes,
+                     bdiag, partials);
 }
 template <typename T>
-void launch_res_partials(const T *X, const double *LX, int64_t n, int m, int ld,
+void launch_res_partials(const T *X, const double *LX, int64_t n, int m, int ld, int lanes,
                          const double *bdiag, const double *theta, double *partials,
                          int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL((k_res<T>), dim3(nblocks), dim3(256), 0, s, X, LX, n, m, ld, bdiag, theta,
-                     partials);
+  hipLaunchKernelGGL((k_res<T>), dim3(nblocks), dim3(256), 0, s, X, LX, n, m, ld, lanes,
+                     bdiag, theta, partials);
 }
 void launch_sum_partials(const double *partials, int nblocks, int cols, double *out,
                          hipStream_t s) {
@@ -1351,7 +1371,7 @@ int normalize_columns(T *X, int64_t n, int m, const double *scale_host, void *sc
   double *sign = reinterpret_cast<double *>(pi + kColBlocks * kMaxNev);
   int nb = (int)grid_for(n, 256 / m, kColBlocks);
   hipLaunchKernelGGL((k_colmax<T>), dim3(nb), dim3(256), 0, s, X, n, m, pv, pi);
-  hipLaunchKernelGGL((k_colsign<T>), dim3(1), dim3(64), 0, s, X, m, nb, pv, pi, sign);
+  hipLaunchKernelGGL((k_colsign<T>), dim3(1), dim3(64 * kMaxNev), 0, s, X, m, nb, pv, pi, sign);
   Scales sc;
   for (int c = 0; c < kMaxNev; ++c) sc.s[c] = c < m ? scale_host[c] : 1.0;
   hipLaunchKernelGGL((k_colscale<T>), dim3(grid_for(n * m, 256, 4096)), dim3(256), 0, s, X, n,
@@ -1378,9 +1398,9 @@ void launch_copy_cols(const T *in, int ldin, T *out, int ldout, int64_t n, int m
                        const GramArgs &, double *, int, double *, hipStream_t);            \
   template int launch_update<T>(T *, const T *, T *, const T *, T *, const double *,      \
                                  const UpdateArgs &, hipStream_t);                         \
-  template void launch_rq_partials<T>(const T *, const double *, int64_t, int, int,        \
+  template void launch_rq_partials<T>(const T *, const double *, int64_t, int, int, int,   \
                                       const double *, double *, int, hipStream_t);         \
-  template void launch_res_partials<T>(const T *, const double *, int64_t, int, int,       \
+  template void launch_res_partials<T>(const T *, const double *, int64_t, int, int, int,  \
                                        const double *, const double *, double *, int,      \
                                        hipStream_t);                                       \
   template int normalize_columns<T>(T *, int64_t, int, const double *, void *, hipStream_t); \

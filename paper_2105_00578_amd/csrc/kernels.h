@@ -147,11 +147,22 @@ template <typename T>
 int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
               const ColMap &cm, EpiChebP<T> epi, hipStream_t s);
 
-// Padded blocks: n x ld with ld * sizeof(T) a multiple of 16 bytes (columns
-// m..ld-1 are padding).  Thread-per-row products with 16-byte vector loads.
+// Row width padded to whole 16-byte vectors.
 inline int padded_ld(int m, int elem_bytes) {
   const int e = 16 / elem_bytes;
   return (m + e - 1) / e * e;
+}
+
+// Row width of the solver's blocks of m columns.  Where rows have at most 12
+// neighbours (one lane per row) a solve is bound by the bytes of its blocks, so
+// they have exactly their columns (at least 2), except for FP32 rows of 5 and
+// 6 values, which would be read as three 8-byte vectors with two partial sums
+// instead of two 16-byte ones with four.  With more neighbours the gathers
+// decide, and rows off the 16-byte grid cost more of them than they save bytes
+// (27-point mesh, 5 FP64 columns: 26.0 instead of 22.9 us per product).
+inline int block_ld(int m, int elem_bytes, bool short_rows) {
+  if (!short_rows || (elem_bytes == 4 && (m == 5 || m == 6))) return padded_ld(m, elem_bytes);
+  return m < 2 ? 2 : m;
 }
 
 // Events that bracket the kernels of one product: a single launch is stamped
@@ -233,25 +244,26 @@ struct UpdateArgs {
   ColMap act;
   int use_h, use_p;
 };
-// SPHX_E_INVALID_ARG unless ld is at most 256, at least m and, for FP32, a
-// multiple of 4.  With LP non-null, LP is updated along with P from LH and
+// SPHX_E_INVALID_ARG unless 1 <= m <= ld.  With LP non-null, LP is updated along with P from LH and
 // LP (otherwise the caller forms L P by a product).
 template <typename T>
 int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
                   const UpdateArgs &a, hipStream_t s);
 
-// Reduce norm partials -> rho, convergence, active list (one workgroup).
+// Reduce norm partials -> rho, convergence, active list (one workgroup), in st
+// and in host (the device address of the host's pinned copy).
 void launch_finalize(const double *norm_partials, int n_blocks, int m,
                      const double *theta, double tol, int locking,
-                     DevStatus *st, hipStream_t s);
+                     DevStatus *st, DevStatus *host, hipStream_t s);
 
-// Rayleigh quotients / residual norms in FP64 of a final block.
+// Rayleigh quotients / residual norms in FP64 of a final block; `lanes` threads
+// per row (the order of the sums).
 template <typename T>
-void launch_rq_partials(const T *X, const double *LX, int64_t n, int m, int ld,
+void launch_rq_partials(const T *X, const double *LX, int64_t n, int m, int ld, int lanes,
                         const double *bdiag, double *partials, int nblocks,
                         hipStream_t s);
 template <typename T>
-void launch_res_partials(const T *X, const double *LX, int64_t n, int m, int ld,
+void launch_res_partials(const T *X, const double *LX, int64_t n, int m, int ld, int lanes,
                          const double *bdiag, const double *theta,
                          double *partials, int nblocks, hipStream_t s);
 // Sum partials[nblocks][2*kMaxNev] into out[2*kMaxNev] (fixed order).

@@ -187,10 +187,20 @@ struct VStore {
   }
 };
 
+// Norm epilogues: slot s = v E + e of the thread's sums is column v E + e, and
+// in the last vector column last + e, which the vector before holds already
+// where that is below (NV - 1) E (slot_column gives -1 then).
+template <int E, int NV>
+__device__ __forceinline__ int slot_column(int v, int e, int last) {
+  if (v < NV - 1) return v * E + e;
+  return last + e >= (NV - 1) * E ? last + e : -1;
+}
+
 template <typename T, int VB, int NV>
 struct VResidual {
   EpiResidualP<T> p;
   int m;
+  int last;
   bool store_lx = true;   // false: L X is already in p.LX (streaming pass)
   static constexpr bool kNorms = true;
   static constexpr bool kBoth = true;
@@ -202,33 +212,31 @@ struct VResidual {
     const double b = p.generalized ? di : 1.0;
     // one division per row for the B^-1-norm terms (exactly 1 when B = I)
     const double ib = p.generalized ? 1.0 / di : 1.0;
-    V *lx = reinterpret_cast<V *>(p.LX + i * p.ld);
-    V *out = reinterpret_cast<V *>(p.OUT + i * p.ld);
+    V o[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      V o;
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const int c = v * E + e;
+        const int c = v < NV - 1 ? v * E + e : last + e;
         const double x = double(xi[v][e]);
         const double th = c < m ? p.theta[c] : 0.0;
         const double r = double(acc[v][e]) - b * th * x;
-        o[e] = T(p.jacobi ? r / di : r);
-        if (c < m) {
-          n1[c] += r * r * ib;
-          n2[c] += b * x * x;
+        o[v][e] = T(p.jacobi ? r / di : r);
+        if (slot_column<E, NV>(v, e, last) >= 0 && c < m) {
+          n1[v * E + e] += r * r * ib;
+          n2[v * E + e] += b * x * x;
         }
       }
-      if (store_lx) lx[v] = acc[v];
-      out[v] = o;
-    }
+    if (store_lx) store_row<T, VB, NV>(p.LX + i * p.ld, last, acc);
+    store_row<T, VB, NV>(p.OUT + i * p.ld, last, o);
   }
 };
 
 template <typename T, int VB, int NV>
-struct VShiftDot {
+struct VShiftDot {     // padded blocks: vectors do not overlap
   EpiShiftDotP<T> p;
   int m;
+  int last;
   static constexpr bool kNorms = true;
   static constexpr bool kBoth = false;
   using V = typename Vec<T, VB>::type;
@@ -322,24 +330,27 @@ struct VPoly {
 // Per-column block sums of the thread norms (columns < m), fixed order:
 // butterfly within each wavefront, then the 4 wavefronts in order.
 // kBoth false: only the first of the two sums is wanted and stored.
-template <int LD, bool kBoth>
-__device__ void block_norms(const double (&n1)[LD], const double (&n2)[LD], int m,
-                            double *partials, int slot) {
+template <int E, int NV, bool kBoth>
+__device__ void block_norms(const double (&n1)[E * NV], const double (&n2)[E * NV], int last,
+                            int m, double *partials, int slot) {
   __shared__ double sh[4][2 * kMaxNev];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int c = 0; c < LD; ++c) {
-    if (c >= m) break;
-    double a = n1[c], b = n2[c];
-    for (int off = 32; off >= 1; off >>= 1) {
-      a += __shfl_xor(a, off);
-      if constexpr (kBoth) b += __shfl_xor(b, off);
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int c = slot_column<E, NV>(v, e, last);
+      if (c < 0 || c >= m) continue;    // uniform
+      double a = n1[v * E + e], b = n2[v * E + e];
+      for (int off = 32; off >= 1; off >>= 1) {
+        a += __shfl_xor(a, off);
+        if constexpr (kBoth) b += __shfl_xor(b, off);
+      }
+      if (lane == 0) {
+        sh[wave][c] = a;
+        if constexpr (kBoth) sh[wave][kMaxNev + c] = b;
+      }
     }
-    if (lane == 0) {
-      sh[wave][c] = a;
-      if constexpr (kBoth) sh[wave][kMaxNev + c] = b;
-    }
-  }
   __syncthreads();
   const int t = threadIdx.x;
   if (t < m) {
@@ -375,7 +386,7 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, int64_t nrows,
     epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms)
-    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)blockIdx.x);
+    block_norms<Vec<T, VB>::E, NV, Epi::kBoth>(n1, n2, ld - Vec<T, VB>::E, m, partials, (int)blockIdx.x);
 }
 
 template <typename T, int VB, int NV, int G>
@@ -422,7 +433,7 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A, int64_t nrows,
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms)
-    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)blockIdx.x);
+    block_norms<Vec<T, VB>::E, NV, Epi::kBoth>(n1, n2, ld - Vec<T, VB>::E, m, partials, (int)blockIdx.x);
 }
 
 // Rows of 13..48 neighbours in natural order (mesh-like graphs), G lanes per
@@ -569,7 +580,7 @@ __global__ __launch_bounds__(256) void k_vbin(Csr<IdxT, WT> A, BinRows B,
     bin_rows<T, VB, NV, 1>(A, B.rows[0], B.nrows[0], b - B.end[3], B.end[4] - B.end[3], Xs, ld,
                            epi, n1, n2);
   if constexpr (Epi::kNorms)
-    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, (int)(b - B.end[0]));
+    block_norms<Vec<T, VB>::E, NV, Epi::kBoth>(n1, n2, ld - Vec<T, VB>::E, m, partials, (int)(b - B.end[0]));
 }
 
 // Hub rows: one wavefront per hub row, lanes over its chunks, combined by a
@@ -603,7 +614,7 @@ __global__ __launch_bounds__(256) void k_vhub_combine(BinRows B, const T *__rest
     if (lane == 0) epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms)
-    block_norms<LD, Epi::kBoth>(n1, n2, m, partials, slot0 + (int)blockIdx.x);
+    block_norms<Vec<T, VB>::E, NV, Epi::kBoth>(n1, n2, ld - Vec<T, VB>::E, m, partials, slot0 + (int)blockIdx.x);
 }
 
 // The residual epilogue as a streaming pass over an L X that a store product
@@ -615,9 +626,7 @@ __global__ __launch_bounds__(256) void k_resid_rows(int64_t n, const T *__restri
                                                     double *partials, int m) {
   using V = typename Vec<T, VB>::type;
   constexpr int LD = NV * Vec<T, VB>::E;
-  const V *X = reinterpret_cast<const V *>(Xs);
-  const V *LXv = reinterpret_cast<const V *>(epi.p.LX);
-  const int ldv = epi.p.ld / Vec<T, VB>::E;
+  const int ld = epi.p.ld;
   double n1[LD], n2[LD];
 #pragma unroll
   for (int c = 0; c < LD; ++c) { n1[c] = 0.0; n2[c] = 0.0; }
@@ -625,14 +634,41 @@ __global__ __launch_bounds__(256) void k_resid_rows(int64_t n, const T *__restri
     const int64_t i = ((int64_t)blockIdx.x * rpt + q) * 256 + threadIdx.x;
     if (i >= n) break;
     V xi[NV], acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      xi[v] = X[i * ldv + v];
-      acc[v] = LXv[i * ldv + v];
-    }
+    load_row<T, VB, NV>(Xs + i * ld, epi.last, xi);
+    load_row<T, VB, NV>(epi.p.LX + i * ld, epi.last, acc);
     epi.row(i, xi, acc, n1, n2);
   }
-  block_norms<LD, true>(n1, n2, m, partials, (int)blockIdx.x);
+  block_norms<Vec<T, VB>::E, NV, true>(n1, n2, epi.last, m, partials, (int)blockIdx.x);
+}
+
+// go(VB, NV) for the vectors of a row of ld values.  FP32 rows of 2, 3, 5, 6,
+// 10 or 14 values: 8-byte vectors (no 16-byte vector fits, or 8-byte ones
+// fetch less than overlapping 16-byte ones).
+template <typename T, typename F>
+int with_vectors(int ld, F &&go) {
+#define SPHX_NV(VB_, NV_) \
+  case NV_: return go(std::integral_constant<int, VB_>{}, std::integral_constant<int, NV_>{});
+  if constexpr (std::is_same_v<T, float>) {
+    if (ld == 3 || ld == 5 || ld % 4 == 2) {
+      switch ((ld + 1) / 2) {
+        SPHX_NV(8, 1) SPHX_NV(8, 2) SPHX_NV(8, 3) SPHX_NV(8, 5) SPHX_NV(8, 7)
+        default: return SPHX_E_INVALID_ARG;
+      }
+    }
+  }
+  constexpr int E = 16 / (int)sizeof(T);
+  switch ((ld + E - 1) / E) {
+    SPHX_NV(16, 1) SPHX_NV(16, 2) SPHX_NV(16, 3) SPHX_NV(16, 4)
+    default: break;
+  }
+  if constexpr (std::is_same_v<T, double>) {
+    switch ((ld + E - 1) / E) {
+      SPHX_NV(16, 5) SPHX_NV(16, 6) SPHX_NV(16, 7) SPHX_NV(16, 8)
+      default: break;
+    }
+  }
+#undef SPHX_NV
+  return SPHX_E_INVALID_ARG;
 }
 
 template <typename T>
@@ -641,30 +677,17 @@ int resid_stream(int64_t n, const T *X, int ld, int m, const EpiResidualP<T> &p,
   const int64_t nb0 = ceil_div(n, 256);
   const int rpt = (int)ceil_div(nb0, kMaxNormBlocks);
   const unsigned nb = (unsigned)ceil_div(n, 256 * (int64_t)rpt);
-  const int row_bytes = ld * (int)sizeof(T);
-  if (row_bytes % 16) return SPHX_E_INVALID_ARG;
-#define SPHX_RS(NV_)                                                                        \
-  case NV_: {                                                                               \
-    VResidual<T, 16, NV_> e{p};                                                             \
-    e.m = m;                                                                                \
-    e.store_lx = false;                                                                     \
-    hipLaunchKernelGGL((k_resid_rows<T, 16, NV_>), dim3(nb), dim3(256), 0, s, n, X, e, rpt, \
-                       partials, m);                                                        \
-    break;                                                                                  \
-  }
-  switch (row_bytes / 16) {
-    SPHX_RS(1) SPHX_RS(2) SPHX_RS(3) SPHX_RS(4)
-    default:
-      if constexpr (std::is_same_v<T, double>) {
-        switch (row_bytes / 16) {
-          SPHX_RS(5) SPHX_RS(6) SPHX_RS(7) SPHX_RS(8)
-          default: return SPHX_E_INVALID_ARG;
-        }
-      } else {
-        return SPHX_E_INVALID_ARG;
-      }
-  }
-#undef SPHX_RS
+  const int r = with_vectors<T>(ld, [&](auto vb, auto nv) -> int {
+    constexpr int VB = decltype(vb)::value, NV = decltype(nv)::value;
+    VResidual<T, VB, NV> e{p};
+    e.m = m;
+    e.last = ld - Vec<T, VB>::E;
+    e.store_lx = false;
+    hipLaunchKernelGGL((k_resid_rows<T, VB, NV>), dim3(nb), dim3(256), 0, s, n, X, e, rpt,
+                       partials, m);
+    return SPHX_OK;
+  });
+  if (r != SPHX_OK) return r;
   if (nparts) *nparts = (int)nb;
   return hipGetLastError() == hipSuccess ? SPHX_OK : SPHX_E_HIP;
 }
@@ -779,7 +802,7 @@ int dispatch_types(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, cons
     else col = g->col;
     Csr<IdxT, WT> A{static_cast<const IdxT *>(g->rowptr), col, static_cast<const WT *>(g->w)};
     EpiT<T, VB, NV> epi{p};
-    if constexpr (!EpiT<T, VB, NV>::kNorms) epi.last = ld - Vec<T, VB>::E;
+    epi.last = ld - Vec<T, VB>::E;
     if constexpr (std::is_same_v<EpiT<T, VB, NV>, VResidual<T, VB, NV>> ||
                   std::is_same_v<EpiT<T, VB, NV>, VShiftDot<T, VB, NV>>)
       epi.m = m;
@@ -803,34 +826,13 @@ int dispatch_nv(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, const P
                 double *partials, int *nparts, hipStream_t s,
                 const LaunchEvents *ev = nullptr) {
   if (ld < m || ld > kMaxNev || ld < 2) return SPHX_E_INVALID_ARG;
-#define SPHX_NV(VB_, NV_)                                                                 \
-  case NV_:                                                                               \
-    return dispatch_types<T, VB_, NV_, EpiT>(g, plan, X, ld, p, m, partials, nparts, s, ev);
-  if constexpr (EpiT<T, 16, 1>::kNorms)   // padded blocks only
+  // the shifted product's blocks are padded
+  if constexpr (std::is_same_v<EpiT<T, 16, 1>, VShiftDot<T, 16, 1>>)
     if ((ld * (int)sizeof(T)) % 16) return SPHX_E_INVALID_ARG;
-  // FP32 rows of 2, 3, 5, 6, 10 or 14 values: 8-byte vectors (no 16-byte
-  // vector fits, or 8-byte ones fetch less than overlapping 16-byte ones)
-  if constexpr (std::is_same_v<T, float>) {
-    if (ld == 3 || ld == 5 || ld % 4 == 2) {
-      switch ((ld + 1) / 2) {
-        SPHX_NV(8, 1) SPHX_NV(8, 2) SPHX_NV(8, 3) SPHX_NV(8, 5) SPHX_NV(8, 7)
-        default: return SPHX_E_INVALID_ARG;
-      }
-    }
-  }
-  constexpr int E = 16 / (int)sizeof(T);
-  switch ((ld + E - 1) / E) {
-    SPHX_NV(16, 1) SPHX_NV(16, 2) SPHX_NV(16, 3) SPHX_NV(16, 4)
-    default: break;
-  }
-  if constexpr (std::is_same_v<T, double>) {
-    switch ((ld + E - 1) / E) {
-      SPHX_NV(16, 5) SPHX_NV(16, 6) SPHX_NV(16, 7) SPHX_NV(16, 8)
-      default: break;
-    }
-  }
-#undef SPHX_NV
-  return SPHX_E_INVALID_ARG;
+  return with_vectors<T>(ld, [&](auto vb, auto nv) -> int {
+    return dispatch_types<T, decltype(vb)::value, decltype(nv)::value, EpiT>(
+        g, plan, X, ld, p, m, partials, nparts, s, ev);
+  });
 }
 
 }  // namespace
@@ -844,7 +846,7 @@ template <typename T>
 int vspmm_residual(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, int m,
                    EpiResidualP<T> epi, double *norm_partials, int *n_norm_blocks,
                    hipStream_t s) {
-  if (!plan.binned && plan.group > 1 && (ld * (int)sizeof(T)) % 16 == 0) {
+  if (!plan.binned && plan.group > 1) {
     // 13..48-neighbour meshes: the LDS-staged store product writes L X, then
     // a streaming pass forms the residual, the Jacobi step and the norms
     // (the fused residual epilogue keeps per-lane index reads and ran at
