@@ -437,28 +437,42 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A, int64_t nrows,
 }
 
 // Rows of 13..48 neighbours in natural order (mesh-like graphs), G lanes per
-// row, with the column indices (and weights) staged in LDS: the block takes
-// its rows in chunks of 256 / G consecutive rows, whose CSR entries form one
-// contiguous run; the block loads that run with coalesced loads (adjacent
-// threads, adjacent entries) into LDS, and the groups then walk their rows
-// from LDS.  Read per lane from global memory instead, the index and weight
-// lines of all resident waves exceed the L2 and are fetched again (measured:
-// about twice the algorithmic bytes on the weighted 27-point mesh).  A chunk
-// with more than kLdsEntries entries is read from global memory.  Blocks take
-// contiguous chunk ranges, remapped per XCD as above.  The summation order is
-// the same as k_vgroup's.
-constexpr int kLdsEntries = 4096;
+// row, with the column indices (and weights) staged in LDS: a block takes
+// chunks of kLdsThreads / G consecutive rows (one, up to 2^20 chunks), whose
+// CSR entries form one contiguous run; it loads that run with coalesced loads
+// (adjacent threads, adjacent entries) into LDS, and the groups then walk their
+// rows from LDS.  Read per lane from global memory instead, the index and
+// weight lines of all resident waves exceed the L2 and are fetched again
+// (measured: about twice the algorithmic bytes on the weighted 27-point mesh).
+// A chunk with more than cap entries (those of rows of the graph's largest
+// degree, at most kLdsEntries) is read from global memory.
+// Chunks are remapped per XCD as above.  The summation order is the same as
+// k_vgroup's.
+//
+// Bound by the latency of the two steps, so what counts is how much is in
+// flight: a thread loads kLdsLoads entries before it stores the first (one
+// load at a time left 13 waits in a row: 66.9 us per Chebyshev step of 5 FP64
+// columns on the weighted 27-point mesh of 512,000 rows, now 54.5), the arrays
+// have the length that the graph's rows need (26 neighbours: four waves per
+// SIMD beside FP64 weights, 52.6), and blocks are two waves instead of four
+// (51.5, that is 4.8 TB/s; the mesh of 216,000 rows: 22.9 -> 20.1).  More gathers in flight
+// per lane cost registers and measured no better.
+constexpr int kLdsThreads = 128;
+constexpr int kLdsEntries = 16 * kLdsThreads;
+constexpr int kLdsBlocks = 1 << 20;
+constexpr int kLdsLoads = 7;
 
 template <typename T, int VB, int NV, int G, typename IdxT, typename WT, typename Epi>
-__global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
-                                              const T *__restrict__ Xs, int ld, int64_t rpb,
-                                              Epi epi) {
+__global__ __launch_bounds__(kLdsThreads) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
+                                                      const T *__restrict__ Xs, int ld,
+                                                      int64_t rpb, int cap, Epi epi) {
   static_assert(!Epi::kNorms, "the epilogue takes no norms");
   using V = typename Vec<T, VB>::type;
   using L = LdsCsr<WT>;
-  constexpr int R = 256 / G;   // rows per chunk
-  __shared__ typename L::CT scol[kLdsEntries];
-  __shared__ typename L::WS sw[kUnitW<WT> ? 1 : kLdsEntries];
+  constexpr int R = kLdsThreads / G;   // rows per chunk
+  extern __shared__ double lds_entries[];     // cap weights (none of a unit graph), cap columns
+  auto *sw = reinterpret_cast<typename L::WS *>(lds_entries);
+  auto *scol = reinterpret_cast<typename L::CT *>(sw + (kUnitW<WT> ? 0 : cap));
   const int last = ld - Vec<T, VB>::E;
   const int gl = threadIdx.x & (G - 1);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
@@ -466,11 +480,24 @@ __global__ __launch_bounds__(256) void k_vlds(Csr<IdxT, WT> A, int64_t nrows,
   for (int64_t r0 = b * rpb; r0 < rend; r0 += R) {
     const int64_t r1 = min(rend, r0 + (int64_t)R);
     const int64_t k0 = A.rp[r0], k1 = A.rp[r1];
-    const bool staged = k1 - k0 <= kLdsEntries;
+    const bool staged = k1 - k0 <= cap;
     if (staged) {
-      for (int64_t k = k0 + threadIdx.x; k < k1; k += 256) {
-        scol[k - k0] = A.col[k];
-        if constexpr (!kUnitW<WT>) sw[k - k0] = A.w[k];
+      for (int64_t kb = k0; kb < k1; kb += kLdsThreads * kLdsLoads) {
+        typename L::CT c[kLdsLoads];
+        typename L::WS w[kUnitW<WT> ? 1 : kLdsLoads];
+#pragma unroll
+        for (int u = 0; u < kLdsLoads; ++u) {
+          const int64_t k = min(kb + kLdsThreads * u + (int64_t)threadIdx.x, k1 - 1);
+          c[u] = A.col[k];
+          if constexpr (!kUnitW<WT>) w[u] = A.w[k];
+        }
+#pragma unroll
+        for (int u = 0; u < kLdsLoads; ++u) {
+          const int64_t k = kb + kLdsThreads * u + (int64_t)threadIdx.x;
+          if (k >= k1) continue;
+          scol[k - k0] = c[u];
+          if constexpr (!kUnitW<WT>) sw[k - k0] = w[u];
+        }
       }
     }
     __syncthreads();
@@ -702,7 +729,7 @@ static_assert(kMaxShortBlocks <= kMaxNormBlocks && kGroupBlocks <= kMaxNormBlock
               "norm partial slots");
 
 template <typename T, int VB, int NV, typename IdxT, typename WT, typename Epi>
-void run_vec(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X, int ld,
+void run_vec(const Csr<IdxT, WT> &A, int64_t n, int64_t max_deg, const SpmmPlan &plan, const T *X, int ld,
              const Epi &epi, double *partials, int *nparts, int m, hipStream_t s,
              const LaunchEvents *ev) {
   // Every launch writes one norm-partial slot per block: the grids below
@@ -736,13 +763,14 @@ void run_vec(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X
     if (G == 1) {
       short_rows(n);
     } else {
-      const unsigned gb = ranges(G, n, rpb);
       // the LDS-staged index stream pays off for the light epilogues (store,
       // polynomial steps: 8..20 % faster on the weighted 27-point mesh); with
       // the residual epilogue's per-thread norm sums the extra LDS costs more
       // occupancy than it saves (measured 11..30 % slower), so that one reads
       // its indices per lane
       if constexpr (Epi::kNorms) {
+        const unsigned gb = ranges(G, n, rpb);
+        used += (int)gb;
         if (G == 2)
           hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
                                 s, e0, e1, 0, A, n, X, ld, rpb, epi, partials, m);
@@ -750,14 +778,20 @@ void run_vec(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X
           hipExtLaunchKernelGGL((k_vgroup<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0,
                                 s, e0, e1, 0, A, n, X, ld, rpb, epi, partials, m);
       } else {
+        using L = LdsCsr<WT>;
+        const int64_t rows = kLdsThreads / G;   // of a chunk
+        rpb = ceil_div(ceil_div(n, rows), kLdsBlocks) * rows;
+        const unsigned lb = (unsigned)ceil_div(n, rpb);
+        const int cap = (int)std::min<int64_t>(max_deg * rows, kLdsEntries);
+        const unsigned lds = (unsigned)cap * (sizeof(typename L::CT) +
+                                              (kUnitW<WT> ? 0 : sizeof(typename L::WS)));
         if (G == 2)
-          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 2, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                                e0, e1, 0, A, n, X, ld, rpb, epi);
+          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 2, IdxT, WT, Epi>), dim3(lb),
+                                dim3(kLdsThreads), lds, s, e0, e1, 0, A, n, X, ld, rpb, cap, epi);
         else
-          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 4, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                                e0, e1, 0, A, n, X, ld, rpb, epi);
+          hipExtLaunchKernelGGL((k_vlds<T, VB, NV, 4, IdxT, WT, Epi>), dim3(lb),
+                                dim3(kLdsThreads), lds, s, e0, e1, 0, A, n, X, ld, rpb, cap, epi);
       }
-      used += (int)gb;
     }
   } else if constexpr (!std::is_same_v<WT, UnitD16>) {   // (offsets: unbinned plans only)
     BinRows B{};
@@ -806,7 +840,7 @@ int dispatch_types(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, cons
     if constexpr (std::is_same_v<EpiT<T, VB, NV>, VResidual<T, VB, NV>> ||
                   std::is_same_v<EpiT<T, VB, NV>, VShiftDot<T, VB, NV>>)
       epi.m = m;
-    run_vec<T, VB, NV>(A, g->n, plan, X, ld, epi, partials, nparts, m, s, ev);
+    run_vec<T, VB, NV>(A, g->n, g->stats_valid ? g->max_deg : kUnbinnedMaxDeg, plan, X, ld, epi, partials, nparts, m, s, ev);
   };
   if (g->rp64) {
     if (g->wdt == SPHX_UNIT) go(int64_t{}, Unit{});

@@ -83,11 +83,17 @@ def _graph_of(kind):
                                                                          dtype=np.float64))
     if kind == "rmat":            # every degree class
         return graphgen.rmat_graph(11, seed=2, weight_seed=3, weight_dtype=np.float64)
+    if kind.startswith("ring"):   # n vertices, d neighbours each: staged chunks of 64 rows
+        n, d = map(int, kind[4:].split("x"))
+        u = np.repeat(np.arange(n), d // 2)
+        v = (u + np.tile(np.arange(1, d // 2 + 1), n)) % n
+        return graphgen.csr_from_edges(n, u, v, graphgen.uniform_weights(u.size, 4))
     return star_graph(17000)      # a hub row in chunks
 
 
 @pytest.mark.parametrize("m", range(1, 17))
-@pytest.mark.parametrize("kind", ["grid", "brick", "rmat", "hub"])
+@pytest.mark.parametrize("kind", ["grid", "brick", "rmat", "hub", "ring127x26", "ring64x32",
+                                  "ring129x34", "ring97x48"])
 def test_products_every_width(handle, kind, m):
     """Every block width on every row class, from a base that is only aligned
     to its elements: L X, five Chebyshev steps (also in place) and the GMRES
