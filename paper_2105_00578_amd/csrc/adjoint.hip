@@ -594,7 +594,6 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
   double *Mdev2 = a.take<double>(kMaxNev * kMaxNev);
   CgState *st = a.take<CgState>(2);        // the state before and after a step
   CgAlpha *alpha = a.take<CgAlpha>(1);
-  (void)Mdev2;
   const int64_t rpb = ceil_div(n, kSmallBlocks);
   const int nsb = (int)ceil_div(n, rpb);
   const unsigned gew = grid_for((int64_t)blkp, 256, 4096);

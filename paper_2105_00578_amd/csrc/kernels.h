@@ -140,10 +140,6 @@ template <typename T>
 int spmm_store(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
                const ColMap &cm, EpiStoreP<T> epi, hipStream_t s);
 template <typename T>
-int spmm_residual(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
-                  const ColMap &cm, EpiResidualP<T> epi, double *norm_partials,
-                  int *n_norm_blocks, hipStream_t s);
-template <typename T>
 int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
               const ColMap &cm, EpiChebP<T> epi, hipStream_t s);
 

@@ -1,5 +1,6 @@
 // Laplacian block product Y = L_C X for a CSR graph (Eq. 2 with weights),
-// summed per row in difference form y_i = sum_j w_ij (x_i - x_j).
+// summed per row in difference form y_i = sum_j w_ij (x_i - x_j): the products
+// of a single column (wider blocks take the vector-row kernels).
 //
 // Layout: X and Y are row-major n x ld blocks.  The kernels use a
 // column-lane mapping: a group of G lanes serves one row, lane c owning
@@ -16,10 +17,6 @@
 //
 // Epilogues fused into the product:
 //   Store     y = acc
-//   Residual  LX = acc; r = acc - b_i theta_c x_i (b_i = d_i for the
-//             generalized problem, else 1); writes r or the Jacobi step
-//             r / d_i (Sec. 5.1); accumulates ||r||^2_{B^-1} and ||x||^2_B per
-//             column in FP64 (per-block partials).
 //   Cheb      one step of the Chebyshev iteration for L h = r (Sec. 5.2):
 //             out = xs + alpha (xs - prev) + beta s_i (r - L xs), xs = scale x,
 //             s_i = 1 or 1/d_i (generalized).
@@ -75,37 +72,15 @@ __device__ __forceinline__ T row_acc(const Csr<IdxT, WT> &A, int64_t k0,
 template <typename T>
 struct EpiStore {
   EpiStoreP<T> p;
-  static constexpr bool kNorms = false;
-  __device__ void operator()(int64_t i, int c, int col, T xi, T acc, double &,
-                             double &) const {
+  __device__ void operator()(int64_t i, int col, T xi, T acc) const {
     p.Y[i * p.ldy + col] = acc;
-  }
-};
-
-template <typename T>
-struct EpiResidual {
-  EpiResidualP<T> p;
-  static constexpr bool kNorms = true;
-  __device__ void operator()(int64_t i, int c, int col, T xi, T acc, double &n1,
-                             double &n2) const {
-    int64_t o = i * p.ld + col;
-    p.LX[o] = acc;
-    double di = p.d64 ? p.d64[i] : 1.0;
-    double b = p.generalized ? di : 1.0;
-    double x = double(xi);
-    double r = double(acc) - b * p.theta[col] * x;
-    p.OUT[o] = T(p.jacobi ? r / di : r);
-    n1 += r * r / b;
-    n2 += b * x * x;
   }
 };
 
 template <typename T>
 struct EpiCheb {
   EpiChebP<T> p;
-  static constexpr bool kNorms = false;
-  __device__ void operator()(int64_t i, int c, int col, T xi, T acc, double &,
-                             double &) const {
+  __device__ void operator()(int64_t i, int col, T xi, T acc) const {
     int64_t o = i * p.ld + col;
     double xs = p.src_scale * double(xi);
     double pv = p.prev ? p.prev_scale * double(p.prev[o]) : 0.0;
@@ -115,37 +90,11 @@ struct EpiCheb {
   }
 };
 
-// Per-column block sums of (v1, v2) in a fixed order, stored sum-major:
-// partials[q * kMaxNormBlocks + slot], q = column (v1) or kMaxNev + column
-// (v2).  Every thread of the block must call this.  c < 0 marks a lane
-// without a column.
-__device__ void block_colsum(int c, double v1, double v2, int G, double *partials,
-                             int slot) {
-  __shared__ double s1[256], s2[256];
-  __shared__ int sc[256];
-  int t = threadIdx.x;
-  s1[t] = v1;
-  s2[t] = v2;
-  sc[t] = c;
-  __syncthreads();
-  if (t < G) {
-    double a = 0.0, b = 0.0;
-    for (int u = 0; u < (int)blockDim.x; ++u)
-      if (sc[u] == t) {
-        a += s1[u];
-        b += s2[u];
-      }
-    partials[(int64_t)t * kMaxNormBlocks + slot] = a;
-    partials[(int64_t)(kMaxNev + t) * kMaxNormBlocks + slot] = b;
-  }
-}
-
 // ---------------------------------------------------------------- kernels
 template <typename T, typename IdxT, typename WT, typename Epi>
 __global__ __launch_bounds__(256) void k_spmm_group(
     Csr<IdxT, WT> A, const int32_t *__restrict__ rows, int64_t nrows,
-    const T *__restrict__ X, int ldx, ColMap cm, Epi epi, double *partials,
-    int slot0) {
+    const T *__restrict__ X, int ldx, ColMap cm, Epi epi) {
   const int G = cm.count;
   const int gpw = kWave / G;
   const int lane = threadIdx.x & (kWave - 1);
@@ -154,7 +103,6 @@ __global__ __launch_bounds__(256) void k_spmm_group(
   const int c = lane - g * G;
   const bool ok = g < gpw;
   const int col = ok ? cm.col[c] : 0;
-  double n1 = 0.0, n2 = 0.0;
   const int64_t per_block = (int64_t)(blockDim.x / kWave) * gpw;
   if (ok) {
     for (int64_t r = (int64_t)blockIdx.x * per_block + wave * gpw + g; r < nrows;
@@ -162,11 +110,9 @@ __global__ __launch_bounds__(256) void k_spmm_group(
       int64_t i = rows ? rows[r] : r;
       T xi = X[i * ldx + col];
       T acc = row_acc<T>(A, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, X, ldx, col, xi);
-      epi(i, c, col, xi, acc, n1, n2);
+      epi(i, col, xi, acc);
     }
   }
-  if constexpr (Epi::kNorms)
-    block_colsum(ok ? c : -1, n1, n2, G, partials, slot0 + (int)blockIdx.x);
 }
 
 // Sum lane values of all groups for column c (result valid in lanes < G).
@@ -185,8 +131,7 @@ __device__ __forceinline__ T group_reduce(T v, int G, int lane) {
 template <typename T, typename IdxT, typename WT, typename Epi>
 __global__ __launch_bounds__(256) void k_spmm_wave(
     Csr<IdxT, WT> A, const int32_t *__restrict__ rows, int64_t nrows,
-    const T *__restrict__ X, int ldx, ColMap cm, Epi epi, double *partials,
-    int slot0) {
+    const T *__restrict__ X, int ldx, ColMap cm, Epi epi) {
   const int G = cm.count;
   const int ng = kWave / G;
   const int lane = threadIdx.x & (kWave - 1);
@@ -196,7 +141,6 @@ __global__ __launch_bounds__(256) void k_spmm_wave(
   const bool ok = g < ng;
   const int col = cm.col[c];
   const int wpb = blockDim.x / kWave;
-  double n1 = 0.0, n2 = 0.0;
   for (int64_t r = (int64_t)blockIdx.x * wpb + wave; r < nrows;
        r += (int64_t)gridDim.x * wpb) {
     int64_t i = rows[r];
@@ -205,17 +149,16 @@ __global__ __launch_bounds__(256) void k_spmm_wave(
     if (ok)
       acc = row_acc<T>(A, (int64_t)A.rp[i] + g, (int64_t)A.rp[i + 1], ng, X, ldx, col, xi);
     T tot = group_reduce(acc, G, lane);
-    if (lane < G) epi(i, c, col, xi, tot, n1, n2);
+    if (lane < G) epi(i, col, xi, tot);
   }
-  if constexpr (Epi::kNorms)
-    block_colsum(lane < G ? c : -1, n1, n2, G, partials, slot0 + (int)blockIdx.x);
 }
 
 template <typename T, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_spmm_hub_partial(
     Csr<IdxT, WT> A, const int32_t *__restrict__ hub_rows,
     const int32_t *__restrict__ hub_chunk_begin, int64_t n_hub,
-    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s, const T *__restrict__ X, int ldx, ColMap cm, double *out) {
+    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s,
+    const T *__restrict__ X, int ldx, ColMap cm, double *out) {
   const int G = cm.count;
   const int ng = kWave / G;
   const int lane = threadIdx.x & (kWave - 1);
@@ -246,12 +189,11 @@ template <typename T, typename Epi>
 __global__ __launch_bounds__(256) void k_spmm_hub_combine(
     const int32_t *__restrict__ hub_rows, const int32_t *__restrict__ hub_chunk_begin,
     int64_t n_hub, const double *__restrict__ part, const T *__restrict__ X,
-    int ldx, ColMap cm, Epi epi, double *partials, int slot0) {
+    int ldx, ColMap cm, Epi epi) {
   const int G = cm.count;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int wpb = blockDim.x / kWave;
-  double n1 = 0.0, n2 = 0.0;
   const int c = lane;
   for (int64_t h = (int64_t)blockIdx.x * wpb + wave; h < n_hub;
        h += (int64_t)gridDim.x * wpb) {
@@ -262,11 +204,9 @@ __global__ __launch_bounds__(256) void k_spmm_hub_combine(
       T tot = T(0);
       for (int64_t q = hub_chunk_begin[h]; q < hub_chunk_begin[h + 1]; ++q)
         tot += T(part[q * kMaxNev + c]);
-      epi(i, c, col, xi, tot, n1, n2);
+      epi(i, col, xi, tot);
     }
   }
-  if constexpr (Epi::kNorms)
-    block_colsum(c < G ? c : -1, n1, n2, G, partials, slot0 + (int)blockIdx.x);
 }
 
 // --------------------------------------------------------------- dispatch
@@ -276,20 +216,13 @@ constexpr int kHubBlocks = 64;
 
 template <typename T, typename IdxT, typename WT, typename Epi>
 void run_all(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan,
-             const T *X, int ldx, const ColMap &cm, const Epi &epi,
-             double *partials, int *nparts, hipStream_t s) {
+             const T *X, int ldx, const ColMap &cm, const Epi &epi, hipStream_t s) {
   const int G = cm.count;
   const int gpw = kWave / G;
-  int used = 0;
-  auto slot = [&](int blocks) {
-    int b = used;
-    used += blocks;
-    return b;
-  };
   if (!plan.binned) {
     unsigned gb = grid_for(n, 4 * gpw, kGroupBlocks);
     hipLaunchKernelGGL((k_spmm_group<T, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                       A, (const int32_t *)nullptr, n, X, ldx, cm, epi, partials, slot(gb));
+                       A, (const int32_t *)nullptr, n, X, ldx, cm, epi);
   } else {
     // rows of the first kNumBins - 1 classes: one lane group per row; the
     // last class: one wavefront per row
@@ -297,13 +230,12 @@ void run_all(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan,
       if (plan.nrows[c] == 0) continue;
       unsigned gb = grid_for(plan.nrows[c], 4 * gpw, kGroupBlocks);
       hipLaunchKernelGGL((k_spmm_group<T, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                         A, plan.rows[c], plan.nrows[c], X, ldx, cm, epi, partials, slot(gb));
+                         A, plan.rows[c], plan.nrows[c], X, ldx, cm, epi);
     }
     if (plan.nrows[kNumBins - 1] > 0) {
       unsigned gb = grid_for(plan.nrows[kNumBins - 1], 4, kWaveBlocks);
       hipLaunchKernelGGL((k_spmm_wave<T, IdxT, WT, Epi>), dim3(gb), dim3(256), 0, s,
-                         A, plan.rows[kNumBins - 1], plan.nrows[kNumBins - 1], X, ldx, cm, epi,
-                         partials, slot(gb));
+                         A, plan.rows[kNumBins - 1], plan.nrows[kNumBins - 1], X, ldx, cm, epi);
     }
     if (plan.n_hub > 0) {
       unsigned gb = grid_for(plan.n_chunks, 4, kWaveBlocks);
@@ -314,23 +246,21 @@ void run_all(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan,
       unsigned gc = grid_for(plan.n_hub, 4, kHubBlocks);
       hipLaunchKernelGGL((k_spmm_hub_combine<T, Epi>), dim3(gc), dim3(256), 0, s,
                          plan.hub_rows, plan.hub_chunk_begin, plan.n_hub,
-                         (const double *)plan.hub_partial, X, ldx, cm, epi, partials, slot(gc));
+                         (const double *)plan.hub_partial, X, ldx, cm, epi);
     }
   }
-  if (nparts) *nparts = used;
 }
 
 template <typename T, typename Epi>
 int dispatch(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
-             const ColMap &cm, const Epi &epi, double *partials, int *nparts,
-             hipStream_t s) {
+             const ColMap &cm, const Epi &epi, hipStream_t s) {
   if (cm.count < 1 || cm.count > kMaxNev) return SPHX_E_INVALID_ARG;
   auto go = [&](auto idx_tag, auto w_tag) {
     using IdxT = decltype(idx_tag);
     using WT = decltype(w_tag);
     Csr<IdxT, WT> A{static_cast<const IdxT *>(g->rowptr), g->col,
                     static_cast<const WT *>(g->w)};
-    run_all<T>(A, g->n, plan, X, ldx, cm, epi, partials, nparts, s);
+    run_all<T>(A, g->n, plan, X, ldx, cm, epi, s);
   };
   if (g->rp64) {
     if (g->wdt == SPHX_UNIT) go(int64_t{}, Unit{});
@@ -350,33 +280,19 @@ int dispatch(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
 template <typename T>
 int spmm_store(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
                const ColMap &cm, EpiStoreP<T> epi, hipStream_t s) {
-  return dispatch(g, plan, X, ldx, cm, EpiStore<T>{epi}, nullptr, nullptr, s);
-}
-
-template <typename T>
-int spmm_residual(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
-                  const ColMap &cm, EpiResidualP<T> epi, double *norm_partials,
-                  int *n_norm_blocks, hipStream_t s) {
-  return dispatch(g, plan, X, ldx, cm, EpiResidual<T>{epi}, norm_partials,
-                  n_norm_blocks, s);
+  return dispatch(g, plan, X, ldx, cm, EpiStore<T>{epi}, s);
 }
 
 template <typename T>
 int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
               const ColMap &cm, EpiChebP<T> epi, hipStream_t s) {
-  return dispatch(g, plan, X, ldx, cm, EpiCheb<T>{epi}, nullptr, nullptr, s);
+  return dispatch(g, plan, X, ldx, cm, EpiCheb<T>{epi}, s);
 }
 
 template int spmm_store<float>(sphx_graph *, const SpmmPlan &, const float *, int,
                                const ColMap &, EpiStoreP<float>, hipStream_t);
 template int spmm_store<double>(sphx_graph *, const SpmmPlan &, const double *, int,
                                 const ColMap &, EpiStoreP<double>, hipStream_t);
-template int spmm_residual<float>(sphx_graph *, const SpmmPlan &, const float *, int,
-                                  const ColMap &, EpiResidualP<float>, double *, int *,
-                                  hipStream_t);
-template int spmm_residual<double>(sphx_graph *, const SpmmPlan &, const double *, int,
-                                   const ColMap &, EpiResidualP<double>, double *, int *,
-                                   hipStream_t);
 template int spmm_cheb<float>(sphx_graph *, const SpmmPlan &, const float *, int,
                               const ColMap &, EpiChebP<float>, hipStream_t);
 template int spmm_cheb<double>(sphx_graph *, const SpmmPlan &, const double *, int,
