@@ -73,6 +73,7 @@ constexpr int kDegBlocksMax = 1024;
 constexpr int kRqBlocks = 256;
 
 // Workspace layout of a solve (also used for sizing with count_only).
+// split_b: bytes of the split's scratch, 0 for a solve without a split.
 template <typename T>
 struct SolveWs {
   double *d64, *dinv, *sq, *rsq;
@@ -96,7 +97,7 @@ struct SolveWs {
 
 template <typename T>
 void layout(Arena &a, SolveWs<T> &w, int64_t n, int m, int K, size_t plan_b,
-            bool want_split, int poly_degree, size_t ord_b) {
+            size_t split_b, int poly_degree, size_t ord_b) {
   w.d64 = a.take<double>(n);
   w.dinv = a.take<double>(n);
   w.sq = a.take<double>(n);
@@ -128,8 +129,8 @@ void layout(Arena &a, SolveWs<T> &w, int64_t n, int m, int K, size_t plan_b,
   w.norm_scratch = a.take<char>(normalize_scratch_bytes());
   w.deg_scratch = a.take<double>(4 * kDegBlocksMax);
   w.flags = a.take<int>(64);
-  if (want_split) {
-    w.split_scratch = a.take<char>(split_scratch_bytes(n, K));
+  if (split_b) {
+    w.split_scratch = a.take<char>(split_b);
     w.quality_scratch = a.take<char>(quality_scratch_bytes(K));
     w.V = a.take<T>((size_t)n * m);
     w.part = a.take<int32_t>(n);
@@ -933,12 +934,12 @@ static int poly_degree_of(const sphx_options *o) {
 // Bytes of the FP32 solve's layout; a MIXED solve keeps, after it, room for
 // an FP64 continuation (its own layout plus the n x nev initial and result
 // blocks), laid out from this offset.
-static size_t fp32_layout_bytes(sphx_graph *g, int nev, int K, bool split, int poly_degree,
-                                size_t ord_b) {
+static size_t fp32_layout_bytes(sphx_graph *g, int nev, int K, size_t split_b,
+                                int poly_degree, size_t ord_b) {
   Arena a;
   a.count_only = true;
   SolveWs<float> w;
-  layout(a, w, g->n, nev, K, plan_bytes(g), split, poly_degree, ord_b);
+  layout(a, w, g->n, nev, K, plan_bytes(g), split_b, poly_degree, ord_b);
   return align_up(a.off, 256);
 }
 
@@ -949,18 +950,18 @@ static size_t ord_bytes_of(sphx_graph *g, const sphx_options *o) {
   return may ? degree_order_bytes(g) : 0;
 }
 
-static size_t solve_bytes(sphx_graph *g, int nev, int precision, int K, bool split,
+static size_t solve_bytes(sphx_graph *g, int nev, int precision, int K, size_t split_b,
                           int poly_degree, size_t ord_b) {
   Arena a;
   a.count_only = true;
   size_t pb = plan_bytes(g);
   SolveWs<double> w;
   if (precision == SPHX_MIXED) {
-    a.off = fp32_layout_bytes(g, nev, K, split, poly_degree, ord_b);
-    layout(a, w, g->n, nev, K, pb, false, poly_degree, ord_b);
+    a.off = fp32_layout_bytes(g, nev, K, split_b, poly_degree, ord_b);
+    layout(a, w, g->n, nev, K, pb, 0, poly_degree, ord_b);
     (void)a.take<double>((size_t)g->n * nev * 2);
   } else {
-    layout(a, w, g->n, nev, K, pb, split, poly_degree, ord_b);
+    layout(a, w, g->n, nev, K, pb, split_b, poly_degree, ord_b);
   }
   return a.off + 4096;
 }
@@ -968,11 +969,12 @@ static size_t solve_bytes(sphx_graph *g, int nev, int precision, int K, bool spl
 int sphx_workspace_size(sphx_handle *h, sphx_graph *g, int nev, const sphx_options *opt,
                         size_t *bytes) {
   if (!h || !g || !opt || !bytes || nev < 1 || nev > kMaxNev) return SPHX_E_INVALID_ARG;
-  // the largest K with floor(log2 K) + 1 = nev: the split and quality scratch
-  // grow with K, so this bounds every partition into d = nev coordinates
-  int K = (1 << nev) - 1;
-  size_t a = solve_bytes(g, nev, opt->precision, K, true, poly_degree_of(opt),
-                         ord_bytes_of(g, opt));
+  // every partition into d = nev coordinates has floor(log2 K) + 1 = nev: the
+  // quality scratch grows with K, the split's does not (it depends on how K
+  // factors), so its largest over those K is taken
+  const int K = (1 << nev) - 1;
+  size_t a = solve_bytes(g, nev, opt->precision, K, split_scratch_max(g->n, 1 << (nev - 1), K),
+                         poly_degree_of(opt), ord_bytes_of(g, opt));
   size_t b = adjoint_scratch_bytes(g->n, nev) + plan_bytes(g) + sizeof(double) * 2 * g->n +
              4096;
   *bytes = std::max(a, b);
@@ -1307,10 +1309,11 @@ static int eigensolve_impl(sphx_handle *h, sphx_graph *g, int nev, const sphx_op
   h->plog.reset();
   h->plog.on = h->timing && stats;
   const bool split = part != nullptr;
+  const size_t split_b = split ? split_scratch_bytes(g->n, K) : 0;
   char *ws = nullptr;
   const size_t ord_b = ord_bytes_of(g, o);
   SPHX_TRY(get_workspace(h,
-                         solve_bytes(g, nev, o->precision, std::max(K, 1), split,
+                         solve_bytes(g, nev, o->precision, std::max(K, 1), split_b,
                                      poly_degree_of(o), ord_b),
                          &ws));
   bool hit_max = false;
@@ -1320,7 +1323,7 @@ static int eigensolve_impl(sphx_handle *h, sphx_graph *g, int nev, const sphx_op
     Arena a;
     a.base = ws;
     SolveWs<T> w;
-    layout(a, w, g->n, nev, std::max(K, 1), plan_bytes(g), split, poly_degree_of(o), ord_b);
+    layout(a, w, g->n, nev, std::max(K, 1), plan_bytes(g), split_b, poly_degree_of(o), ord_b);
     const size_t used = align_up(a.off, 256);   // the FP64 continuation starts here
     T *vecs = eigvecs ? static_cast<T *>(eigvecs) : w.V;
     if (!vecs) return set_err(h, SPHX_E_INVALID_ARG, "eigvecs is NULL");
@@ -1335,7 +1338,7 @@ static int eigensolve_impl(sphx_handle *h, sphx_graph *g, int nev, const sphx_op
         Arena a64;
         a64.base = ws + used;
         SolveWs<double> w64;
-        layout(a64, w64, g->n, nev, std::max(K, 1), plan_bytes(g), false,
+        layout(a64, w64, g->n, nev, std::max(K, 1), plan_bytes(g), 0,
                poly_degree_of(o), ord_b);
         double *x0 = a64.take<double>((size_t)g->n * nev);
         double *v64 = a64.take<double>((size_t)g->n * nev);

@@ -741,6 +741,16 @@ size_t split_scratch_bytes(int64_t n, int K) {
   return std::max(b, f) + 1024;
 }
 
+// The radix passes' part grows with K, and so does the sample bins' over the
+// K that have it; these are at most kFastSections * p with
+// kFastSections * (p - 1) <= kFastTargets.
+size_t split_scratch_max(int64_t n, int klo, int khi) {
+  size_t b = split_scratch_bytes(n, khi);
+  for (int k = std::min(khi, kFastTargets + kFastSections); k >= klo; --k)
+    if (fast_levels(section_counts(k))) return std::max(b, split_scratch_bytes(n, k));
+  return b;
+}
+
 // The levels by sample bins.  *flags: F_NAN, F_CROWDED (part is then not
 // usable).
 template <typename T>

@@ -62,3 +62,18 @@ def test_without_workspace_the_handle_allocates_and_releases():
     assert sx.workspace_owned(h) > 0
     sx.workspace_release(h)
     assert sx.workspace_owned(h) == 0
+
+
+@pytest.mark.parametrize("prec", [sx.FP64, sx.MIXED])
+@pytest.mark.parametrize("K", [64, 96, 100, 127, 256, 289])
+def test_workspace_size_bounds_every_part_count(prec, K):
+    """The split's scratch depends on K's prime factors (127 is prime, the
+    others have small ones), not only on its size: the size for
+    nev = floor(log2 K) + 1 holds for each of them."""
+    h = sx.Handle(0)
+    g = graphgen.config_graph("grid7_128", scale_down=8)          # 16^3 grid
+    rp, col, w = upload(g)
+    G = sx.Graph(h, rp, col, w)
+    opts = sx.options_default(True, sx.PRECOND_JACOBI, precision=prec, max_iter=3)
+    sx.partition(h, G, K, opts, allow_not_converged=True)
+    assert sx.workspace_owned(h) == 0
