@@ -946,7 +946,7 @@ static size_t fp32_layout_bytes(sphx_graph *g, int nev, int K, size_t split_b,
 // room for the degree-ordered copy of the graph: while the degrees are not
 // known yet, whenever the option asks for it
 static size_t ord_bytes_of(sphx_graph *g, const sphx_options *o) {
-  const bool may = o->reorder && (!g->stats_valid || g->max_deg > kUnbinnedMaxDeg);
+  const bool may = o->reorder && (!known(g->stats_valid) || g->max_deg > kUnbinnedMaxDeg);
   return may ? degree_order_bytes(g) : 0;
 }
 

@@ -127,15 +127,17 @@ struct sphx_graph {
   const void *w = nullptr;
   int wdt = SPHX_UNIT;
   const int32_t *vwgt = nullptr;
-  // cached statistics (computed on first use)
-  int stats_valid = 0;
+  // Facts of the arrays, computed on first use.  Calls of several handles (host
+  // threads) on one graph may meet here: a flag is set by a release store
+  // behind its values and read by an acquire load before them (sphx::publish,
+  // sphx::known); whoever computes them finds the same values.
+  int stats_valid = 0;             // max_deg, min_deg, sum_deg
   int64_t max_deg = 0;
   int64_t min_deg = 0;
   int64_t sum_deg = 0;
+  int wrange_valid = 0;            // wmin, wmax: the edge weights' range
+  double wmin = 0.0, wmax = 0.0;
   int offsets16 = 0;               // int16 column offsets: 0 not tried, 1 fit, 2 do not
-  double max_wdeg = 0.0;
-  double wmin = 0.0, wmax = 0.0;   // edge weight range (weighted graphs)
-  int wrange_valid = 0;            // wmin / wmax computed
 };
 
 // ----------------------------------------------------------------- helpers
@@ -159,6 +161,12 @@ inline int set_err(sphx_handle *h, int code, const std::string &msg) {
     int s_ = (expr);                \
     if (s_ < 0) return s_;          \
   } while (0)
+
+// A graph's recorded facts: their flag (nonzero: the facts may be read).
+inline int known(const int &flag) { return __atomic_load_n(&flag, __ATOMIC_ACQUIRE); }
+inline void publish(int &flag, int value = 1) {
+  __atomic_store_n(&flag, value, __ATOMIC_RELEASE);
+}
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

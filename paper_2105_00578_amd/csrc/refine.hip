@@ -779,7 +779,7 @@ int refine(sphx_graph *g, int32_t *part, int K, double eps, int max_passes, doub
   int64_t nmoves = 0;
   const unsigned gv = grid_for(n, 256, 8192);
   // rows above kThreadDeg are listed and take the block kernels
-  const bool long_rows = !(g->stats_valid && g->max_deg <= kThreadDeg);
+  const bool long_rows = !(known(g->stats_valid) && g->max_deg <= kThreadDeg);
   auto go = [&](auto s_tag, auto idx_tag, auto w_tag) -> int {
     using S = decltype(s_tag);
     using IdxT = decltype(idx_tag);

@@ -396,7 +396,7 @@ int validate_graph(sphx_graph *g, hipStream_t s, int32_t *flags_dev, int *flags_
 constexpr int kDegBlocks = 1024;
 
 int weight_range(sphx_graph *g, void *scratch, void *pinned, hipStream_t s) {
-  if (g->wdt == SPHX_UNIT || g->wrange_valid) return SPHX_OK;
+  if (g->wdt == SPHX_UNIT || known(g->wrange_valid)) return SPHX_OK;
   double *stats = static_cast<double *>(scratch);
   double *host = static_cast<double *>(pinned);
   const unsigned gw = grid_for(g->nnz, 256, kWrangeBlocks);
@@ -423,7 +423,7 @@ int weight_range(sphx_graph *g, void *scratch, void *pinned, hipStream_t s) {
                    "edge weights span more than a factor 2^40 (exact sums unsupported)");
   g->wmax = a;
   g->wmin = b;
-  g->wrange_valid = 1;
+  publish(g->wrange_valid);
   return SPHX_OK;
 }
 
@@ -470,24 +470,26 @@ int compute_degrees(sphx_graph *g, double *d64, float *d32, void *scratch,
   out->sum_deg = g->nnz;
   out->max_wdeg = wmx;
   out->min_wdeg = wmn;
-  g->max_deg = out->max_deg;
-  g->min_deg = out->min_deg;
-  g->sum_deg = out->sum_deg;
-  g->max_wdeg = wmx;
-  g->stats_valid = 1;
+  if (!known(g->stats_valid)) {
+    g->max_deg = out->max_deg;
+    g->min_deg = out->min_deg;
+    g->sum_deg = out->sum_deg;
+    publish(g->stats_valid);
+  }
   return SPHX_OK;
 }
 
 int pattern_stats(sphx_graph *g, void *scratch, DegreeStats *out, void *pinned, hipStream_t s) {
   SPHX_TRY(weight_range(g, scratch, pinned, s));
-  if (!g->stats_valid) {
+  if (!known(g->stats_valid)) {
     sphx_graph u = *g;        // the same pattern with unit weights
     u.wdt = SPHX_UNIT;
+    u.stats_valid = 0;
     SPHX_TRY(compute_degrees(&u, nullptr, nullptr, scratch, out, pinned, s));
     g->max_deg = u.max_deg;
     g->min_deg = u.min_deg;
     g->sum_deg = u.sum_deg;
-    g->stats_valid = 1;
+    publish(g->stats_valid);
   }
   out->max_deg = g->max_deg;
   out->min_deg = g->min_deg;
@@ -776,7 +778,7 @@ int build_degree_order(sphx_graph *g, void *scratch, sphx_graph *out, int32_t **
 // the int16 column offsets are kept for unit-weight graphs with 32-bit row
 // pointers that are (or may be, before their degrees are known) unbinned
 static bool may_compress(const sphx_graph *g) {
-  return g->wdt == SPHX_UNIT && !g->rp64 && (!g->stats_valid || g->max_deg <= kUnbinnedMaxDeg);
+  return g->wdt == SPHX_UNIT && !g->rp64 && (!known(g->stats_valid) || g->max_deg <= kUnbinnedMaxDeg);
 }
 
 size_t plan_bytes(sphx_graph *g) {
@@ -809,20 +811,22 @@ int build_plan(sphx_graph *g, Arena &ws, SpmmPlan *plan, const DegreeStats &st,
   int *counts = ws.take<int>(nb * kNumCls + kNumCls);
   if (st.max_deg <= kUnbinnedMaxDeg) {   // natural order, one group size
     plan->group = st.max_deg <= bin_max_deg(0) ? bin_group(0) : bin_group(1);
-    if (offsets && may_compress(g) && g->nnz > 0 && g->offsets16 != 2) {
+    int fits = known(g->offsets16);
+    if (offsets && may_compress(g) && g->nnz > 0 && fits != 2) {
       int16_t *d = ws.take<int16_t>(g->nnz);
       int *flag = ws.take<int>(4);
       hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, flag, 4, 0);
       hipLaunchKernelGGL(k_delta16, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n,
                          (const int32_t *)g->rowptr, g->col, d, flag);
       SPHX_HIP(g->h, hipGetLastError());
-      if (g->offsets16 == 0) {   // whether the pattern's offsets fit is known after this
+      if (fits == 0) {           // whether the pattern's offsets fit is known after this
         int *hf = static_cast<int *>(pinned);
         SPHX_HIP(g->h, hipMemcpyAsync(hf, flag, sizeof(int), hipMemcpyDeviceToHost, s));
         SPHX_HIP(g->h, hipStreamSynchronize(s));
-        g->offsets16 = hf[0] == 0 ? 1 : 2;
+        fits = hf[0] == 0 ? 1 : 2;
+        publish(g->offsets16, fits);
       }
-      if (g->offsets16 == 1) plan->dcol = d;
+      if (fits == 1) plan->dcol = d;
     }
     return SPHX_OK;
   }

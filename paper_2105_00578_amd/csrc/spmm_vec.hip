@@ -862,7 +862,7 @@ int dispatch_types(sphx_graph *g, const SpmmPlan &plan, const T *X, int ld, cons
     if constexpr (std::is_same_v<EpiT<T, VB, NV>, VResidual<T, VB, NV>> ||
                   std::is_same_v<EpiT<T, VB, NV>, VShiftDot<T, VB, NV>>)
       epi.m = m;
-    run_vec<T, VB, NV>(A, g->n, g->stats_valid ? g->max_deg : kUnbinnedMaxDeg, plan, X, ld, epi, partials, nparts, m, s, ev);
+    run_vec<T, VB, NV>(A, g->n, known(g->stats_valid) ? g->max_deg : kUnbinnedMaxDeg, plan, X, ld, epi, partials, nparts, m, s, ev);
   };
   if (g->rp64) {
     if (g->wdt == SPHX_UNIT) go(int64_t{}, Unit{});
