@@ -24,9 +24,11 @@
 // sections' histograms, and only its members (about n / 2048) go through the
 // radix select, in one workgroup's LDS.  The bins are intervals of the
 // composite order, so ties and any distribution of the values are as good as
-// another; a target whose bin is too full for one workgroup raises a flag,
-// and the radix passes over all members (in split_mj, also for more sections
-// or cuts) are run instead.  2 M members, K = 64, FP32: 1.13 ms by the radix
+// another, unless the levels before have cut a section out of few of its
+// coordinate's bins: a target whose bin is too full for its list raises a flag,
+// the levels after it do nothing, and the radix passes over all members (in
+// split_mj, also for more sections or cuts, and where fast_levels expects such
+// bins) are run instead.  2 M members, K = 64, FP32: 1.13 ms by the radix
 // passes (8 per level, each over all members, the first ones with most
 // members in a few counters), 0.35 ms by sample bins, of which the strided
 // reads of the coordinates take about a third.
@@ -93,6 +95,9 @@ __device__ __forceinline__ bool prefix_match(K ord, uint32_t id, K pord, uint32_
   uint32_t mask = dd >= 4 ? ~0u : (~0u << (8 * (4 - dd)));
   return (id & mask) == pid;
 }
+
+// flags of the sample bins: NaN coordinate, a bin too full for one workgroup
+enum : int { F_NAN = 1, F_CROWDED = 2 };
 
 // Up to 32 targets count in LDS first (16 or 32 rows of 256 bins), more in
 // global memory.
@@ -220,10 +225,14 @@ __global__ void k_finish_sections(int nsec, int p, const long long *lo, const lo
   }
 }
 
-// child = number of cuts of the member's section that it lies after
+// child = number of cuts of the member's section that it lies after; nothing
+// where the levels before were given up (flag, or null): part may then hold no
+// sections
 template <typename K>
 __global__ void k_assign(int64_t n, const K *keys, int32_t *part, int p, const K *pord,
-                         const uint32_t *pid, const int *incl, const long long *W) {
+                         const uint32_t *pid, const int *incl, const long long *W,
+                         const int *flag) {
+  if (flag && (*flag & F_CROWDED)) return;
   const int pm = p - 1;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -278,15 +287,19 @@ constexpr int kFastSections = 256;
 constexpr int kFastCuts = 63;         // cuts per section
 constexpr int kFastTargets = 4096;
 constexpr int kFastLds = 4096;        // candidates kept in LDS
-constexpr int kFastCap = 65536;       // candidates per target, at most
+constexpr int kFastCap = 65536;       // candidates per target (see fast_cap)
 constexpr int kCutThreads = 1024;
 // Candidates of a target are appended through kSub counters, a cache line
 // each, to kSub runs of its list: appends to one counter go one after the
 // other at about 0.2 us (with one counter per target the pass over 2 M members
-// took 218 us).
-constexpr int kSub = 32;
+// took 218 us).  A hash of the member's id chooses the run, and a full run
+// passes the member on to the next one, so that the whole list is a target's
+// room wherever its members lie (with the run chosen by the block, lattices in
+// natural order, whose late sections lie in few blocks, filled single runs and
+// ran into the radix passes: 30,000 vertices, K = 256, FP32 880 us).
+constexpr int kSub = 32, kSubBits = 5;
+static_assert(kSub == 1 << kSubBits, "runs are chosen by kSubBits of a hash");
 constexpr int kSubStride = 16;
-enum : int { F_NAN = 1, F_CROWDED = 2 };
 
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   z += 0x9E3779B97F4A7C15ull;
@@ -371,6 +384,7 @@ __global__ __launch_bounds__(512) void k_level(const T *__restrict__ coords, int
   __shared__ K so[kSample];
   __shared__ uint32_t si[kSample];
   __shared__ H h[kBins];
+  const int stop = *flag & F_CROWDED;       // (set by the levels before only)
   for (int q = threadIdx.x; q < B - 1; q += 512) {
     const int at = (int)((int64_t)(q + 1) * kSample / B);
     so[q] = sord[at];
@@ -378,6 +392,7 @@ __global__ __launch_bounds__(512) void k_level(const T *__restrict__ coords, int
   }
   for (int q = threadIdx.x; q < B * nsec; q += 512) h[q] = 0;
   __syncthreads();
+  if (stop) return;
   bool nan = false;
   for (int64_t i = (int64_t)blockIdx.x * 512 + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * 512) {
@@ -471,25 +486,42 @@ __global__ __launch_bounds__(256) void k_find_bins(int B, int p, Cuts<K> prev, l
   }
 }
 
-// the members of every target's bin (in no particular order); cap: of a run
+// The members of every target's bin (in no particular order); cap: of a run.
+// Does nothing once a bin was too full (the levels are then not used).
 __global__ __launch_bounds__(256) void k_candidates(int64_t n, const uint16_t *__restrict__ bins,
                                                     const int32_t *__restrict__ part, int first,
                                                     int p, int ntgt, const int *__restrict__ tbin,
                                                     int cap, int *cnt, uint32_t *list,
                                                     int *flag) {
   __shared__ int tb[kFastTargets];
+  __shared__ int stop;            // one reading for the block: others may set it
+  if (threadIdx.x == 0) stop = *flag & F_CROWDED;
   for (int q = threadIdx.x; q < ntgt; q += 256) tb[q] = tbin[q];
   __syncthreads();
+  if (stop) return;
   const int pm = p - 1;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * 256) {
     const int b = bins[i], t0 = (first ? 0 : part[i]) * pm;
     for (int j = 0; j < pm; ++j)
       if (tb[t0 + j] == b) {
-        const int64_t run = (int64_t)(t0 + j) * kSub + (blockIdx.x & (kSub - 1));
-        const int at = atomicAdd(&cnt[run * kSubStride], 1);
-        if (at < cap) list[run * cap + at] = (uint32_t)i;
-        else atomicOr(flag, F_CROWDED);
+        const unsigned r0 = ((uint32_t)i * 0x9E3779B1u) >> (32 - kSubBits);   // Fibonacci hash
+        unsigned q = 0;
+        for (; q < kSub; ++q) {
+          const int64_t run = (int64_t)(t0 + j) * kSub + ((r0 + q) & (kSub - 1));
+          if (q && __hip_atomic_load(&cnt[run * kSubStride], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT) >= cap)
+            continue;                                            // full already
+          const int at = atomicAdd(&cnt[run * kSubStride], 1);
+          if (at < cap) {
+            list[run * cap + at] = (uint32_t)i;
+            break;
+          }
+        }
+        if (q == kSub) {
+          atomicOr(flag, F_CROWDED);
+          return;
+        }
       }
   }
 }
@@ -506,7 +538,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_bin(int64_t n, int p, const
                                                   uint32_t *list, int cap,
                                                   const int *__restrict__ cnt,
                                                   const long long *__restrict__ base_in,
-                                                  Cuts<K> out) {
+                                                  const int *__restrict__ flag, Cuts<K> out) {
   __shared__ K ck[kFastLds];
   __shared__ uint32_t ci[kFastLds];
   __shared__ unsigned long long h[256];
@@ -518,6 +550,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_bin(int64_t n, int p, const
   __shared__ int one;
   const int tg = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int s = tg / (p - 1);
+  const int stop = *flag & F_CROWDED;
   const long long Ws = out.W[s];
   const long long jW = (long long)(tg - s * (p - 1) + 1) * Ws;
   // the runs' starts among the target's candidates
@@ -541,6 +574,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_bin(int64_t n, int p, const
     }
   }
   __syncthreads();
+  if (stop) return;
   const int c = at[kSub];
   const uint32_t *mine = list + (int64_t)tg * kSub * cap;
   const bool lds = c <= kFastLds;
@@ -700,16 +734,36 @@ std::vector<int> section_counts(int K) {
   return f;
 }
 
-// candidates per run (kSub of them per target) of a level with ntgt targets
+// Candidates per run (kSub of them per target) of a level with ntgt targets:
+// in all at most 4 n + 256 ntgt, and per target at most kFastCap or 32 average
+// bins (a bin lies between two neighbours of the sorted sample, so its size
+// varies like an exponential variable's: 16 times the average once in 10^6).
 static int fast_cap(int64_t n, int ntgt) {
-  return (int)std::min<int64_t>(kFastCap, std::max<int64_t>(256, 4 * n / ntgt)) / kSub;
+  const int64_t most = std::max<int64_t>(kFastCap, n / kBins * 32);
+  return (int)(std::min<int64_t>(most, std::max<int64_t>(256, 4 * n / ntgt)) / kSub);
 }
 
-// every level of K within the sample bins' limits
-static bool fast_levels(const std::vector<int> &counts) {
+// Every level of K within the sample bins' limits (n = 0), and with n members
+// in ncoord coordinates worth them: a section that earlier levels have cut r-fold
+// along the level's coordinate lies in one r-th of the coordinate's bins, so a
+// target's bin holds about n r / kBins members (at most the section), which one
+// workgroup goes over.  Measured against the radix passes (FP32, with r up to
+// 32 and 8 M members in one coordinate 5.8 instead of 2.8 ms, with r up to 8 and
+// 32 M 6.2 instead of 4.3; in two coordinates, r up to 8, 64 M members into 256
+// parts 23 instead of 45 ms): beyond kFastCap / 2 members it loses from r = 8 on
+// where the radix passes count in LDS, and from some r above 9 where they count
+// in memory.
+static bool fast_levels(const std::vector<int> &counts, int64_t n = 0, int ncoord = 1) {
   int64_t nsec = 1;
-  for (int p : counts) {
-    if (nsec > kFastSections || p - 1 > kFastCuts || nsec * (p - 1) > kFastTargets) return false;
+  std::vector<int64_t> cut(counts.size(), 1);   // r per coordinate in use
+  for (size_t l = 0; l < counts.size(); ++l) {
+    const int p = counts[l];
+    const int64_t ntgt = nsec * (p - 1);
+    if (nsec > kFastSections || p - 1 > kFastCuts || ntgt > kFastTargets) return false;
+    int64_t &r = cut[l % (size_t)ncoord];
+    if (std::min(n / kBins * r, n / nsec) > kFastCap / 2 && r > (ntgt <= kLdsTargets ? 4 : 9))
+      return false;
+    r *= p;
     nsec *= p;
   }
   return !counts.empty();
@@ -825,13 +879,13 @@ static int split_levels(sphx_graph *g, const T *coords, int ld, int ncoord, int 
     now.p = p;
     hipLaunchKernelGGL((k_cut_bin<KT>), dim3(ntgt), dim3(kCutThreads), 0, s, n, p, (const KT *)keys,
                        g->vwgt, list, cap, (const int *)cnt,
-                       (const long long *)base, now);
+                       (const long long *)base, (const int *)flag, now);
     nsec *= p;
   }
   const Cuts<KT> &z = cut[(nlev - 1) & 1];
   if (nlev == 1) hipLaunchKernelGGL(k_zero_parts, dim3(gn), dim3(256), 0, s, n, part);
   hipLaunchKernelGGL((k_assign<KT>), dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n, keys,
-                     part, z.p, z.ord, z.id, z.incl, z.W);
+                     part, z.p, z.ord, z.id, z.incl, z.W, (const int *)flag);
   if (hipGetLastError() != hipSuccess) {
     *err = "split kernel launch failed";
     return SPHX_E_HIP;
@@ -851,7 +905,7 @@ int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K, int32_t 
   using KT = typename Ord<T>::K;
   const int64_t n = g->n;
   const std::vector<int> counts = section_counts(K);
-  if (fast_levels(counts)) {
+  if (fast_levels(counts, n, ncoord)) {
     int flags = 0;
     const int r = split_levels<T>(g, coords, ld, ncoord, K, counts, part, scratch, pinned, s,
                                   err, &flags);
@@ -911,7 +965,7 @@ int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K, int32_t 
     hipLaunchKernelGGL(k_finish_sections, dim3(grid_for(nsec, 256, 1 << 16)), dim3(256), 0, s,
                        nsec, p, lo, W, Wnext);
     hipLaunchKernelGGL((k_assign<KT>), dim3(gn), dim3(256), 0, s, n, keys, part, p, pord, pid,
-                       incl, W);
+                       incl, W, (const int *)nullptr);
     nsec *= p;
     ok &= hipMemcpyAsync(W, Wnext, sizeof(long long) * nsec, hipMemcpyDeviceToDevice, s) ==
           hipSuccess;

@@ -175,3 +175,55 @@ def test_partition_general_k_grid(handle, K):
     assert imb == quality.imbalance(ref, K)
     sizes = np.bincount(ref, minlength=K)
     assert sizes.min() >= n // K and sizes.max() <= -(-n // K)
+
+
+def _split_kernels(handle, G, coords, K):
+    """The split's parts and the names of the kernels that it ran."""
+    from torch.profiler import ProfilerActivity, profile
+    x = torch.from_numpy(np.ascontiguousarray(coords)).to(dev())
+    sx.split(handle, G, x, K)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        part = sx.split(handle, G, x, K)
+        torch.cuda.synchronize()
+    names = {e.name for e in prof.events()}
+    assert any("k_assign" in q for q in names)       # the trace holds the library's kernels
+    return part.cpu().numpy(), any("k_hist" in q for q in names)
+
+
+def _path(handle, n):
+    g = graphgen.csr_from_edges(n, np.arange(n - 1), np.arange(1, n))
+    return sx.Graph(handle, *upload(g))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("sides,K", [((48, 62), 64), ((48, 62), 100), ((48, 62), 256),
+                                     ((23, 19, 14), 64), ((115, 150), 256), ((40, 33, 24), 256)])
+def test_lattice_embeddings_stay_on_the_sample_bins(handle, sides, K, dtype):
+    """Smooth embeddings of lattices in natural order, whose late sections are
+    compact pieces (their members' ids lie close together): no target's list
+    may overflow, which would run the radix passes after the sample bins."""
+    n = int(np.prod(sides))
+    d = sx.num_eigenvectors(K) - 1
+    modes = sorted((t for t in np.ndindex(*[min(s, 8) for s in sides]) if any(t)),
+                   key=lambda t: sum((k / s) ** 2 for k, s in zip(t, sides)))[:d]
+    axes = np.indices(sides).reshape(len(sides), n)
+    V = np.stack([np.prod([np.cos(np.pi * k * (x + 0.5) / s) for k, x, s in zip(t, axes, sides)],
+                          axis=0) for t in modes], axis=1)
+    V = (V @ (np.eye(d) + 0.05 * np.random.default_rng(K).standard_normal((d, d)))).astype(dtype)
+    part, radix = _split_kernels(handle, _path(handle, n), V, K)
+    assert np.array_equal(part, split.split_mj(V, K))
+    assert not radix
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,K", [(40000, 506),      # 23 x 11 x 2: the second of three levels
+                                 (20000, 3721)])    # 61 x 61: the last level
+def test_crowded_bins_end_in_the_radix_passes(handle, n, K, dtype):
+    """One coordinate cut again and again: its sections lie in one or two bins
+    each, which hold more members than a target's list; the levels are given up
+    there and the radix passes give the parts."""
+    x = np.random.default_rng(K).standard_normal((n, 1)).astype(dtype)
+    part, radix = _split_kernels(handle, _path(handle, n), x, K)
+    assert np.array_equal(part, split.split_mj(x, K))
+    assert radix
