@@ -335,8 +335,8 @@ int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
   const int wd = compact ? lda : ld;     // row width of the iteration buffers
   const int mm = compact ? na : m;
   auto launch = [&](const T *src, EpiChebP<T> e, double bytes) -> int {
-    // rows of at least two values take the vector-row kernels; the
-    // column-lane kernels serve a caller's single column
+    // rows of at least two values take the vector-row kernels, a caller's
+    // single column those of its own
     int st;
     if (wd >= 2) {
       LaunchEvents ev;
@@ -344,7 +344,7 @@ int cheb_apply(sphx_handle *h, sphx_graph *g, const SpmmPlan &plan, int m, int l
       st = vspmm_cheb<T>(g, plan, src, wd, mm, e, s, timed ? &ev : nullptr);
     } else {
       int id = h->plog.begin(PH_PRECOND, bytes, s);
-      st = spmm_cheb<T>(g, plan, src, m, cm, e, s);
+      st = spmm_cheb<T>(g, plan, src, e, s);
       h->plog.end(id, s);
     }
     ++*calls;
@@ -1052,7 +1052,6 @@ int sphx_laplacian_apply(sphx_handle *h, sphx_graph *g, int problem, int m, int 
                          s, (const double *)X, (const double *)rsq, 1.0, (double *)tmp, n, m);
     src = tmp;
   }
-  ColMap cm = identity_map(m);
   // rows of at least two values take the vector-row kernels (their vectors
   // need no more than the elements' alignment)
   const bool vec = m >= 2;
@@ -1060,13 +1059,11 @@ int sphx_laplacian_apply(sphx_handle *h, sphx_graph *g, int problem, int m, int 
   if (dtype == SPHX_F32)
     r = vec ? vspmm_store<float>(g, plan, (const float *)src, m, m,
                                  EpiStoreP<float>{(float *)Y, m}, s)
-            : spmm_store<float>(g, plan, (const float *)src, m, cm,
-                                EpiStoreP<float>{(float *)Y, m}, s);
+            : spmm_store<float>(g, plan, (const float *)src, (float *)Y, s);
   else
     r = vec ? vspmm_store<double>(g, plan, (const double *)src, m, m,
                                   EpiStoreP<double>{(double *)Y, m}, s)
-            : spmm_store<double>(g, plan, (const double *)src, m, cm,
-                                 EpiStoreP<double>{(double *)Y, m}, s);
+            : spmm_store<double>(g, plan, (const double *)src, (double *)Y, s);
   if (r != SPHX_OK || !norm) return r;
   if (dtype == SPHX_F32)
     hipLaunchKernelGGL(k_scale_rows<float>, dim3(grid_for(n * m, 256, 4096)), dim3(256), 0, s,

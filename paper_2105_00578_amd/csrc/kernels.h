@@ -35,7 +35,7 @@ struct SpmmPlan {
   // unbinned unit-weight graphs with 32-bit row pointers whose neighbours all
   // lie within 32767 rows: column offsets from the row, 2 bytes per entry
   const int16_t *dcol = nullptr;
-  const int32_t *rows[kNumBins] = {};    // row lists of the classes (binned)
+  const int32_t *rows[kNumBins] = {};    // row lists of the classes (binned), in one array
   int64_t nrows[kNumBins] = {};
   const int32_t *hub_rows = nullptr;     // hub rows
   int64_t n_hub = 0;
@@ -136,12 +136,11 @@ constexpr int kMaxNormBlocks = 10240;
 // Rayleigh-quotient partials: up to kRqStride blocks, sum-major.
 constexpr int kRqStride = 256;
 
+// Products of a single column (epi.ld is 1).
 template <typename T>
-int spmm_store(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
-               const ColMap &cm, EpiStoreP<T> epi, hipStream_t s);
+int spmm_store(sphx_graph *g, const SpmmPlan &plan, const T *X, T *Y, hipStream_t s);
 template <typename T>
-int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, int ldx,
-              const ColMap &cm, EpiChebP<T> epi, hipStream_t s);
+int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, EpiChebP<T> epi, hipStream_t s);
 
 // Row width padded to whole 16-byte vectors.
 inline int padded_ld(int m, int elem_bytes) {

@@ -160,14 +160,11 @@ int poly_roots(sphx_graph *g, const SpmmPlan &plan, bool gen, const double *d64,
   hipLaunchKernelGGL(k_scale_vec, dim3(ge), dim3(256), 0, s, (const double *)V, n,
                      1.0 / std::sqrt(host[0]), (const double *)nullptr, V);
   std::vector<double> H((size_t)(k1 + 1) * k1, 0.0);
-  ColMap one;
-  one.count = 1;
-  for (int q = 0; q < kMaxNev; ++q) one.col[q] = 0;
   int kk = k1;
   for (int j = 0; j < k1; ++j) {
     const double *vj = V + (size_t)j * n;
     // w = A v_j (A = L, or D^-1 L)
-    SPHX_TRY(spmm_store<double>(g, plan, vj, 1, one, EpiStoreP<double>{w, 1}, s));
+    SPHX_TRY(spmm_store<double>(g, plan, vj, w, s));
     if (gen)
       hipLaunchKernelGGL(k_scale_vec, dim3(ge), dim3(256), 0, s, (const double *)w, n, 1.0,
                          dinv, w);

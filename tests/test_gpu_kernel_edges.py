@@ -252,3 +252,25 @@ def test_refine_sum_widths(handle, log_range, deg):
     ref, kept_ref, moves_ref = refine.refine(g.rowptr, g.col, g.w, part0, K, eps=0.2)
     assert np.array_equal(pd.cpu().numpy(), ref) and (kept, moves) == (kept_ref, moves_ref)
     assert moves > 0
+
+
+@pytest.mark.parametrize("leaves", [1024, 1025, 1536, 64 * 512, 64 * 512 + 1, 130 * 512 + 7])
+@pytest.mark.parametrize("f32", [False, True])
+def test_single_column_hub_rows_vs_numpy(handle, leaves, f32):
+    """The last row of a wavefront, the first hub, and hubs of 64 chunks of 512
+    entries (one per lane that combines them), 65 and 131.  A lane adds at most
+    4 entries twice over, 64 lanes 6 times, at most 3 chunks and 6 times again,
+    and each difference is rounded: below 24 roundings of the sum of |terms|."""
+    import torch
+    import paper_2105_00578_amd as sx
+    from tests.gpu_util import star_graph, upload
+    g = star_graph(leaves)
+    G = sx.Graph(handle, *upload(g))
+    dt, eps = (np.float32, 2.0 ** -24) if f32 else (np.float64, 2.0 ** -53)
+    x = np.random.default_rng(leaves).standard_normal(g.n).astype(dt)
+    y = sx.laplacian_apply(handle, G, torch.from_numpy(x).cuda()).cpu().numpy()
+    row = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+    t = x.astype(np.float64)[row] - x.astype(np.float64)[g.col]
+    bound = 24 * eps * np.bincount(row, np.abs(t), g.n)
+    want = np.array([math.fsum(t[a:b]) for a, b in zip(g.rowptr[:-1], g.rowptr[1:])])
+    assert np.all(np.abs(y.astype(np.float64) - want) <= bound)
