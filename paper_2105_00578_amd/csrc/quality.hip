@@ -27,9 +27,14 @@ namespace {
 // memory per chunk and end by a single thread, took 205 us there and 190 us on
 // a weighted 27-point mesh of 883,200 rows, now 65.  Not kept: 16 or 8 entries
 // per thread (127 and 110 us), the next chunk's columns loaded ahead (128 us).
+//
+// A chunk is served from LDS when the row behind its last is staged too, so
+// kCutRows allows one more pass of the block than rows of one entry need: with
+// room for kCutChunk rows only, the leaves of a star (16 M of them) were
+// searched through memory, call 576 us, now 223.
 constexpr int kCutPer = 4;
 constexpr int kCutChunk = 256 * kCutPer;
-constexpr int kCutRows = 1024;
+constexpr int kCutRows = kCutChunk + 256;
 
 template <typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_cut(int64_t n, int64_t nnz, const IdxT *rp,

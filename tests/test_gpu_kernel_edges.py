@@ -274,3 +274,54 @@ def test_single_column_hub_rows_vs_numpy(handle, leaves, f32):
     bound = 24 * eps * np.bincount(row, np.abs(t), g.n)
     want = np.array([math.fsum(t[a:b]) for a, b in zip(g.rowptr[:-1], g.rowptr[1:])])
     assert np.all(np.abs(y.astype(np.float64) - want) <= bound)
+
+
+@pytest.mark.parametrize("wd", [None, np.float64])
+def test_cut_from_chunk_to_chunk_vs_numpy(handle, wd):
+    """More than 2 x 2048 chunks of 1024 entries, so that every block goes over
+    several: a row of five whole chunks that ends with one, 3000 empty rows
+    behind it, rows of one entry (1024 to a chunk, 1280 staged) with none, one
+    in 5 and one in 3 empty between them, runs of 40,000 empty rows between
+    chunks and inside them, and rows of 2 and 3 entries.  Weights are multiples
+    of 1/8, so numpy's sums are exact."""
+    import graphgen
+    import torch
+    import paper_2105_00578_amd as sx
+    rng = np.random.default_rng(11)
+    u, v, n = [], [], 0
+
+    def pairs(ids):
+        u.append(ids[0::2])
+        v.append(ids[1::2])
+
+    hub = 5 * 1024                    # vertex 0 and its leaves, 3000 rows further on
+    u.append(np.zeros(hub, dtype=np.int64))
+    v.append(3001 + np.arange(hub))
+    n = 3001 + hub
+    for every in (0, 5, 3):           # rows of one entry, each `every`-th row empty
+        ids = n + np.arange(1_200_000)
+        n += ids.size
+        if every:
+            ids = ids[np.arange(ids.size) % every != 0]
+        pairs(ids[:ids.size // 2 * 2])
+    for size in (1024, 1500, 1024, 2048, 3000):
+        n += 40_000                   # a run of empty rows
+        pairs(n + np.arange(size))
+        n += size
+    path = n + np.arange(900_000)     # rows of 2 entries, and of 3 where chords end
+    u += [path[:-1], path[:-7:11]]
+    v += [path[1:], path[:-7:11] + 5]
+    n += path.size + 2000             # empty rows at the end
+    u, v = np.concatenate(u), np.concatenate(v)
+    w = None if wd is None else (rng.integers(1, 64, u.size) / 8).astype(wd)
+    g = graphgen.csr_from_edges(n, u, v, w)
+    assert g.col.size > 2 * 2048 * 1024
+    for rpt in (np.int32, np.int64):
+        G = sx.Graph(handle, torch.from_numpy(g.rowptr.astype(rpt)),
+                     torch.from_numpy(g.col.astype(np.int32)),
+                     None if w is None else torch.from_numpy(g.w), validate=True)
+        part = rng.integers(0, 7, n).astype(np.int32)
+        cross = part[u] != part[v]
+        want = float(cross.sum()) if w is None else float(w[cross].sum())
+        cut, _, _, pw = sx.quality(handle, G, torch.from_numpy(part).cuda(), 7)
+        assert cut == want and pw == np.bincount(part, minlength=7).tolist()
