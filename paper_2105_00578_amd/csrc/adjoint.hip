@@ -28,7 +28,7 @@
 // Laplacian kernel with the shift lam_k B and the dots p^T A p fused into its
 // epilogue.  The CG scalars (r^T z, alpha, beta, convergence flags) live on
 // the device and are computed by one-block reductions in a fixed order; the
-// host reads the flags of a batch of kCgCheck steps while the next batch runs.
+// host reads the flags of a batch of steps while the next batch runs.
 // Convergence: the relative residual in the preconditioner's norm,
 // sqrt(r^T z / f^T J f) <= cg_tol; a converged column no longer moves.
 #include <algorithm>
@@ -524,7 +524,16 @@ __global__ __launch_bounds__(256) void k_add_vertex_terms(int64_t n, const IdxT 
 }
 
 constexpr int kSmallBlocks = 1024;
-constexpr int kCgCheck = 8;   // CG steps between host reads of the flags
+// CG steps between host reads of the flags, at most.  A batch costs some 10 us
+// beside its steps; the flags are read one batch behind, so up to two batches
+// are run past convergence, at full cost.  The first batches are short (2 steps
+// up to step 8, 4 up to step 16: they may be the only ones), and so are all of
+// them where a step takes longer than 10 such batches, from kCgLarge values per
+// block on.  With 8 steps throughout: 2 M rows, 7 steps needed, 1 column
+// 3.10 ms, now 2.69; 9 columns 19.7 ms, now 15.6; 31,680 rows, 2 steps needed,
+// 5 columns 0.56 ms, now 0.31.
+constexpr int kCgCheck = 8;
+constexpr int64_t kCgLarge = 1 << 22;
 
 }  // namespace
 
@@ -675,7 +684,7 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
     ep.lam = lam_dev;
     int cur = 0;
     step_tail(0, cur);
-    // Batches of kCgCheck steps; the state after a batch is copied to pinned
+    // Batches of up to kCgCheck steps; the state after a batch is copied to pinned
     // memory behind it and read while the next batch runs (steps past the
     // last column's convergence leave x as it is).
     struct Events {
@@ -693,11 +702,13 @@ int eig_backward(sphx_graph *g, const SpmmPlan &plan, int problem, int nev,
     static_assert(2 * sizeof(CgState) <= kPinnedSmallBytes, "pinned states");
     CgState *hp = static_cast<CgState *>(pinned);
     CgState hs{};
+    const bool large = n * ld >= kCgLarge;
     int it = 0, batches = 0, seen = 0;
     bool all = false;
     while (seen < batches || it < cg_max_iter) {
       if (it < cg_max_iter) {
-        const int steps = std::min(kCgCheck, cg_max_iter - it);
+        const int batch = large || it < 8 ? 2 : (it < 16 ? 4 : kCgCheck);
+        const int steps = std::min(batch, cg_max_iter - it);
         for (int q = 0; q < steps; ++q) {
           int np = 0;
           int r = vspmm_shiftdot<double>(g, plan, Pp, ld, nev, ep, pap_parts, &np, s);
