@@ -40,7 +40,7 @@ struct SpmmPlan {
   const int32_t *hub_rows = nullptr;     // hub rows
   int64_t n_hub = 0;
   const int64_t *chunk_k0 = nullptr;     // per chunk: first entry
-  const int64_t *chunk_k1 = nullptr;     // per chunk: one past last entry
+  const int32_t *chunk_row = nullptr;    // per chunk: its row
   const int32_t *hub_chunk_begin = nullptr;  // per hub: first chunk (n_hub+1)
   int64_t n_chunks = 0;                  // at most (hub_chunk_begin[n_hub] of them)
   double *hub_partial = nullptr;         // n_chunks * kMaxNev scratch (T-sized)

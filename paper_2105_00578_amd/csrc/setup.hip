@@ -282,10 +282,10 @@ __global__ __launch_bounds__(1024) void k_bin_scan(int nblocks, int *counts, int
 }
 
 // Chunk table of the hub rows (one block): begin[h] is hub h's first chunk
-// (begin[nh] the number of chunks), k0 / k1 a chunk's entries.
+// (begin[nh] the number of chunks), k0 and row a chunk's first entry and its row.
 template <typename IdxT>
 __global__ __launch_bounds__(1024) void k_hub_table(const IdxT *rp, const int32_t *hubs, int nh,
-                                                    int32_t *begin, int64_t *k0, int64_t *k1) {
+                                                    int32_t *begin, int64_t *k0, int32_t *row) {
   __shared__ int sh[1024];
   const int t = threadIdx.x;
   int base = 0;
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(1024) void k_hub_table(const IdxT *rp, const int32_
       begin[h] = at;
       for (int q = 0; q < cnt; ++q) {
         k0[at + q] = b + (int64_t)q * kHubChunk;
-        k1[at + q] = min(e, b + (int64_t)(q + 1) * kHubChunk);
+        row[at + q] = hubs[h];
       }
     }
     base += sh[1023];
@@ -789,7 +789,8 @@ size_t plan_bytes(sphx_graph *g) {
   size_t b = 0;
   b += align_up(sizeof(int32_t) * n, 256);              // packed class lists
   b += align_up(sizeof(int32_t) * (max_hub + 1), 256);  // hub chunk begin
-  b += align_up(sizeof(int64_t) * max_chunks, 256) * 2; // chunk ranges
+  b += align_up(sizeof(int64_t) * max_chunks, 256) +    // chunks: first entries
+       align_up(sizeof(int32_t) * max_chunks, 256);     // and rows
   b += align_up(sizeof(double) * max_chunks * kMaxNev, 256);
   b += align_up(sizeof(int) * (nb * kNumCls + kNumCls), 256);
   if (may_compress(g)) b += align_up(sizeof(int16_t) * g->nnz, 256) + 256;
@@ -806,7 +807,7 @@ int build_plan(sphx_graph *g, Arena &ws, SpmmPlan *plan, const DegreeStats &st,
   int32_t *packed = ws.take<int32_t>(n);
   int32_t *hcb = ws.take<int32_t>(max_hub + 1);
   int64_t *k0 = ws.take<int64_t>(max_chunks);
-  int64_t *k1 = ws.take<int64_t>(max_chunks);
+  int32_t *krow = ws.take<int32_t>(max_chunks);
   double *hp = ws.take<double>(max_chunks * kMaxNev);
   int *counts = ws.take<int>(nb * kNumCls + kNumCls);
   if (st.max_deg <= kUnbinnedMaxDeg) {   // natural order, one group size
@@ -860,16 +861,16 @@ int build_plan(sphx_graph *g, Arena &ws, SpmmPlan *plan, const DegreeStats &st,
   plan->n_hub = th[kNumBins];
   plan->hub_chunk_begin = hcb;
   plan->chunk_k0 = k0;
-  plan->chunk_k1 = k1;
+  plan->chunk_row = krow;
   plan->hub_partial = hp;
   if (plan->n_hub > 0) {
     plan->n_chunks = max_chunks;
     if (g->rp64)
       hipLaunchKernelGGL((k_hub_table<int64_t>), dim3(1), dim3(1024), 0, s,
-                         (const int64_t *)g->rowptr, l2, (int)plan->n_hub, hcb, k0, k1);
+                         (const int64_t *)g->rowptr, l2, (int)plan->n_hub, hcb, k0, krow);
     else
       hipLaunchKernelGGL((k_hub_table<int32_t>), dim3(1), dim3(1024), 0, s,
-                         (const int32_t *)g->rowptr, l2, (int)plan->n_hub, hcb, k0, k1);
+                         (const int32_t *)g->rowptr, l2, (int)plan->n_hub, hcb, k0, krow);
     SPHX_HIP(g->h, hipGetLastError());
   }
   return SPHX_OK;

@@ -124,22 +124,16 @@ __global__ __launch_bounds__(256) void k_spmm_wave(Csr<IdxT, WT> A,
 // out[q]: the sum of chunk q
 template <typename T, typename IdxT, typename WT>
 __global__ __launch_bounds__(256) void k_spmm_hub_partial(
-    Csr<IdxT, WT> A, const int32_t *__restrict__ hub_rows,
-    const int32_t *__restrict__ hub_chunk_begin, int64_t n_hub,
-    const int64_t *__restrict__ k0s, const int64_t *__restrict__ k1s,
+    Csr<IdxT, WT> A, const int32_t *__restrict__ hub_chunk_begin, int64_t n_hub,
+    const int64_t *__restrict__ k0s, const int32_t *__restrict__ chunk_row,
     const T *__restrict__ X, double *out) {
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t n_chunks = hub_chunk_begin[n_hub];
   for (int64_t q = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave; q < n_chunks;
        q += (int64_t)gridDim.x * 4) {
-    // hub row owning chunk q: last h with hub_chunk_begin[h] <= q
-    int64_t lo = 0, hi = n_hub - 1;
-    while (lo < hi) {
-      int64_t mid = (lo + hi + 1) / 2;
-      if (hub_chunk_begin[mid] <= q) lo = mid; else hi = mid - 1;
-    }
-    const T xi = X[hub_rows[lo]];
-    const T tot = wave_total(row_acc<T>(A, k0s[q] + lane, k1s[q], kWave, X, xi));
+    const int64_t i = chunk_row[q], k0 = k0s[q];
+    const int64_t k1 = min(k0 + kHubChunk, (int64_t)A.rp[i + 1]);
+    const T tot = wave_total(row_acc<T>(A, k0 + lane, k1, kWave, X, X[i]));
     if (lane == 0) out[q] = double(tot);
   }
 }
@@ -189,8 +183,8 @@ void run_all(const Csr<IdxT, WT> &A, int64_t n, const SpmmPlan &plan, const T *X
   if (plan.n_hub > 0) {
     hipLaunchKernelGGL((k_spmm_hub_partial<T, IdxT, WT>),
                        dim3(grid_for(plan.n_chunks, 4, kWaveBlocks)), dim3(256), 0, s, A,
-                       plan.hub_rows, plan.hub_chunk_begin, plan.n_hub, plan.chunk_k0,
-                       plan.chunk_k1, X, plan.hub_partial);
+                       plan.hub_chunk_begin, plan.n_hub, plan.chunk_k0, plan.chunk_row, X,
+                       plan.hub_partial);
     hipLaunchKernelGGL((k_spmm_hub_combine<T, Epi>), dim3(grid_for(plan.n_hub, 4, kHubBlocks)),
                        dim3(256), 0, s, plan.hub_rows, plan.hub_chunk_begin, plan.n_hub,
                        (const double *)plan.hub_partial, X, epi);

@@ -119,7 +119,15 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t nb) {
 // acc = sum over entries k0, k0 + step, ... < k1 of w_k (x_i - x_col[k]).
 // U independent partial sums (U gathers in flight per lane), combined in a
 // fixed order.
-template <typename T, int VB, int NV, typename WT, typename Src>
+// kWhole: the vectors of a neighbour row are loaded one behind the other.  Left
+// to itself the compiler loads the first vectors of all U rows and then the last
+// ones, whose address it forms later; where the neighbours of 64 lanes are
+// anywhere (binned plans), U x 64 lines of 128 bytes are the whole of a compute
+// unit's L1, and the last vectors are fetched from L2 again: store product of 5
+// FP32 columns on R-MAT 22 1347 us, with whole rows 1094; R-MAT 17 37.4 and 30.4.
+// On meshes the lines stay, and the order costs the 27-point mesh's 5 FP64
+// columns 2 %.
+template <typename T, int VB, int NV, typename WT, bool kWhole, typename Src>
 __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, int64_t k1,
                                          int step, const T *__restrict__ X, int ld, int last,
                                          const typename Vec<T, VB>::type (&xi)[NV],
@@ -138,7 +146,10 @@ __device__ __forceinline__ void vrow_acc(const Src &A, int64_t i, int64_t k0, in
     for (int u = 0; u < U; ++u) j[u] = A.nbr(i, k + u * step);
     V x[U][NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_row<T, VB, NV>(X + j[u] * ld, last, x[u]);
+    for (int u = 0; u < U; ++u) {
+      load_row<T, VB, NV>(X + j[u] * ld, last, x[u]);
+      if constexpr (kWhole && NV > 1) __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if constexpr (kUnitW<WT>) {
@@ -404,7 +415,7 @@ __global__ __launch_bounds__(256) void k_vrow(Csr<IdxT, WT> A, int64_t nrows,
     if (i >= nrows) break;
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
-    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, Xs, ld, last, xi, acc);
+    vrow_acc<T, VB, NV, WT, false>(A, i, (int64_t)A.rp[i], (int64_t)A.rp[i + 1], 1, Xs, ld, last, xi, acc);
     epi.row(i, xi, acc, n1, n2);
   }
   if constexpr (Epi::kNorms)
@@ -450,7 +461,7 @@ __global__ __launch_bounds__(256) void k_vgroup(Csr<IdxT, WT> A, int64_t nrows,
   for (int64_t i = b * rpb + threadIdx.x / G; i < rend; i += GPB) {
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
-    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last, xi, acc);
+    vrow_acc<T, VB, NV, WT, false>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last, xi, acc);
     group_sum<T, VB, NV, G>(acc);
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
   }
@@ -530,9 +541,9 @@ __global__ __launch_bounds__(kLdsThreads) void k_vlds(Csr<IdxT, WT> A, int64_t n
       const int64_t ka = (int64_t)A.rp[i] + gl, kb = (int64_t)A.rp[i + 1];
       if (staged) {
         const L S{scol, sw, k0};
-        vrow_acc<T, VB, NV, WT>(S, i, ka, kb, G, Xs, ld, last, xi, acc);
+        vrow_acc<T, VB, NV, WT, false>(S, i, ka, kb, G, Xs, ld, last, xi, acc);
       } else {
-        vrow_acc<T, VB, NV, WT>(A, i, ka, kb, G, Xs, ld, last, xi, acc);
+        vrow_acc<T, VB, NV, WT, false>(A, i, ka, kb, G, Xs, ld, last, xi, acc);
       }
       group_sum<T, VB, NV, G>(acc);
       if (gl == 0) epi.row(i, xi, acc, nullptr, nullptr);
@@ -545,7 +556,14 @@ __global__ __launch_bounds__(kLdsThreads) void k_vlds(Csr<IdxT, WT> A, int64_t n
 // blocks take the chunks of the hub rows, then the row classes from the
 // widest group down, so that the long rows start first and the short ones
 // fill the chip behind them (one launch per class ran them one after the
-// other: 24 products of 5 FP32 columns on R-MAT 17 took 2.3 ms, now 1.03).
+// other: 24 products of 5 FP32 columns on R-MAT 17 took 2.3 ms, now 0.9).
+// On 4 M rows, where each class fills the chip, that wins little: R-MAT 22, 5
+// columns, one launch per class and then this one: FP32 store 1195 and 1094 us,
+// residual 1380 and 1192; FP64 store 1610 and 1655 (7 columns 1552 and 1661),
+// residual 1843 and 1715.  This kernel class by class is slower than at once at
+// every size (R-MAT 22, FP32 store 1415 instead of 1347 before rows were loaded
+// whole), and hubs from 16384 neighbours on gain 2 % there and lose half of the
+// speed on R-MAT 17, so there is no rule on sizes.
 // Hub chunks write partial row sums (as double), which k_vhub_combine adds.
 struct BinRows {
   const int32_t *rows[kNumBins];
@@ -553,7 +571,8 @@ struct BinRows {
   unsigned end[kNumBins + 1];     // end[0]: hub blocks; then class 3, 2, 1, 0
   const int32_t *hub_rows, *hub_chunk_begin;
   int64_t n_hub;
-  const int64_t *k0, *k1;
+  const int64_t *k0;
+  const int32_t *chunk_row;
   double *hub_partial;
 };
 
@@ -571,7 +590,7 @@ __device__ __forceinline__ void bin_rows(const Csr<IdxT, WT> &A, const int32_t *
     const int64_t i = rows[r];
     V xi[NV], acc[NV];
     load_row<T, VB, NV>(Xs + i * ld, last, xi);
-    vrow_acc<T, VB, NV, WT>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last,
+    vrow_acc<T, VB, NV, WT, true>(A, i, (int64_t)A.rp[i] + gl, (int64_t)A.rp[i + 1], G, Xs, ld, last,
                             xi, acc);
     if constexpr (G > 1) group_sum<T, VB, NV, G>(acc);
     if (gl == 0) epi.row(i, xi, acc, n1, n2);
@@ -592,15 +611,11 @@ __global__ __launch_bounds__(256) void k_vbin(Csr<IdxT, WT> A, BinRows B,
     const int64_t n_chunks = B.hub_chunk_begin[B.n_hub];
     for (int64_t q = (int64_t)b * 4 + (threadIdx.x >> 6); q < n_chunks;
          q += (int64_t)B.end[0] * 4) {
-      int64_t lo = 0, hi = B.n_hub - 1;
-      while (lo < hi) {
-        int64_t mid = (lo + hi + 1) / 2;
-        if (B.hub_chunk_begin[mid] <= q) lo = mid; else hi = mid - 1;
-      }
-      const int64_t i = B.hub_rows[lo];
+      const int64_t i = B.chunk_row[q], k0 = B.k0[q];
+      const int64_t k1 = min(k0 + kHubChunk, (int64_t)A.rp[i + 1]);
       V xi[NV], acc[NV];
       load_row<T, VB, NV>(Xs + i * ld, last, xi);
-      vrow_acc<T, VB, NV, WT>(A, i, B.k0[q] + lane, B.k1[q], 64, Xs, ld, last, xi, acc);
+      vrow_acc<T, VB, NV, WT, true>(A, i, k0 + lane, k1, 64, Xs, ld, last, xi, acc);
       group_sum<T, VB, NV, 64>(acc);
       if (lane == 0)
 #pragma unroll
@@ -821,7 +836,7 @@ void run_vec(const Csr<IdxT, WT> &A, int64_t n, int64_t max_deg, const SpmmPlan 
     B.hub_chunk_begin = plan.hub_chunk_begin;
     B.n_hub = plan.n_hub;
     B.k0 = plan.chunk_k0;
-    B.k1 = plan.chunk_k1;
+    B.chunk_row = plan.chunk_row;
     B.hub_partial = plan.hub_partial;
     // n_chunks is an upper bound: blocks without a chunk end at once
     B.end[0] = plan.n_hub > 0 ? grid_for(plan.n_chunks, 4, kBinBlocks) : 0;
