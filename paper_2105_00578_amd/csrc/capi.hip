@@ -971,7 +971,7 @@ int sphx_workspace_size(sphx_handle *h, sphx_graph *g, int nev, const sphx_optio
   if (!h || !g || !opt || !bytes || nev < 1 || nev > kMaxNev) return SPHX_E_INVALID_ARG;
   // every partition into d = nev coordinates has floor(log2 K) + 1 = nev: the
   // quality scratch grows with K, the split's does not (it depends on how K
-  // factors), so its largest over those K is taken
+  // factors), so a bound of it over those K is taken
   const int K = (1 << nev) - 1;
   size_t a = solve_bytes(g, nev, opt->precision, K, split_scratch_max(g->n, 1 << (nev - 1), K),
                          poly_degree_of(opt), ord_bytes_of(g, opt));

@@ -278,7 +278,7 @@ void launch_copy_cols(const T *in, int ldin, T *out, int ldout, int64_t n,
 
 // ------------------------------------------------------------------ split
 size_t split_scratch_bytes(int64_t n, int K);
-// the largest split_scratch_bytes(n, K) over K = klo .. khi
+// a bound of split_scratch_bytes(n, K) for K = klo .. khi
 size_t split_scratch_max(int64_t n, int klo, int khi);
 template <typename T>
 int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K,

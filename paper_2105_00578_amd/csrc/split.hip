@@ -769,9 +769,9 @@ static bool fast_levels(const std::vector<int> &counts, int64_t n = 0, int ncoor
   return !counts.empty();
 }
 
-size_t split_scratch_bytes(int64_t n, int K) {
-  // targets of a level (nsec * (p - 1)), sections and children all fit in K
-  int64_t ns = K < 1 ? 1 : K;
+// of the radix passes: targets of a level (nsec * (p - 1)), sections and
+// children all fit in K
+static size_t radix_bytes(int64_t n, int64_t ns) {
   size_t b = 0;
   b += align_up(sizeof(uint64_t) * n, 256);                 // keys
   b += align_up(sizeof(unsigned long long) * ns * 256, 256); // hist (one row per target)
@@ -780,29 +780,37 @@ size_t split_scratch_bytes(int64_t n, int K) {
   b += align_up(sizeof(long long) * ns, 256) * 4;           // base, wstar, W, lo
   b += align_up(sizeof(long long) * ns, 256);               // Wnext
   b += align_up(sizeof(int) * ns, 256);                     // incl
-  size_t f = 0;                                             // sample bins
-  if (fast_levels(section_counts((int)ns))) {
-    f += align_up(sizeof(uint64_t) * n, 256);               // keys
-    f += align_up(sizeof(uint16_t) * n, 256);               // bins
-    f += align_up(sizeof(uint32_t) * (4 * n + 256 * ns), 256);   // candidates
-    f += align_up(sizeof(unsigned long long) * kBins, 256);
-    f += align_up(sizeof(uint64_t) * kSample * 64, 256) +   // samples: a coordinate per level
-         align_up(sizeof(uint32_t) * kSample * 64, 256);
-    f += 2 * (align_up(sizeof(uint64_t) * ns, 256) * 3 + align_up(sizeof(int) * ns, 256) * 2);
-    f += align_up(sizeof(int) * ns, 256) + align_up(sizeof(long long) * ns, 256) +
-         align_up(sizeof(int) * ns * kSub * kSubStride, 256);
-  }
-  return std::max(b, f) + 1024;
+  return b + 1024;
 }
 
-// The radix passes' part grows with K, and so does the sample bins' over the
-// K that have it; these are at most kFastSections * p with
-// kFastSections * (p - 1) <= kFastTargets.
+// of the sample bins
+static size_t bins_bytes(int64_t n, int64_t ns) {
+  size_t f = 0;
+  f += align_up(sizeof(uint64_t) * n, 256);               // keys
+  f += align_up(sizeof(uint16_t) * n, 256);               // bins
+  f += align_up(sizeof(uint32_t) * (4 * n + 256 * ns), 256);   // candidates
+  f += align_up(sizeof(unsigned long long) * kBins, 256);
+  f += align_up(sizeof(uint64_t) * kSample * 64, 256) +   // samples: a coordinate per level
+       align_up(sizeof(uint32_t) * kSample * 64, 256);
+  f += 2 * (align_up(sizeof(uint64_t) * ns, 256) * 3 + align_up(sizeof(int) * ns, 256) * 2);
+  f += align_up(sizeof(int) * ns, 256) + align_up(sizeof(long long) * ns, 256) +
+       align_up(sizeof(int) * ns * kSub * kSubStride, 256);
+  return f + 1024;
+}
+
+size_t split_scratch_bytes(int64_t n, int K) {
+  const int ns = K < 1 ? 1 : K;
+  const size_t b = radix_bytes(n, ns);
+  return fast_levels(section_counts(ns)) ? std::max(b, bins_bytes(n, ns)) : b;
+}
+
+// Both parts grow with K, but the sample bins' is only there for some K: for at
+// most kFastSections * p parts with kFastSections * (p - 1) <= kFastTargets.
+// (Callers ask for sizes before every call, so the factors of the K between
+// are not looked at: a bound.)
 size_t split_scratch_max(int64_t n, int klo, int khi) {
-  size_t b = split_scratch_bytes(n, khi);
-  for (int k = std::min(khi, kFastTargets + kFastSections); k >= klo; --k)
-    if (fast_levels(section_counts(k))) return std::max(b, split_scratch_bytes(n, k));
-  return b;
+  const int kf = std::min(khi, kFastTargets + kFastSections);
+  return std::max(radix_bytes(n, khi), kf >= klo ? bins_bytes(n, kf) : 0);
 }
 
 // The levels by sample bins.  *flags: F_NAN, F_CROWDED (part is then not
