@@ -185,6 +185,14 @@ struct Arena {
   }
 };
 
+// Orders the LDS accesses of one wavefront before and after it: they complete in
+// order, so this only keeps the compiler from moving them (no instructions).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Launch helper: grid size for n items with `per_block` items per block,
 // capped so that grid-stride loops cover the rest.
 inline unsigned grid_for(int64_t n, int64_t per_block, int64_t cap = 1 << 20) {

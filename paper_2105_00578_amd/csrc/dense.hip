@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kRRThreads) void k_rr(const double *__restrict__ gr
           ipiv[p] = k;
         }
         // one wave: its LDS writes are read in order by the next step
-        __builtin_amdgcn_wave_barrier();
+        wave_order();
       }
       if (t == 0) rank = k;
     } else {

@@ -335,7 +335,7 @@ __global__ __launch_bounds__(1024) void k_sample(const T *coords, int ld, int64_
   for (int w = 2; w <= kSample; w <<= 1)
     for (int j = w >> 1; j >= 1; j >>= 1) {
       if (wide || j > 64) __syncthreads();
-      else __builtin_amdgcn_wave_barrier();
+      else wave_order();
       wide = j > 64;
       const int a = 2 * t - (t & (j - 1)), b = a + j;   // pairs j apart
       const bool up = (a & w) == 0;
