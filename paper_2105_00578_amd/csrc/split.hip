@@ -26,9 +26,9 @@
 // composite order, so ties and any distribution of the values are as good as
 // another, unless the levels before have cut a section out of few of its
 // coordinate's bins: a target whose bin is too full for its list raises a flag,
-// the levels after it do nothing, and the radix passes over all members (in
-// split_mj, also for more sections or cuts, and where fast_levels expects such
-// bins) are run instead.  2 M members, K = 64, FP32: 1.13 ms by the radix
+// its level and those after select nothing, and the radix passes over all members
+// (in split_mj, also for more sections or cuts, and where fast_levels expects
+// such bins) are run instead.  2 M members, K = 64, FP32: 1.13 ms by the radix
 // passes (8 per level, each over all members, the first ones with most
 // members in a few counters), 0.35 ms by sample bins, of which the strided
 // reads of the coordinates take about a third.
@@ -95,9 +95,6 @@ __device__ __forceinline__ bool prefix_match(K ord, uint32_t id, K pord, uint32_
   uint32_t mask = dd >= 4 ? ~0u : (~0u << (8 * (4 - dd)));
   return (id & mask) == pid;
 }
-
-// flags of the sample bins: NaN coordinate, a bin too full for one workgroup
-enum : int { F_NAN = 1, F_CROWDED = 2 };
 
 // Up to 32 targets count in LDS first (16 or 32 rows of 256 bins), more in
 // global memory.
@@ -225,14 +222,10 @@ __global__ void k_finish_sections(int nsec, int p, const long long *lo, const lo
   }
 }
 
-// child = number of cuts of the member's section that it lies after; nothing
-// where the levels before were given up (flag, or null): part may then hold no
-// sections
+// child = number of cuts of the member's section that it lies after
 template <typename K>
 __global__ void k_assign(int64_t n, const K *keys, int32_t *part, int p, const K *pord,
-                         const uint32_t *pid, const int *incl, const long long *W,
-                         const int *flag) {
-  if (flag && (*flag & F_CROWDED)) return;
+                         const uint32_t *pid, const int *incl, const long long *W) {
   const int pm = p - 1;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -292,15 +285,17 @@ constexpr int kCutThreads = 1024;
 // Candidates of a target are appended through kSub counters, a cache line
 // each, to kSub runs of its list: appends to one counter go one after the
 // other at about 0.2 us (with one counter per target the pass over 2 M members
-// took 218 us).  A hash of the member's id chooses the run, and a full run
-// passes the member on to the next one, so that the whole list is a target's
-// room wherever its members lie (with the run chosen by the block, lattices in
-// natural order, whose late sections lie in few blocks, filled single runs and
-// ran into the radix passes: 30,000 vertices, K = 256, FP32 880 us).
-constexpr int kSub = 32, kSubBits = 5;
-static_assert(kSub == 1 << kSubBits, "runs are chosen by kSubBits of a hash");
+// took 218 us).  A block has its run, so that neighbouring members share lines
+// of the list (runs chosen by a hash of the id: 14.5 instead of 9.4 us); a full
+// run passes the member on to the next, so that the whole list is a target's
+// room wherever its members lie (without that, lattices in natural order, whose
+// late sections lie in few blocks, ran into the radix passes: 16,000 vertices,
+// K = 256, FP32 910 us, now 289).
+constexpr int kSub = 32;
 constexpr int kSubStride = 16;
+enum : int { F_NAN = 1, F_CROWDED = 2 };
 
+// splitmix64 (Steele, Lea, Flood 2014)
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   z += 0x9E3779B97F4A7C15ull;
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -384,7 +379,6 @@ __global__ __launch_bounds__(512) void k_level(const T *__restrict__ coords, int
   __shared__ K so[kSample];
   __shared__ uint32_t si[kSample];
   __shared__ H h[kBins];
-  const int stop = *flag & F_CROWDED;       // (set by the levels before only)
   for (int q = threadIdx.x; q < B - 1; q += 512) {
     const int at = (int)((int64_t)(q + 1) * kSample / B);
     so[q] = sord[at];
@@ -392,7 +386,6 @@ __global__ __launch_bounds__(512) void k_level(const T *__restrict__ coords, int
   }
   for (int q = threadIdx.x; q < B * nsec; q += 512) h[q] = 0;
   __syncthreads();
-  if (stop) return;
   bool nan = false;
   for (int64_t i = (int64_t)blockIdx.x * 512 + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * 512) {
@@ -486,42 +479,38 @@ __global__ __launch_bounds__(256) void k_find_bins(int B, int p, Cuts<K> prev, l
   }
 }
 
-// The members of every target's bin (in no particular order); cap: of a run.
-// Does nothing once a bin was too full (the levels are then not used).
+// the members of every target's bin (in no particular order); cap: of a run
 __global__ __launch_bounds__(256) void k_candidates(int64_t n, const uint16_t *__restrict__ bins,
                                                     const int32_t *__restrict__ part, int first,
                                                     int p, int ntgt, const int *__restrict__ tbin,
                                                     int cap, int *cnt, uint32_t *list,
                                                     int *flag) {
   __shared__ int tb[kFastTargets];
-  __shared__ int stop;            // one reading for the block: others may set it
-  if (threadIdx.x == 0) stop = *flag & F_CROWDED;
   for (int q = threadIdx.x; q < ntgt; q += 256) tb[q] = tbin[q];
   __syncthreads();
-  if (stop) return;
   const int pm = p - 1;
+  // appends member i to run `run` of target t, unless it is full
+  auto append = [&](int t, unsigned run, uint32_t i) {
+    const int64_t r = (int64_t)t * kSub + run;
+    const int at = atomicAdd(&cnt[r * kSubStride], 1);
+    if (at < cap) list[r * cap + at] = i;
+    return at < cap;
+  };
+  const unsigned own = blockIdx.x & (kSub - 1);
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * 256) {
     const int b = bins[i], t0 = (first ? 0 : part[i]) * pm;
     for (int j = 0; j < pm; ++j)
-      if (tb[t0 + j] == b) {
-        const unsigned r0 = ((uint32_t)i * 0x9E3779B1u) >> (32 - kSubBits);   // Fibonacci hash
-        unsigned q = 0;
+      if (tb[t0 + j] == b && !append(t0 + j, own, (uint32_t)i)) {
+        unsigned q = 1;
         for (; q < kSub; ++q) {
-          const int64_t run = (int64_t)(t0 + j) * kSub + ((r0 + q) & (kSub - 1));
-          if (q && __hip_atomic_load(&cnt[run * kSubStride], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT) >= cap)
-            continue;                                            // full already
-          const int at = atomicAdd(&cnt[run * kSubStride], 1);
-          if (at < cap) {
-            list[run * cap + at] = (uint32_t)i;
-            break;
-          }
+          const unsigned run = (own + q) & (kSub - 1);
+          const int have =
+              __hip_atomic_load(&cnt[((int64_t)(t0 + j) * kSub + run) * kSubStride],
+                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (have < cap && append(t0 + j, run, (uint32_t)i)) break;
         }
-        if (q == kSub) {
-          atomicOr(flag, F_CROWDED);
-          return;
-        }
+        if (q == kSub) atomicOr(flag, F_CROWDED);
       }
   }
 }
@@ -893,7 +882,7 @@ static int split_levels(sphx_graph *g, const T *coords, int ld, int ncoord, int 
   const Cuts<KT> &z = cut[(nlev - 1) & 1];
   if (nlev == 1) hipLaunchKernelGGL(k_zero_parts, dim3(gn), dim3(256), 0, s, n, part);
   hipLaunchKernelGGL((k_assign<KT>), dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n, keys,
-                     part, z.p, z.ord, z.id, z.incl, z.W, (const int *)flag);
+                     part, z.p, z.ord, z.id, z.incl, z.W);
   if (hipGetLastError() != hipSuccess) {
     *err = "split kernel launch failed";
     return SPHX_E_HIP;
@@ -973,7 +962,7 @@ int split_mj(sphx_graph *g, const T *coords, int ld, int ncoord, int K, int32_t 
     hipLaunchKernelGGL(k_finish_sections, dim3(grid_for(nsec, 256, 1 << 16)), dim3(256), 0, s,
                        nsec, p, lo, W, Wnext);
     hipLaunchKernelGGL((k_assign<KT>), dim3(gn), dim3(256), 0, s, n, keys, part, p, pord, pid,
-                       incl, W, (const int *)nullptr);
+                       incl, W);
     nsec *= p;
     ok &= hipMemcpyAsync(W, Wnext, sizeof(long long) * nsec, hipMemcpyDeviceToDevice, s) ==
           hipSuccess;
