@@ -913,7 +913,6 @@ __global__ __launch_bounds__(kJacobiThreads) void k_harmonic_ritz(const double *
 struct UpdDev {
   int64_t n;
   int m, ld;
-  int na;
   int pos[kMaxNev];   // column -> position among the active ones, or -1
   int use_h, use_p;
   int offH, offP;     // rows of Y for the H and P parts
@@ -1309,13 +1308,13 @@ int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
   d.n = a.n;
   d.m = a.m;
   d.ld = a.ld;
-  d.na = a.act.count;
+  const int na = a.act.count;
   for (int c = 0; c < kMaxNev; ++c) d.pos[c] = -1;
-  for (int q = 0; q < d.na; ++q) d.pos[a.act.col[q]] = q;
-  d.use_h = a.use_h && d.na > 0;
-  d.use_p = a.use_p && d.na > 0;
+  for (int q = 0; q < na; ++q) d.pos[a.act.col[q]] = q;
+  d.use_h = a.use_h && na > 0;
+  d.use_p = a.use_p && na > 0;
   d.offH = a.m;
-  d.offP = a.m + (d.use_h ? d.na : 0);
+  d.offP = a.m + (d.use_h ? na : 0);
   d.update_lp = LP != nullptr && (d.use_h || d.use_p);
   if (a.m < 1 || a.m > a.ld) return SPHX_E_INVALID_ARG;
   const unsigned gb = grid_for(a.n, 256, 1 << 16);

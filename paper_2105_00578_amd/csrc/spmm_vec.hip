@@ -1,23 +1,25 @@
-// Laplacian block product Y = L_C X over padded row-major blocks (Eq. 2 with
-// weights, difference form y_i = sum_j w_ij (x_i - x_j)).
+// Laplacian block product Y = L_C X over row-major blocks of at least two
+// columns (Eq. 2 with weights, difference form y_i = sum_j w_ij (x_i - x_j)).
 //
 // A row of ld values is read as NV vectors of E values: vector v starts at
 // value v E, the last one at ld - E, so that a width that is no multiple of E
 // makes the last two overlap (the shared values are computed twice, to the
 // same bits) and nothing outside the row is touched.  Vectors are only aligned
-// to their elements.  The LOBPCG blocks are padded to whole 16-byte vectors;
-// the polynomial's blocks and the caller's have exactly their columns.  Short
-// rows
-// are handled one thread per row: the thread keeps x_i and the NV-vector
-// accumulator in registers and gathers each neighbour row with NV vector
-// loads (adjacent threads take adjacent rows, so on mesh-like graphs the
+// to their elements.  The caller's blocks have exactly their columns; so have
+// the solver's (block_ld) and the polynomials' (compact_ld) where every row has
+// at most 12 neighbours (but for 5 and 6 FP32 columns of the solver's, which
+// are padded), elsewhere the solver's rows are whole 16-byte vectors and the
+// polynomials' an even number of values; the adjoint's are always padded.
+// Short rows are handled one thread per row: the thread keeps x_i and the
+// NV-vector accumulator in registers and gathers each neighbour row with NV
+// vector loads (adjacent threads take adjacent rows, so on mesh-like graphs the
 // gathers of a wavefront are contiguous).  Blocks of rows are mapped so that
 // each of the 8 XCDs (hardware places consecutive workgroups round robin on
 // them) works on one contiguous eighth of the rows, which keeps the gathered
 // neighbours of a mesh in that XCD's L2.  Longer rows of power-law graphs use
 // groups of 4, 16 or 64 lanes (lanes over the neighbours, butterfly reduction
-// in a fixed order), hub rows fixed-size chunks combined in a second pass.  All sums are in a
-// fixed order, so results are bitwise reproducible.
+// in a fixed order), hub rows fixed-size chunks combined in a second pass.  All
+// sums are in a fixed order, so results are bitwise reproducible.
 //
 // Epilogues (whole rows): Store, Residual (r = acc - b_i theta_c x_i, output r
 // or the Jacobi step r / d_i, FP64 norm partials of ||r||^2_{B^-1} and
@@ -32,8 +34,8 @@
 namespace sphx {
 namespace {
 
-// Row vectors of VB bytes: 16 (float4 / double2), or 8 (float2) for FP32
-// rows of an even, non-multiple-of-4 width.
+// Row vectors of VB bytes: 16 (float4 / double2), or 8 (float2) for the FP32
+// widths that with_vectors names.
 template <typename T, int VB> struct Vec;
 template <> struct Vec<float, 16> {
   typedef float type __attribute__((ext_vector_type(4)));
@@ -705,9 +707,14 @@ __global__ __launch_bounds__(256) void k_resid_rows(int64_t n, const T *__restri
   block_norms<Vec<T, VB>::E, NV, true>(n1, n2, epi.last, m, partials, (int)blockIdx.x);
 }
 
-// go(VB, NV) for the vectors of a row of ld values.  FP32 rows of 2, 3, 5, 6,
-// 10 or 14 values: 8-byte vectors (no 16-byte vector fits, or 8-byte ones
-// fetch less than overlapping 16-byte ones).
+// go(VB, NV) for the vectors of a row of ld values.  FP32 rows of 2 and 3
+// values hold no 16-byte vector; those of 5, 6, 10 and 14 take 8-byte ones too,
+// whose number of partial sums the solver's results depend on.  Measured
+// against overlapping 16-byte ones (Chebyshev apply, 25 steps): better where
+// lanes read neighbouring rows (2 M-row 7-point grid, 5 columns 944 and 974 us,
+// 9,504-row 27-point brick 166 and 208), worse where the loads or the index
+// stream count (R-MAT 17 945 and 910 us, R-MAT 20 8.0 and 7.7 ms, 512,000-row
+// brick with FP32 weights 1086 and 964 us); 10 and 14 columns within 3 %.
 template <typename T, typename F>
 int with_vectors(int ld, F &&go) {
 #define SPHX_NV(VB_, NV_) \
