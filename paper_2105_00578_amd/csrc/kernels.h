@@ -11,9 +11,10 @@ namespace sphx {
 // below), served by bin_group(c) lanes per row; rows beyond kHubDeg are hubs,
 // split into kHubChunk-entry chunks of one wavefront each.
 // A row served by one wavefront takes degree / 64 dependent trips to memory per
-// lane, so a few long rows decide a product's time: on R-MAT 17 (5 FP32
-// columns) the wavefront rows took 63 of a product's 98 us with hubs above
-// 16384 entries in chunks of 4096; with these limits all rows take 43 us.
+// lane, so a few long rows decide a product's time: with hubs above 16384
+// entries in chunks of 4096 a product of 5 FP32 columns on R-MAT 17 takes 61 us,
+// with these limits 31; on R-MAT 22, which has enough rows of any length, 1033
+// and 1094.
 constexpr int kHubDeg = 1024;
 constexpr int kHubChunk = 512;
 constexpr int kNumBins = 4;
