@@ -912,7 +912,6 @@ __global__ __launch_bounds__(kJacobiThreads) void k_harmonic_ritz(const double *
 // --------------------------------------------------------------- update
 struct UpdDev {
   int64_t n;
-  int m, ld;
   int pos[kMaxNev];   // column -> position among the active ones, or -1
   int use_h, use_p;
   int offH, offP;     // rows of Y for the H and P parts
@@ -924,68 +923,113 @@ struct UpdDev {
 // cache.  Every output is a sum in a fixed order: the H part over the active
 // columns, then the P part, plus the X part over k.  Bound by the blocks'
 // bytes.  With rows and coefficients in LDS each multiply-add waited on two
-// LDS reads: 2 M rows of 7 FP32 columns took 91 us, now 48 (5 passes of
-// 55 MB); 216,000 rows of 5 FP64 columns 21 us, now 15.
-template <typename T, int M>
+// LDS reads; what a row per thread costs instead is registers and lines read in
+// parts, so
+//  - a thread has one row only: over several, the compiler keeps the
+//    coefficients from one to the next, in scalar registers and then in lanes of
+//    vector ones (1306 lane moves among 3856 instructions at 16 FP64 columns);
+//  - FP32 and padded rows form P, then X, then L P, each from its own loads
+//    (kPhased); FP64 rows of exactly M values load X, H and P at once, up to 8
+//    columns also L H and L P (kFront: small solves are bound by latency);
+//  - padded rows (LD > M) are read and written whole by 16-byte accesses, the
+//    padding as zeros: their M values alone were written as parts of lines.
+// us per update, with LDS, with all rows in registers, and now: 2 M rows of 7
+// FP32 columns 90, 48, 45; of 16 FP64 columns 431, 561, 385; 860,000 rows (R-MAT
+// 20) of 5 FP32 columns 33.8, 23.7, 20.9; of 16 FP64 columns 152, 209, 141.  On
+// 190,000 rows (R-MAT 18), which the cache holds, 14 and 16 FP64 columns take
+// 39.5, 50.8, 48.1 and 46.2, 73.8, 48.8.
+template <typename T, int LD>
+__device__ __forceinline__ void upd_load(const T *__restrict__ p, T (&x)[LD]) {
+  constexpr int E = 16 / (int)sizeof(T);
+  if constexpr (LD % E == 0) {
+    typedef T V __attribute__((ext_vector_type(E)));
+#pragma unroll
+    for (int v = 0; v < LD / E; ++v) {
+      const V q = reinterpret_cast<const V *>(p)[v];
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[v * E + e] = q[e];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < LD; ++c) x[c] = p[c];
+  }
+}
+template <typename T, int M, int LD>
+__device__ __forceinline__ void upd_store(T *p, const double (&x)[M]) {
+  constexpr int E = 16 / (int)sizeof(T);
+  if constexpr (LD % E == 0) {
+    typedef T V __attribute__((ext_vector_type(E)));
+#pragma unroll
+    for (int v = 0; v < LD / E; ++v) {
+      V q;
+#pragma unroll
+      for (int e = 0; e < E; ++e) q[e] = v * E + e < M ? T(x[v * E + e < M ? v * E + e : 0]) : T(0);
+      reinterpret_cast<V *>(p)[v] = q;
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < LD; ++c) p[c] = c < M ? T(x[c < M ? c : 0]) : T(0);
+  }
+}
+
+template <typename T, int M, int LD>
 __global__ __launch_bounds__(256) void k_update(T *X, const T *__restrict__ H, T *P,
                                                 const T *__restrict__ LH, T *LP,
                                                 const double *__restrict__ Y, UpdDev a) {
+  constexpr bool kPhased = sizeof(T) == 4 || LD != M, kFront = !kPhased && M <= 8;
   const bool write_p = a.use_h || a.use_p;
   const bool lp_too = a.update_lp;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n;
-       i += (int64_t)gridDim.x * 256) {
-    const int64_t o = i * a.ld;
-    T xr[M], hr[M], pr[M], lh[M], lp[M];
+  // s += sum over the active columns k of v_k Y[off + pos_k], in increasing k
+  auto add = [&](double (&s)[M], const T (&v)[LD], int off) {
 #pragma unroll
-    for (int c = 0; c < M; ++c) xr[c] = X[o + c];
-    if (a.use_h) {
+    for (int k = 0; k < M; ++k)
+      if (a.pos[k] >= 0) {
+        const double *y = Y + (off + a.pos[k]) * kMaxNev;
+        const double vd = double(v[k]);
 #pragma unroll
-      for (int c = 0; c < M; ++c) hr[c] = H[o + c];
-      if (lp_too)
+        for (int c = 0; c < M; ++c) s[c] = fma(vd, y[c], s[c]);
+      }
+  };
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.n) return;
+  const int64_t o = i * LD;
+  T xr[LD], hr[LD], pr[LD], lh[LD], lp[LD];
+  double p[M], x[M];
+  auto load_l = [&]() {
+    if (a.use_h) upd_load<T, LD>(LH + o, lh);
+    if (a.use_p) upd_load<T, LD>(LP + o, lp);
+  };
+  if constexpr (!kPhased) upd_load<T, LD>(X + o, xr);
+  if (a.use_h) upd_load<T, LD>(H + o, hr);
+  if (a.use_p) upd_load<T, LD>(P + o, pr);
+  if (kFront && lp_too) load_l();
 #pragma unroll
-        for (int c = 0; c < M; ++c) lh[c] = LH[o + c];
-    }
-    if (a.use_p) {
+  for (int c = 0; c < M; ++c) p[c] = x[c] = 0.0;
+  if (a.use_h) add(p, hr, a.offH);
+  if (a.use_p) add(p, pr, a.offP);
+  if constexpr (kPhased) {
+    __builtin_amdgcn_sched_barrier(0);
+    upd_load<T, LD>(X + o, xr);
+  }
 #pragma unroll
-      for (int c = 0; c < M; ++c) pr[c] = P[o + c];
-      if (lp_too)
+  for (int k = 0; k < M; ++k) {
+    const double v = double(xr[k]);
 #pragma unroll
-        for (int c = 0; c < M; ++c) lp[c] = LP[o + c];
-    }
-    double p[M], l[M], x[M];
+    for (int c = 0; c < M; ++c) x[c] = fma(v, Y[k * kMaxNev + c], x[c]);
+  }
 #pragma unroll
-    for (int c = 0; c < M; ++c) p[c] = l[c] = x[c] = 0.0;
-    auto add = [&](const double *y, T v, T lv) {
-      const double vd = double(v), ld = double(lv);
+  for (int c = 0; c < M; ++c) x[c] += p[c];
+  upd_store<T, M, LD>(X + o, x);
+  if (write_p) upd_store<T, M, LD>(P + o, p);
+  if constexpr (kPhased) __builtin_amdgcn_sched_barrier(0);
+  if (lp_too) {
+    double l[M];
 #pragma unroll
-      for (int c = 0; c < M; ++c) p[c] = fma(vd, y[c], p[c]);
-      if (lp_too)
-#pragma unroll
-        for (int c = 0; c < M; ++c) l[c] = fma(ld, y[c], l[c]);
-    };
-    if (a.use_h)
-#pragma unroll
-      for (int k = 0; k < M; ++k)
-        if (a.pos[k] >= 0) add(Y + (a.offH + a.pos[k]) * kMaxNev, hr[k], lp_too ? lh[k] : T(0));
-    if (a.use_p)
-#pragma unroll
-      for (int k = 0; k < M; ++k)
-        if (a.pos[k] >= 0) add(Y + (a.offP + a.pos[k]) * kMaxNev, pr[k], lp_too ? lp[k] : T(0));
-#pragma unroll
-    for (int k = 0; k < M; ++k) {
-      const double v = double(xr[k]);
-#pragma unroll
-      for (int c = 0; c < M; ++c) x[c] = fma(v, Y[k * kMaxNev + c], x[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < M; ++c) X[o + c] = T(x[c] + p[c]);
-    if (write_p) {
-#pragma unroll
-      for (int c = 0; c < M; ++c) P[o + c] = T(p[c]);
-      if (lp_too)
-#pragma unroll
-        for (int c = 0; c < M; ++c) LP[o + c] = T(l[c]);
-    }
+    for (int c = 0; c < M; ++c) l[c] = 0.0;
+    if constexpr (!kFront) load_l();
+    if (a.use_h) add(l, lh, a.offH);
+    if (a.use_p) add(l, lp, a.offP);
+    upd_store<T, M, LD>(LP + o, l);
   }
 }
 
@@ -1306,8 +1350,6 @@ int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
                   const UpdateArgs &a, hipStream_t s) {
   UpdDev d;
   d.n = a.n;
-  d.m = a.m;
-  d.ld = a.ld;
   const int na = a.act.count;
   for (int c = 0; c < kMaxNev; ++c) d.pos[c] = -1;
   for (int q = 0; q < na; ++q) d.pos[a.act.col[q]] = q;
@@ -1316,12 +1358,20 @@ int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
   d.offH = a.m;
   d.offP = a.m + (d.use_h ? na : 0);
   d.update_lp = LP != nullptr && (d.use_h || d.use_p);
-  if (a.m < 1 || a.m > a.ld) return SPHX_E_INVALID_ARG;
-  const unsigned gb = grid_for(a.n, 256, 1 << 16);
-#define SPHX_UPD(M_)                                                                        \
-  case M_:                                                                                  \
-    hipLaunchKernelGGL((k_update<T, M_>), dim3(gb), dim3(256), 0, s, X, H, P, LH, LP, Y, d); \
-    break;
+  const unsigned gb = (unsigned)ceil_div(a.n, 256);   // n < 2^31
+  auto go = [&](auto m, auto ld) {
+    hipLaunchKernelGGL((k_update<T, decltype(m)::value, decltype(ld)::value>), dim3(gb),
+                       dim3(256), 0, s, X, H, P, LH, LP, Y, d);
+  };
+#define SPHX_UPD(M_)                                                                \
+  case M_: {                                                                        \
+    constexpr int kExact = M_ < 2 ? 2 : M_, kPadded = padded_ld(M_, sizeof(T));     \
+    const std::integral_constant<int, M_> m;                                        \
+    if (a.ld == kExact) go(m, std::integral_constant<int, kExact>{});               \
+    else if (a.ld == kPadded) go(m, std::integral_constant<int, kPadded>{});        \
+    else return SPHX_E_INVALID_ARG;                                                 \
+    break;                                                                          \
+  }
   switch (a.m) {
     SPHX_UPD(1) SPHX_UPD(2) SPHX_UPD(3) SPHX_UPD(4) SPHX_UPD(5) SPHX_UPD(6) SPHX_UPD(7)
     SPHX_UPD(8) SPHX_UPD(9) SPHX_UPD(10) SPHX_UPD(11) SPHX_UPD(12) SPHX_UPD(13) SPHX_UPD(14)

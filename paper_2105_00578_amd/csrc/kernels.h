@@ -144,7 +144,7 @@ template <typename T>
 int spmm_cheb(sphx_graph *g, const SpmmPlan &plan, const T *X, EpiChebP<T> epi, hipStream_t s);
 
 // Row width padded to whole 16-byte vectors.
-inline int padded_ld(int m, int elem_bytes) {
+constexpr int padded_ld(int m, int elem_bytes) {
   const int e = 16 / elem_bytes;
   return (m + e - 1) / e * e;
 }
@@ -240,8 +240,9 @@ struct UpdateArgs {
   ColMap act;
   int use_h, use_p;
 };
-// SPHX_E_INVALID_ARG unless 1 <= m <= ld.  With LP non-null, LP is updated along with P from LH and
-// LP (otherwise the caller forms L P by a product).
+// SPHX_E_INVALID_ARG unless ld is one that block_ld gives for m.  The padding of
+// the updated blocks is set to zero.  With LP non-null, LP is updated along with
+// P from LH and LP (otherwise the caller forms L P by a product).
 template <typename T>
 int launch_update(T *X, const T *H, T *P, const T *LH, T *LP, const double *Y,
                   const UpdateArgs &a, hipStream_t s);

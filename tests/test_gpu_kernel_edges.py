@@ -325,3 +325,40 @@ def test_cut_from_chunk_to_chunk_vs_numpy(handle, wd):
         want = float(cross.sum()) if w is None else float(w[cross].sum())
         cut, _, _, pw = sx.quality(handle, G, torch.from_numpy(part).cuda(), 7)
         assert cut == want and pw == np.bincount(part, minlength=7).tolist()
+
+
+@pytest.mark.parametrize("nev", range(1, 17))
+@pytest.mark.parametrize("kind", ["short", "long"])
+def test_solver_widths_vs_dense(handle, kind, nev):
+    """Blocks of every width, with exactly their columns (rows of at most 4
+    neighbours) and padded (20 to 30 neighbours), 257 rows, so that the update
+    has a block of one row.  Each value lies within its residual of an
+    eigenvalue (Weinstein), and the solver stops at
+    ||r|| <= tol max(theta, theta_1): that bound against the dense values, plus
+    the rounding of an FP32 product (2^-20 of ||L||) in mixed precision.  (One
+    vector: the value is 0, and no residual is small beside that.)"""
+    import graphgen
+    import paper_2105_00578_amd as sx
+    from tests.gpu_util import upload
+    n, rng = 257, np.random.default_rng(nev)
+    i = np.arange(n)
+    if kind == "short":
+        u, v = np.concatenate([i[:-1], i[:-16]]), np.concatenate([i[1:], i[16:]])
+    else:
+        u = np.repeat(i, 12)
+        v = (u + 1 + np.tile(np.arange(12) ** 2, n)) % n
+    w = 0.5 + rng.random(u.size)
+    g = graphgen.csr_from_edges(n, u, v, w)
+    L = np.zeros((n, n))
+    np.add.at(L, (np.repeat(i, np.diff(g.rowptr)), g.col), -g.w)
+    L[i, i] = -L.sum(axis=1)
+    ref = np.linalg.eigvalsh(L)
+    G = sx.Graph(handle, *upload(g))
+    for prec, tol in ((sx.FP64, 1e-7), (sx.MIXED, 1e-4)):
+        opts = sx.options_default(True, sx.PRECOND_JACOBI, precision=prec, tol=tol, max_iter=3000)
+        lam, V, st = sx.eigensolve(handle, G, nev, opts, allow_not_converged=nev == 1)
+        scale = np.maximum(ref[:nev], ref[min(1, nev - 1)])
+        slack = 1e-12 if prec == sx.FP64 else 2.0 ** -20 * ref[-1]
+        assert np.all(np.abs(np.array(lam) - ref[:nev]) <= 1.01 * tol * np.abs(scale) + slack)
+        x = V.double().cpu().numpy()
+        assert np.allclose(x.T @ x, np.eye(nev), atol=1e-9 if prec == sx.FP64 else 1e-4)
