@@ -322,9 +322,9 @@ int sphx_quality_noalloc(sphx_handle *h, sphx_graph *g, const int32_t *part, int
  *     (W / K)(1 + eps) (departures are not credited);
  *  4. accepted movers take their targets.
  * A pass is kept only when the exact cut drops; passes repeat while it does,
- * at most max_passes.  All sums are exact (float weights in 128-bit fixed
- * point, ratio of weights at most 2^40), so the result does not depend on
- * the order of the additions.
+ * at most max_passes.  All sums are exact (float weights in fixed point of 64
+ * bits where their range fits, else 128; ratio of weights at most 2^40), so the
+ * result does not depend on the order of the additions.
  * part: device int32[n] with values in [0, K), refined in place.
  * eps >= 0.  cut, imbalance (host, may be NULL): of the returned partition,
  * as in sphx_quality.  passes (host, may be NULL): passes kept.  moves
